@@ -437,7 +437,16 @@ __global__ __launch_bounds__(256) void k_embed_absmax(const float* __restrict__ 
   if (tail0 + tid < n) m = max(m, __float_as_uint(dOut[tail0 + tid]) & 0x7fffffffu);
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, d, 64));
-  if ((threadIdx.x & 63) == 0 && m != 0u) atomicMax(&fs->absmax_bits, m);
+  __shared__ uint32_t s_m[4];
+  if ((threadIdx.x & 63) == 0) s_m[threadIdx.x >> 6] = m;
+  __syncthreads();
+  // Atomics on one address complete one after the other (12 ns each: one per wave of 2048 workgroups
+  // took 100 us whatever the size of dOut): one per workgroup, and none where the maximum found
+  // so far is as large already.
+  if (threadIdx.x == 0) {
+    m = max(max(s_m[0], s_m[1]), max(s_m[2], s_m[3]));
+    if (m > __hip_atomic_load(&fs->absmax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&fs->absmax_bits, m);
+  }
 }
 
 // 2^shift as a double; NaN when dOut holds an Inf or NaN (the result is then NaN everywhere).
