@@ -353,7 +353,13 @@ roast_status launch_embed(const EmbedArgs& a, const int64_t* rows, const uint32_
 //              with global atomics -- R adds per workgroup instead of Z adds per chunk.
 // Needs Z % 4 == 0, D % Z == 0, C <= kMaxC, |M| < 2^31 and at most kMaxBuckets buckets of at most
 // kMaxR slots; other shapes use the direct atomic kernel above.
-constexpr int kSeg = 8192;          // chunks per accumulate workgroup
+// Values per accumulate workgroup (kSegValues / Z chunks).  A short segment costs one more flush of the
+// image (4096 adds), a long one leaves a few workgroups running at the end, and with small batches
+// too few workgroups altogether: 1024 against 8192 chunks of 32 took 230 against 249 us on 6.8 M chunks
+// over 313 buckets and 70 against 93 us (pooled, both passes) on 0.85 M.
+constexpr int kSegValues = 32768;
+constexpr int kListSlack = 8192;    // list capacity beyond twice the mean load
+constexpr int kAccThreads = 256;
 constexpr int kMaxBuckets = 2048;
 constexpr int kMaxR = 8192;         // largest bucket (slots); its fp64 LDS image is (kMaxR + Z) * 8 bytes, up to 72 KiB
 constexpr int kRouteItems = 8192;   // chunks per route workgroup (lookups per workgroup = kRouteItems / C)
@@ -381,7 +387,7 @@ inline BucketPlan bucket_plan(const EmbedArgs& a) {
   p.nb = (int)((a.m_size + (1ll << r) - 1) >> r);
   if (p.nb > kMaxBuckets) { p.ok = false; return p; }
   // twice the mean load plus one segment: uniform hashing stays far below, skewed ids mostly too
-  p.cap = (uint32_t)(2 * (p.n_items / p.nb) + kSeg);
+  p.cap = (uint32_t)(2 * (p.n_items / p.nb) + kListSlack);
   auto up = [](size_t v) { return (v + 255) / 256 * 256; };
   size_t o = 0;
   p.cursor_off = o; o += up((size_t)p.nb * 4);
@@ -499,7 +505,7 @@ __global__ __launch_bounds__(256) void k_embed_fixed_finish(int64_t m_size, floa
 
 // entry = (chunk number g, key); key = offset | (negative sign << 31)
 template <bool FIXED>
-__global__ __launch_bounds__(kRouteThreads) void k_embed_route(EmbedArgs a, int r_log2, int nb, uint32_t cap, int walk,
+__global__ __launch_bounds__(kRouteThreads) void k_embed_route(EmbedArgs a, int r_log2, int nb, uint32_t cap, int walk, int items,
                                                      const int64_t* __restrict__ rows,
                                                      const uint32_t* __restrict__ tables, uint32_t* __restrict__ cursor,
                                                      uint2* __restrict__ list, const float* __restrict__ dOut,
@@ -507,8 +513,7 @@ __global__ __launch_bounds__(kRouteThreads) void k_embed_route(EmbedArgs a, int 
                                                      unsigned long long* __restrict__ acc) {
   extern __shared__ __attribute__((aligned(16))) uint32_t s_route[];
   const int C = (int)a.C;
-  const int rows_wg = kRouteItems / C;
-  constexpr int items = kRouteItems;
+  const int rows_wg = items / C;
   uint32_t* s_key = s_route;                                       // [items]
   uint16_t* s_pos = reinterpret_cast<uint16_t*>(s_key + items);   // [items] rank inside (workgroup, bucket)
   uint32_t* hist = s_key + items + items / 2;                      // [nb]  chunks of this workgroup per bucket
@@ -591,7 +596,7 @@ __global__ __launch_bounds__(kRouteThreads) void k_embed_route(EmbedArgs a, int 
 }
 
 template <bool FIXED>
-__global__ __launch_bounds__(256) void k_embed_accum(EmbedArgs a, int r_log2, uint32_t cap, int segs_per_bucket,
+__global__ __launch_bounds__(kAccThreads) void k_embed_accum(EmbedArgs a, int r_log2, uint32_t cap, int nb, uint32_t seg_len,
                                                      const uint32_t* __restrict__ cursor, const uint2* __restrict__ list,
                                                      const float* __restrict__ dOut, float* __restrict__ dM, int pbits,
                                                      const FixedScale* fs, unsigned long long* __restrict__ acc) {
@@ -602,18 +607,21 @@ __global__ __launch_bounds__(256) void k_embed_accum(EmbedArgs a, int r_log2, ui
   img_t* img = reinterpret_cast<img_t*>(img_raw);   // R + Z slots
   double scale = 0.0;
   if constexpr (FIXED) scale = fixed_scale(fs, a.lambda, pbits);
-  const int b = blockIdx.x / segs_per_bucket, seg = blockIdx.x % segs_per_bucket;
+  // Workgroup numbers run over the buckets first: the lists have room for about twice their mean load,
+  // so most of the later segments are empty, and with the segments of a bucket next to one another
+  // the occupied ones would be every 2nd or 4th workgroup -- all on the same few XCDs.
+  const int b = blockIdx.x % nb, seg = blockIdx.x / nb;
   const uint32_t count = min(cursor[b], cap);
-  const uint32_t first = (uint32_t)seg * kSeg;
+  const uint32_t first = (uint32_t)seg * seg_len;
   if (first >= count) return;
-  const uint32_t end = min(count, first + kSeg);
+  const uint32_t end = min(count, first + seg_len);
   const uint2* lst = list + (size_t)b * cap;
   const int R = 1 << r_log2, span = R + a.Z;
   const int64_t slot0 = (int64_t)b << r_log2;
-  for (int i = threadIdx.x; i < span; i += 256) img[i] = img_t(0);
+  for (int i = threadIdx.x; i < span; i += kAccThreads) img[i] = img_t(0);
   __syncthreads();
   const int lpi = a.Z / 4;                       // lanes per chunk
-  const int ipp = 256 / lpi;                     // chunks per pass of the workgroup (Z <= 1024)
+  const int ipp = kAccThreads / lpi;                      // chunks per pass of the workgroup (Z <= 1024)
   const int sub = threadIdx.x % lpi, which = threadIdx.x / lpi;
   // Several chunks per thread in flight: the list entry and then the dOut chunk it points at are
   // dependent loads, so the entries of the next batch are fetched while this batch's chunks load.
@@ -642,7 +650,7 @@ __global__ __launch_bounds__(256) void k_embed_accum(EmbedArgs a, int r_log2, ui
     const int lane = threadIdx.x & 63;
     auto fetch_one = [&](uint32_t i) { return i < end ? lst[i] : make_uint2(0u, 0xffffffffu); };
     uint2 nxt = fetch_one(first + threadIdx.x);
-    for (uint32_t i0 = first; i0 < end; i0 += 256) {       // uniform trip count for the workgroup
+    for (uint32_t i0 = first; i0 < end; i0 += kAccThreads) {       // uniform trip count for the workgroup
       const uint2 mine = nxt;
       uint2 e[U];
       vfloat4 d[U];
@@ -654,7 +662,7 @@ __global__ __launch_bounds__(256) void k_embed_accum(EmbedArgs a, int r_log2, ui
         const uint32_t chunk = e[u].y != 0xffffffffu ? e[u].x : 0u;
         d[u] = __builtin_nontemporal_load(reinterpret_cast<const vfloat4*>(dOut + (int64_t)chunk * a.Z) + sub);
       }
-      nxt = fetch_one(i0 + 256 + threadIdx.x);
+      nxt = fetch_one(i0 + kAccThreads + threadIdx.x);
 #pragma unroll
       for (int u = 0; u < U; ++u) add_chunk(e[u], d[u]);
     }
@@ -684,7 +692,7 @@ __global__ __launch_bounds__(256) void k_embed_accum(EmbedArgs a, int r_log2, ui
   }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < span; i += 256) {
+  for (int i = threadIdx.x; i < span; i += kAccThreads) {
     if constexpr (FIXED) {
       const unsigned long long v = img[i];
       if (v != 0ull && slot0 + i < a.m_size) atomicAdd(acc + slot0 + i, v);
@@ -717,8 +725,12 @@ roast_status bucket_run(const EmbedArgs& a, const BucketPlan& p, const int64_t* 
   uint32_t* cursor = (uint32_t*)(base + p.cursor_off);
   uint2* list = (uint2*)(base + p.list_off);
   hipLaunchKernelGGL(k_embed_zero, dim3((p.nb + 255) / 256), dim3(256), 0, s, cursor, (int64_t)p.nb);
-  const int rows_wg = kRouteItems / (int)a.C;
-  const size_t lds_route = (size_t)kRouteItems * (4 + 2 + 2) + (size_t)3 * p.nb * 4 + (a.bag_off ? (size_t)rows_wg * 4 : 0);
+  // Chunks per route workgroup: 8192 (long runs per bucket, few reservations) once that leaves a
+  // workgroup for every CU, fewer for smaller batches (0.85 M chunks: 2048 instead of 8192, -9 us).
+  int items = kRouteItems;
+  while (items > 2048 && p.n_items / items < 256) items /= 2;
+  const int rows_wg = items / (int)a.C;
+  const size_t lds_route = (size_t)items * (4 + 2 + 2) + (size_t)3 * p.nb * 4 + (a.bag_off ? (size_t)rows_wg * 4 : 0);
   static std::atomic<bool> configured{false};   // per instantiation; a race between host threads only repeats the call
   if (!configured.load(std::memory_order_acquire)) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_embed_route<FIXED>),
@@ -732,11 +744,12 @@ roast_status bucket_run(const EmbedArgs& a, const BucketPlan& p, const int64_t* 
     configured.store(true, std::memory_order_release);
   }
   hipLaunchKernelGGL(k_embed_route<FIXED>, dim3((unsigned)((a.N + rows_wg - 1) / rows_wg)), dim3(kRouteThreads), lds_route, s, a,
-                     p.r_log2, p.nb, p.cap, walk_ok(a), rows, tables, cursor, list, dOut, dM, pbits, fs, acc);
-  const int segs = (int)((p.cap + kSeg - 1) / kSeg);
+                     p.r_log2, p.nb, p.cap, walk_ok(a), items, rows, tables, cursor, list, dOut, dM, pbits, fs, acc);
+  const int seg_len = kSegValues / a.Z;
+  const int segs = (int)((p.cap + seg_len - 1) / seg_len);
   const size_t lds = ((size_t)(1 << p.r_log2) + a.Z) * 8;
-  hipLaunchKernelGGL(k_embed_accum<FIXED>, dim3((unsigned)(p.nb * segs)), dim3(256), lds, s, a, p.r_log2, p.cap, segs,
-                     cursor, list, dOut, dM, pbits, fs, acc);
+  hipLaunchKernelGGL(k_embed_accum<FIXED>, dim3((unsigned)(p.nb * segs)), dim3(kAccThreads), lds, s, a, p.r_log2, p.cap, p.nb,
+                     (uint32_t)seg_len, cursor, list, dOut, dM, pbits, fs, acc);
   return hip_status(hipGetLastError());
 }
 
