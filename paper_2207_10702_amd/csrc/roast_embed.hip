@@ -6,8 +6,6 @@
 // the part of the hash that depends on (table, row) is computed once and the chunk index is walked
 // incrementally.  With Z = 32 and VEC = 4, eight lanes serve a chunk and one step of a wave moves
 // 1 KiB of contiguous output.
-#include <stdlib.h>
-
 #include <algorithm>
 #include <atomic>
 #include <type_traits>
@@ -61,8 +59,8 @@ __device__ inline int64_t grad_row(const EmbedArgs& a, int64_t n) { return a.bag
 // Streaming lookup / direct-atomic gradient.  A wave takes 64 lookups: each lane hashes the chunks
 // of one lookup into the wave's LDS key list (offset | sign bit, 32-bit), then the wave walks the
 // 64*C chunks in order, LPI lanes per chunk, VEC floats per lane.
-// VEC = 4 requires Z % 4 == 0 and D % Z == 0 (then every chunk is full and out is 16-byte aligned
-// per lane, given a 16-byte aligned base).  Needs |M| < 2^31 and C <= kMaxC.
+// VEC = 4 (forward only) requires Z % 4 == 0 and D % Z == 0 (then every chunk is full and out is 16-byte
+// aligned per lane, given a 16-byte aligned base).  Needs |M| < 2^31 and C <= kMaxC.
 constexpr int kMaxC = 16;
 
 // slices > 1 (forward only; 2, 4 or 8): M is larger than one XCD's L2, so the gathered reads would
@@ -74,8 +72,9 @@ template <int VEC, bool BWD>
 __global__ __launch_bounds__(256) void k_embed(EmbedArgs a, int lpi_log2, int walk, const int64_t* __restrict__ rows,
                                                const uint32_t* __restrict__ tables, const float* __restrict__ M,
                                                float* __restrict__ out, const float* __restrict__ dOut,
-                                               float* __restrict__ dM, int slices) {
+                                               float* __restrict__ dM, int slices, int rows_wave) {
   extern __shared__ uint32_t s_keys[];           // [4 waves][64 * C] keys, then [4 waves][64 * C] selected chunk numbers (16 bit)
+  __shared__ int64_t s_src[BWD ? 4 * 64 : 1];    // gradient row of each lookup
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int C = (int)a.C;
   uint32_t* keys = s_keys + wv * 64 * C;
@@ -84,11 +83,12 @@ __global__ __launch_bounds__(256) void k_embed(EmbedArgs a, int lpi_log2, int wa
   const int slice = (int)(blockIdx.x & 7) / per;
   const int64_t lblock = slices == 1 ? (int64_t)blockIdx.x : (int64_t)(blockIdx.x >> 3) * per + (blockIdx.x & (per - 1));
   const int64_t wave = lblock * 4 + wv;
-  const int64_t n0 = wave * 64;
+  const int64_t n0 = wave * rows_wave;
   if (n0 >= a.N) return;
-  const int rows_here = (int)min((int64_t)64, a.N - n0);
+  const int rows_here = (int)min((int64_t)rows_wave, a.N - n0);
   if (lane < rows_here) {
     const int64_t n = n0 + lane;
+    if (BWD) s_src[wv * 64 + lane] = grad_row(a, n);
     for_each_chunk(a, walk != 0, tables[n], (uint64_t)rows[n], [&](int64_t c, int64_t off, int sgn) {
       keys[lane * C + c] = (uint32_t)off | (sgn < 0 ? 0x80000000u : 0u);
     });
@@ -150,21 +150,12 @@ __global__ __launch_bounds__(256) void k_embed(EmbedArgs a, int lpi_log2, int wa
     const int64_t g = g0 + j;
     const int64_t n = g / C, c = g - n * C;
     const int len = (int)min((int64_t)a.Z, a.D - c * a.Z);   // last chunk of a row may be short
-    const int64_t obase = (BWD ? grad_row(a, n) : n) * a.D + c * a.Z;
+    const int64_t obase = (BWD ? s_src[wv * 64 + (int)(n - n0)] : n) * a.D + c * a.Z;
     for (int o = sub * VEC; o < len; o += lpi * VEC) {
-      if (VEC == 4) {
-        if (!BWD) {
-          const f4u m = *reinterpret_cast<const f4u*>(M + off + o);
-          vfloat4 v = {scale * m.v[0], scale * m.v[1], scale * m.v[2], scale * m.v[3]};
-          __builtin_nontemporal_store(v, reinterpret_cast<vfloat4*>(out + obase + o));
-        } else {
-          const vfloat4 d = __builtin_nontemporal_load(reinterpret_cast<const vfloat4*>(dOut + obase + o));
-          float* p = dM + off + o;
-          unsafeAtomicAdd(p + 0, scale * d.x);
-          unsafeAtomicAdd(p + 1, scale * d.y);
-          unsafeAtomicAdd(p + 2, scale * d.z);
-          unsafeAtomicAdd(p + 3, scale * d.w);
-        }
+      if constexpr (VEC == 4) {
+        const f4u m = *reinterpret_cast<const f4u*>(M + off + o);
+        const vfloat4 v = {scale * m.v[0], scale * m.v[1], scale * m.v[2], scale * m.v[3]};
+        __builtin_nontemporal_store(v, reinterpret_cast<vfloat4*>(out + obase + o));
       } else {
         if (!BWD) {
           __builtin_nontemporal_store(scale * M[off + o], out + obase + o);
@@ -314,16 +305,25 @@ roast_status launch_embed(const EmbedArgs& a, const int64_t* rows, const uint32_
     hipLaunchKernelGGL((k_embed_elem<BWD>), dim3((unsigned)blocks), dim3(256), 0, s, a, rows, tables, M, out, dOut, dM);
     return hip_status(hipGetLastError());
   }
-  const int64_t waves = (a.N + 63) / 64;
-  int64_t blocks = (waves + 3) / 4;
-  const void* io = BWD ? (const void*)dOut : (const void*)out;
-  const bool vec4 = (a.Z % 4 == 0) && (a.D % a.Z == 0) && (((uintptr_t)io & 15) == 0);
+  // The gradient takes one value per lane: the chip serves atomic adds by the 64-byte piece of a wave
+  // instruction (18.7 G pieces/s, however many of its 16 slots are added to), so an instruction has to
+  // cover consecutive slots.  Four values per lane -- slots 16 bytes apart in one instruction -- ran at
+  // 0.08 T adds/s instead of 0.2-0.3: 62 400 chunks of 32 took 54 us, now 18.
+  const bool vec4 = !BWD && (a.Z % 4 == 0) && (a.D % a.Z == 0) && (((uintptr_t)out & 15) == 0);
   const int per_lane = vec4 ? 4 : 1;
   int lpi_log2 = 0;
   while ((1 << lpi_log2) < 64 && (int64_t)(1 << lpi_log2) * per_lane < a.Z) ++lpi_log2;
   // forward over an M that does not fit one XCD's L2 (4 MiB): four slices (measured on a 5 MiB M:
   // 171 us unsliced, 158 / 144 / 189 us with 2 / 4 / 8 slices -- every slice hashes all lookups),
   // eight once a quarter is too large; not for small calls, nor once even an eighth does not fit
+  // Lookups per wave: 64 (one per lane) once the call fills the chip with full waves; below that fewer,
+  // so that a small call spreads over up to 8192 waves (32 per CU) instead of walking 64 lookups'
+  // chunks one group after the other in a few waves -- but never fewer than one step of the wave
+  // serves (64 >> lpi_log2 chunks).  2028 lookups of 8 chunks, gradient: 32 -> 14 us.
+  int rows_wave = 64;
+  while (rows_wave > 1 && (a.N + rows_wave / 2 - 1) / (rows_wave / 2) <= 8192 && (rows_wave / 2) * a.C >= (64 >> lpi_log2)) rows_wave /= 2;
+  const int64_t waves = (a.N + rows_wave - 1) / rows_wave;
+  int64_t blocks = (waves + 3) / 4;
   int slices = 1;
   if (!BWD && vec4 && a.N * a.C >= 65536) {
     const int64_t bytes = a.m_size * 4, fit = 3584 * 1024;
@@ -333,10 +333,13 @@ roast_status launch_embed(const EmbedArgs& a, const int64_t* rows, const uint32_
   if (blocks > 0x7fffffffll) return ROAST_ERR_UNSUPPORTED;
   const dim3 g((unsigned)blocks), b(256);
   const size_t lds = (size_t)4 * 64 * a.C * (sizeof(uint32_t) + sizeof(uint16_t));
-  if (vec4)
-    hipLaunchKernelGGL((k_embed<4, BWD>), g, b, lds, s, a, lpi_log2, walk_ok(a), rows, tables, M, out, dOut, dM, slices);
-  else
-    hipLaunchKernelGGL((k_embed<1, BWD>), g, b, lds, s, a, lpi_log2, walk_ok(a), rows, tables, M, out, dOut, dM, slices);
+  if constexpr (!BWD) {
+    if (vec4) {
+      hipLaunchKernelGGL((k_embed<4, false>), g, b, lds, s, a, lpi_log2, walk_ok(a), rows, tables, M, out, dOut, dM, slices, rows_wave);
+      return hip_status(hipGetLastError());
+    }
+  }
+  hipLaunchKernelGGL((k_embed<1, BWD>), g, b, lds, s, a, lpi_log2, walk_ok(a), rows, tables, M, out, dOut, dM, slices, rows_wave);
   return hip_status(hipGetLastError());
 }
 
@@ -753,8 +756,11 @@ roast_status bucket_run(const EmbedArgs& a, const BucketPlan& p, const int64_t* 
   return hip_status(hipGetLastError());
 }
 
-inline bool bucket_worthwhile(const BucketPlan& p, const float* dOut) {
-  return p.ok && p.n_items >= 65536 && ((uintptr_t)dOut & 15) == 0;
+// Below about 2.5 M values the direct adds (0.2 T/s: 12 us) are done before the three kernels of the
+// pipeline are (62 400 chunks of 32: 18 against 23 us, 104 000: 29 against 27); the fixed-point mode's
+// direct kernel hashes every element, so there the line stays lower.
+inline bool bucket_worthwhile(const BucketPlan& p, int64_t z, bool fixed, const float* dOut) {
+  return p.ok && p.n_items >= 65536 && (fixed || p.n_items * z >= 2500000) && ((uintptr_t)dOut & 15) == 0;
 }
 
 struct DetLayoutE {
@@ -778,7 +784,7 @@ roast_status embed_bwd_atomic_launch(const EmbedArgs& a, const int64_t* rows, co
                                      const float* dOut, float* dM, void* ws, size_t ws_bytes, hipStream_t s) {
   const BucketPlan p = bucket_plan(a);
   // small problems, odd shapes, or no workspace: plain atomics straight into dM
-  if (!bucket_worthwhile(p, dOut) || ws == nullptr || ws_bytes < p.total)
+  if (!bucket_worthwhile(p, a.Z, false, dOut) || ws == nullptr || ws_bytes < p.total)
     return launch_embed<true>(a, rows, tables, nullptr, nullptr, dOut, dM, s);
   return bucket_run<false>(a, p, rows, tables, dOut, dM, (char*)ws, 0, nullptr, nullptr, s);
 }
@@ -810,7 +816,7 @@ roast_status embed_bwd_det_run(const EmbedArgs& a, const int64_t* rows, const ui
   hipLaunchKernelGGL(k_embed_absmax, dim3((unsigned)ab), dim3(256), 0, s, dOut, n_grad, fs);
   const BucketPlan p = bucket_plan(a);
   roast_status st;
-  if (bucket_worthwhile(p, dOut)) {
+  if (bucket_worthwhile(p, a.Z, true, dOut)) {
     st = bucket_run<true>(a, p, rows, tables, dOut, dM, base + l.bucket_off, pbits, fs, acc, s);
   } else {
     const int64_t blocks = (n_el + 255) / 256;
