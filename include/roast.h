@@ -152,7 +152,8 @@ roast_status roast_chunk_index_device(const roast_embed_desc* d, int64_t N, cons
  * from this copy gives bit-identical results with half the weight traffic.  Make it once per update
  * of M and pass it to as many roast_mm_fwd / roast_mm_bwd_dx calls as share that M.
  * The buffer holds two copies, the second shifted by one element, so that a tile at an odd offset
- * can be read with dword-aligned loads as well; its layout is private to the library.
+ * can be read with dword-aligned loads as well, and for a small M both again with every sign
+ * flipped, so that a tile of negative sign is read as it is used; its layout is private to the library.
  * shadow: DEVICE buffer of roast_m_shadow_bytes(m_size) bytes, 16-byte aligned, owned by the caller.
  */
 size_t roast_m_shadow_bytes(int64_t m_size);

@@ -108,7 +108,7 @@ roast_status roast_chunk_index_device(const roast_embed_desc* d, int64_t N, cons
 }
 
 size_t roast_m_shadow_bytes(int64_t m_size) {
-  return m_size > 0 ? (size_t)(2 * shadow_stride(m_size)) * 2 : 0;
+  return m_size > 0 ? (size_t)(shadow_copies(m_size) * shadow_stride(m_size)) * 2 : 0;
 }
 
 size_t roast_m_planes_bytes(int64_t m_size) { return m_size > 0 ? m_planes_bytes(m_size) : 0; }

@@ -122,6 +122,45 @@ __host__ __device__ inline uint32_t mod_slots32(const HashDev& h, uint32_t u) {
   return r;
 }
 
+// ---- the tile map of one layer, with everything that does not depend on the tile prepared once: an
+// offset and a sign then take four 64-bit reductions instead of fifteen.  Valid when every tile
+// coordinate is below P (fast == 1); otherwise every tile is hashed from scratch.
+struct TileHash {
+  uint32_t cu, cv;  // (a0*layer + a3) mod P, (s0*layer + s3) mod P
+  uint32_t fast;
+};
+
+inline TileHash make_tile_hash(const HashDev& h, uint64_t layer, int64_t nTx, int64_t nTy) {
+  TileHash t;
+  const uint64_t l = bmod(layer, h.P);
+  t.cu = (uint32_t)bmod(bmod(h.a0 * l, h.P) + h.a3, h.P);
+  t.cv = (uint32_t)bmod(bmod(h.s0 * l, h.P) + h.s3, h.P);
+  t.fast = (uint64_t)nTx <= h.P.d && (uint64_t)nTy <= h.P.d && h.use_sign != 2 ? 1u : 0u;
+  return t;
+}
+
+// offset of tile (x, y); *neg: whether its sign is -1 (use_sign == 0: never)
+__host__ __device__ inline int64_t tile_place(const HashDev& h, const TileHash& t, uint64_t layer, uint32_t x, uint32_t y, bool* neg) {
+  if (!t.fast) {
+    *neg = block_sign(h, layer, x, y) < 0;
+    return block_offset(h, layer, x, y);
+  }
+  const uint64_t P = h.P.d;
+  uint64_t u = t.cu + bmod(h.a1 * x, h.P);
+  if (u >= P) u -= P;
+  u += bmod(h.a2 * y, h.P);
+  if (u >= P) u -= P;
+  *neg = false;
+  if (h.use_sign == 1) {
+    uint64_t v = t.cv + bmod(h.s1 * x, h.P);
+    if (v >= P) v -= P;
+    v += bmod(h.s2 * y, h.P);
+    if (v >= P) v -= P;
+    *neg = (v & 1ull) != 0;
+  }
+  return (int64_t)((uint64_t)h.align * mod_slots32(h, (uint32_t)u));
+}
+
 // Walks k2 = 0, 1, 2, ... for one row: t2 = (a2*k2) mod P and ts = (s2*k2) mod P are advanced by
 // one add and one conditional subtract per step.  Valid while k2 < P (the caller checks C <= P).
 struct ChunkWalk {

@@ -106,7 +106,11 @@ roast_status dm_det_run(const MMArgs& a, roast_dtype dt, const void* X, int64_t 
 // ---- bf16 MFMA kernels (roast_mm_mfma.hip): return ROAST_ERR_UNSUPPORTED when the shape does not
 // meet their divisibility rules; the caller then falls back to the generic kernels.
 // M_bf16 (optional): bf16 copy of M made by shadow_bf16_launch; halves the weight traffic.
-int64_t shadow_stride(int64_t m_size);   // elements between the two copies of the bf16 shadow (a multiple of 64)
+int64_t shadow_stride(int64_t m_size);   // elements between the copies of the bf16 shadow (a multiple of 64)
+// Copies in the bf16 shadow: M, M shifted by one element, and for an M that the caches hold the same of -M, which saves
+// the wide kernels the signs.  Up to 4 Mi parameters the optimizer step takes no longer for it (26 us); at 16 Mi
+// it would take 132 us instead of 107.
+inline int shadow_copies(int64_t m_size) { return m_size <= (4ll << 20) ? 4 : 2; }
 roast_status shadow_bf16_launch(const float* M, int64_t m_size, void* shadow, hipStream_t s);
 // ws (optional): room for mfma_*_splits() fp32 partial outputs [parts][I][columns]; when given and the
 // shape has too few output tiles to fill the chip, the contraction axis is split over workgroups.
@@ -136,6 +140,24 @@ roast_status x3_mm_bwd_dM(const MMArgs& a, const float* X, int64_t ldx, const fl
 // ([splits][H][O] floats) for the deterministic reduction; `splits` must equal dm_det_splits().
 roast_status mfma_mm_bwd_dM(const MMArgs& a, const void* X, int64_t ldx, const void* dY, int64_t ldy, float* dM,
                             float* Gws, int splits, hipStream_t s);
+
+// ---- wide bf16 matrix-core kernels (roast_mm_wide.hip) with bm x bn output blocks: 256 x 256, 256 x 192,
+// 256 x 128 or 128 x 192.  The caller has checked pointers and leading dimensions (16-byte aligned, multiples
+// of 8) and, forward / dX, has a shadow (x3: planes) of M.
+// A launch of theirs (bm == 0: they do not take the shape)
+struct WidePlan {
+  int bm, bn;            // output block of a workgroup
+  int nblk;              // consecutive column blocks of a workgroup (a strip)
+  int parts, rows;       // parts of the contraction, contraction indices in each (a multiple of 64)
+};
+constexpr int kWideParts = 16;
+WidePlan wide_fwd_plan(const MMArgs& a, int max_parts, bool x3);   // max_parts: 1 where no workspace is given, else kWideParts
+WidePlan wide_dx_plan(const MMArgs& a, int max_parts, bool x3);
+WidePlan wide_dm_plan(const MMArgs& a, int parts, bool x3);        // parts == 0: atomic adds, any number of parts
+roast_status wide_mm(int which, const MMArgs& a, const WidePlan& plan, const uint16_t* A, int64_t lda, int64_t a_plane,
+                     const uint16_t* Mb, bool x3, uint16_t* C, float* C32, int64_t ldc, float* ws, hipStream_t s);
+roast_status wide_mm_dM(const MMArgs& a, const WidePlan& plan, const uint16_t* X, int64_t ldx, int64_t a_plane, const uint16_t* dY,
+                        int64_t ldy, int64_t b_plane, bool x3, float* dM, float* G, const int* split_begin, hipStream_t s);
 
 // ---- lookup kernels (roast_embed.hip)
 roast_status embed_fwd_launch(const EmbedArgs& a, const int64_t* rows, const uint32_t* tables, const float* M,

@@ -1073,15 +1073,26 @@ roast_status launch(KernArgs p, dim3 blocks, hipStream_t s) {
   return hip_status(hipGetLastError());
 }
 
-// out[i] = bf16(M[i]) and out[stride + i] = bf16(M[i + 1]), zero beyond the end of M
-__global__ __launch_bounds__(256) void k_shadow_bf16(const float* __restrict__ M, int64_t n, int64_t stride,
+// out[i] = bf16(M[i]) and out[stride + i] = bf16(M[i + 1]), zero beyond the end of M; with four copies the
+// same of -M from 2 * stride on.  Eight elements per thread, 16-byte stores (stride % 64 == 0).
+__global__ __launch_bounds__(256) void k_shadow_bf16(const float* __restrict__ M, int64_t n, int64_t stride, int copies,
                                                      uint16_t* __restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
   if (i >= stride) return;
-  const uint16_t cur = i < n ? __builtin_bit_cast(uint16_t, (__bf16)M[i]) : (uint16_t)0;
-  const uint16_t nxt = i + 1 < n ? __builtin_bit_cast(uint16_t, (__bf16)M[i + 1]) : (uint16_t)0;
-  out[i] = cur;
-  out[stride + i] = nxt;
+  float m[9];
+#pragma unroll
+  for (int q = 0; q < 9; ++q) m[q] = i + q < n ? M[i + q] : 0.f;
+  uint4v cur, nxt;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    cur[q] = pack_bf16x2(m[2 * q], m[2 * q + 1]);
+    nxt[q] = pack_bf16x2(m[2 * q + 1], m[2 * q + 2]);
+  }
+  for (int c = 0; c < copies; c += 2) {
+    const uint32_t flip = c ? 0x80008000u : 0u;
+    *reinterpret_cast<uint4v*>(out + c * stride + i) = cur ^ flip;
+    *reinterpret_cast<uint4v*>(out + (c + 1) * stride + i) = nxt ^ flip;
+  }
 }
 
 // C[r][c] = bf16(sum over the parts, in order, of G[part][r][c]); eight columns per thread
@@ -1222,9 +1233,10 @@ int64_t shadow_stride(int64_t m_size) { return shadow_stride_of(m_size); }
 
 roast_status shadow_bf16_launch(const float* M, int64_t m_size, void* shadow, hipStream_t s) {
   const int64_t stride = shadow_stride(m_size);
-  const int64_t blocks = (stride + 255) / 256;
+  const int64_t blocks = (stride / 8 + 255) / 256;
   if (blocks > 0x7fffffffll) return ROAST_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL(k_shadow_bf16, dim3((unsigned)blocks), dim3(256), 0, s, M, m_size, stride, (uint16_t*)shadow);
+  hipLaunchKernelGGL(k_shadow_bf16, dim3((unsigned)blocks), dim3(256), 0, s, M, m_size, stride, shadow_copies(m_size),
+                     (uint16_t*)shadow);
   return hip_status(hipGetLastError());
 }
 
@@ -1307,15 +1319,21 @@ int mfma_dx_strip(const MMArgs& a, bool shadow) {
   return pick_ntile(cdiv(a.I, kBM), a.H, a.Z1, a.O / BK, a.nTy);
 }
 
+// (the same with and without a shadow, so that both give the same sums)
 int mfma_fwd_splits(const MMArgs& a) {
+  const WidePlan w = wide_fwd_plan(a, kWideParts, false);
+  if (w.bm) return w.parts;
   return (mfma_fwd_ok(a) || mfma_elem_ok(a)) ? mm_pick_splits(cdiv(a.O, kBN) * cdiv(a.I, kBM), a.H) : 1;
 }
 int mfma_dx_splits(const MMArgs& a) {
+  const WidePlan w = wide_dx_plan(a, kWideParts, false);
+  if (w.bm) return w.parts;
   return (mfma_dx_ok(a) || mfma_elem_ok(a)) ? mm_pick_splits(cdiv(a.H, kBN) * cdiv(a.I, kBM), a.O) : 1;
 }
 
 roast_status mfma_mm_fwd(const MMArgs& a, const void* X, int64_t ldx, const float* M, const void* M_bf16, void* Y,
                          int64_t ldy, float* ws, hipStream_t s) {
+  const WidePlan wide = M_bf16 ? wide_fwd_plan(a, ws ? kWideParts : 1, false) : WidePlan{};
   const bool elem = !mfma_fwd_ok(a);
   if ((elem && !mfma_elem_ok(a)) || ldx % 8 != 0 || ldy % 8 != 0 || !aligned16(X) || !aligned16(Y))
     return ROAST_ERR_UNSUPPORTED;
@@ -1323,6 +1341,12 @@ roast_status mfma_mm_fwd(const MMArgs& a, const void* X, int64_t ldx, const floa
   KernArgs p{};
   p.a = a; p.A = (const uint16_t*)X; p.lda = ldx; p.M = M; p.Mb = (const uint16_t*)M_bf16;
   p.mb_stride = shadow_stride(a.m_size); p.C = (uint16_t*)Y; p.ldc = ldy;
+  if (wide.bm) {
+    if (wide.parts > 1) p.G = ws;
+    const roast_status st = wide_mm(0, a, wide, p.A, p.lda, 0, p.Mb, false, p.C, nullptr, p.ldc, ws, s);
+    if (st != ROAST_ERR_UNSUPPORTED) return st != ROAST_OK ? st : split_finish(p, (unsigned)wide.parts, a.I, a.O, s);
+    p.G = nullptr;
+  }
   dim3 grid((unsigned)cdiv(a.O, BN), (unsigned)cdiv(a.I, BM), 1);
   split_setup(&p, &grid, a.H, mfma_fwd_splits(a), ws);
   // the shadow is read in 8-column pieces, which must not straddle tiles
@@ -1351,6 +1375,7 @@ roast_status mfma_mm_fwd(const MMArgs& a, const void* X, int64_t ldx, const floa
 
 roast_status mfma_mm_bwd_dx(const MMArgs& a, const void* dY, int64_t ldy, const float* M, const void* M_bf16,
                             void* dX, int64_t ldx, float* ws, hipStream_t s) {
+  const WidePlan wide = M_bf16 ? wide_dx_plan(a, ws ? kWideParts : 1, false) : WidePlan{};
   const bool elem = !mfma_dx_ok(a);
   if ((elem && !mfma_elem_ok(a)) || ldy % 8 != 0 || ldx % 8 != 0 || !aligned16(dY) || !aligned16(dX))
     return ROAST_ERR_UNSUPPORTED;
@@ -1358,6 +1383,12 @@ roast_status mfma_mm_bwd_dx(const MMArgs& a, const void* dY, int64_t ldy, const 
   KernArgs p{};
   p.a = a; p.A = (const uint16_t*)dY; p.lda = ldy; p.M = M; p.Mb = (const uint16_t*)M_bf16;
   p.mb_stride = shadow_stride(a.m_size); p.C = (uint16_t*)dX; p.ldc = ldx;
+  if (wide.bm) {
+    if (wide.parts > 1) p.G = ws;
+    const roast_status st = wide_mm(1, a, wide, p.A, p.lda, 0, p.Mb, false, p.C, nullptr, p.ldc, ws, s);
+    if (st != ROAST_ERR_UNSUPPORTED) return st != ROAST_OK ? st : split_finish(p, (unsigned)wide.parts, a.I, a.H, s);
+    p.G = nullptr;
+  }
   dim3 grid((unsigned)cdiv(a.H, BN), (unsigned)cdiv(a.I, BM), 1);
   split_setup(&p, &grid, a.O, mfma_dx_splits(a), ws);
   roast_status st;

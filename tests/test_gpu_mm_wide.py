@@ -1,0 +1,72 @@
+"""GPU parity of the wide matrix-core kernels (tiles that are multiples of 32, a bf16 shadow of M) where
+their blocks, strips, splits and steps end: rows, columns and contraction lengths around the block edges,
+one contraction step, ragged last steps, every tile extent, odd and even tile bases."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2207_10702_amd import workloads as wl
+from tests.util import BF16_TOL, rel_err, to_dev, to_host_f64
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+# (I, H, O, Z1, Z2, |M|)
+SHAPES = [
+    (1, 8, 8, 32, 32, 1025),               # one row, one 16-byte piece
+    (127, 64, 192, 32, 64, 5001),          # one step; a row and a column block just missed / just full
+    (129, 72, 200, 64, 32, 9000),          # ragged step, one row and one column piece too many
+    (257, 136, 264, 96, 96, 20011),        # tiles that are no power of two
+    (255, 128, 128, 128, 128, 16384),      # |M| == one tile: every tile at base 0
+    (300, 1096, 520, 32, 96, 30000),       # contraction split (with a workspace), ragged last part
+    (8200, 520, 776, 64, 64, 47185),       # many rows: uneven dM parts
+    (2100, 192, 6144, 64, 64, 33333),      # strips
+    (2100, 6144, 192, 64, 64, 33333),
+    (5000, 1024, 4096, 128, 64, 100003),   # 256 x 256 blocks, ragged rows
+    # |M| beyond 4 Mi: the shadow has no negated copies
+    (129, 72, 200, 64, 32, 5000001),
+    (300, 1096, 520, 32, 96, 4300000),
+    (2100, 192, 6144, 64, 64, 4300001),
+    (5000, 1024, 4096, 128, 64, 4300001),
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("pad", [0, 8])
+def test_wide_kernels_match_oracle(roast, shape, pad):
+    I, H, O, Z1, Z2, m = shape
+    rng = np.random.default_rng(I + 7 * H + O)
+    M = wl.draw_m(rng, m, ("normal", 0.05))
+    X = wl.draw_act(rng, I, H, "bf16")
+    dY = wl.draw_act(rng, I, O, "bf16")
+    h = wl.draw_hash(rng, use_sign=True, align=1)
+    d = roast.mm_desc(H, O, Z1, Z2, m, 2, np.float32(0.43), h)
+    Md = to_dev(M)
+    Mb = roast.roast_m_shadow_bf16(Md)
+
+    def padded(x, n, fill):
+        t = torch.full((I, n + pad), fill, dtype=torch.bfloat16, device="cuda")
+        if x is not None:
+            t[:, :n] = to_dev(x)
+        return t[:, :n]
+
+    Xd, dYd = padded(X, H, 9.0), padded(dY, O, 9.0)
+    W = oracle.materialize_w(h, 2, H, O, Z1, Z2, float(np.float32(0.43)), M)
+    Xo, dYo = wl.act_as_f64(X), wl.act_as_f64(dY)
+    Yr, dXr = oracle.mm_fwd(Xo, W), oracle.mm_bwd_dx(dYo, W)
+    need = max(roast.roast_mm_fwd_workspace(d, torch.bfloat16, I), roast.roast_mm_bwd_dx_workspace(d, torch.bfloat16, I), 16)
+    for ws in (None, torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")):
+        Y, dX = padded(None, O, 7.0), padded(None, H, 7.0)
+        roast.roast_mm_fwd(d, Xd, Md, Y, M_bf16=Mb, ws=ws)
+        roast.roast_mm_bwd_dx(d, dYd, Md, dX, M_bf16=Mb, ws=ws)
+        torch.cuda.synchronize()
+        if pad:                                             # nothing is written between the rows
+            assert torch.all(Y._base[:, O:] == 7.0) and torch.all(dX._base[:, H:] == 7.0)
+        assert rel_err(to_host_f64(Y), Yr) <= BF16_TOL
+        assert rel_err(to_host_f64(dX), dXr) <= BF16_TOL
+    dM = torch.zeros(m, device="cuda")
+    roast.roast_mm_bwd_dM(d, Xd, dYd, dM)
+    torch.cuda.synchronize()
+    ref = oracle.mm_bwd_dm(h, 2, Z1, Z2, m, float(np.float32(0.43)), Xo, dYo)
+    assert rel_err(to_host_f64(dM), ref) <= 1e-4
