@@ -1438,6 +1438,14 @@ roast_status mfma_mm_bwd_dM(const MMArgs& a, const void* X, int64_t ldx, const v
   if (a.H % 8 != 0 || a.O % 8 != 0 || ldx % 8 != 0 || ldy % 8 != 0 || !aligned16(X) || !aligned16(dY) ||
       a.H < BM / 32 || a.O < BN / 32)
     return ROAST_ERR_UNSUPPORTED;
+  if (Gws != nullptr && (splits < 1 || splits > 65535)) return ROAST_ERR_UNSUPPORTED;
+  const WidePlan wide = wide_dm_plan(a, Gws ? splits : 0, false);
+  if (wide.bm) {
+    int begin[kWideParts + 1] = {};
+    if (Gws == nullptr) uneven_parts(a.I, wide.parts, begin);
+    const roast_status st = wide_mm_dM(a, wide, (const uint16_t*)X, ldx, 0, (const uint16_t*)dY, ldy, 0, false, dM, Gws, Gws ? nullptr : begin, s);
+    if (st != ROAST_ERR_UNSUPPORTED) return st;
+  }
   // The tiled epilogue looks a tile up once per four accumulator rows and applies one sign per tile;
   // other tile shapes, per-element signs and tile tables that do not fit hash every element instead
   // (raw products for the deterministic reduction carry no sign and need no table either way).
