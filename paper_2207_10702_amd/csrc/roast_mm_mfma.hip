@@ -1493,8 +1493,14 @@ bool x3_dm_ok(const MMArgs& a) {
   return a.hash.use_sign != 2 && a.Z1 % 4 == 0 && a.H % 8 == 0 && a.O % 8 == 0 && a.H >= kBM / 32 && a.O >= kBN / 32 &&
          (cdiv(kBM, a.Z1) + 1) * (cdiv(kBN, a.Z2) + 1) <= kMaxTable;
 }
-int x3_fwd_splits(const MMArgs& a) { return mm_pick_splits(cdiv(a.O, kBN) * cdiv(a.I, kBM), 6 * a.H); }
-int x3_dx_splits(const MMArgs& a) { return mm_pick_splits(cdiv(a.H, kBN) * cdiv(a.I, kBM), 6 * a.O); }
+int x3_fwd_splits(const MMArgs& a) {
+  const WidePlan w = wide_fwd_plan(a, kWideParts, true);
+  return w.bm ? w.parts : mm_pick_splits(cdiv(a.O, kBN) * cdiv(a.I, kBM), 6 * a.H);
+}
+int x3_dx_splits(const MMArgs& a) {
+  const WidePlan w = wide_dx_plan(a, kWideParts, true);
+  return w.bm ? w.parts : mm_pick_splits(cdiv(a.H, kBN) * cdiv(a.I, kBM), 6 * a.O);
+}
 
 size_t x3_fwd_workspace(const MMArgs& a) {
   if (!x3_fwd_ok(a)) return 0;
@@ -1531,6 +1537,13 @@ roast_status x3_mm_fwd(const MMArgs& a, const float* X, int64_t ldx, const float
   KernArgs p{};
   p.a = a; p.A = Xp; p.lda = pad8(a.H); p.a_plane = a.I * pad8(a.H); p.M = M; p.Mb = Mp;
   p.mb_stride = shadow_stride_of(a.m_size); p.mb_plane = 2 * p.mb_stride; p.C32 = Y; p.ldc = ldy;
+  const WidePlan wide = wide_fwd_plan(a, kWideParts, true);
+  if (wide.bm) {
+    if (wide.parts > 1) p.G = parts;
+    st = wide_mm(0, a, wide, Xp, p.lda, p.a_plane, Mp, true, nullptr, Y, ldy, parts, s);
+    if (st != ROAST_ERR_UNSUPPORTED) return st != ROAST_OK ? st : split_finish(p, (unsigned)wide.parts, a.I, a.O, s);
+    p.G = nullptr;
+  }
   dim3 grid((unsigned)cdiv(a.O, kBN), (unsigned)cdiv(a.I, kBM), 1);
   split_setup(&p, &grid, a.H, x3_fwd_splits(a), parts);
   if (grid.z == 1 && a.H % BK == 0 && narrow_pays(cdiv(a.I, kBM), a.O)) {
@@ -1557,6 +1570,13 @@ roast_status x3_mm_bwd_dx(const MMArgs& a, const float* dY, int64_t ldy, const f
   KernArgs p{};
   p.a = a; p.A = Gp; p.lda = pad8(a.O); p.a_plane = a.I * pad8(a.O); p.M = M; p.Mb = Mp;
   p.mb_stride = shadow_stride_of(a.m_size); p.mb_plane = 2 * p.mb_stride; p.C32 = dX; p.ldc = ldx;
+  const WidePlan wide = wide_dx_plan(a, kWideParts, true);
+  if (wide.bm) {
+    if (wide.parts > 1) p.G = parts;
+    st = wide_mm(1, a, wide, Gp, p.lda, p.a_plane, Mp, true, nullptr, dX, ldx, parts, s);
+    if (st != ROAST_ERR_UNSUPPORTED) return st != ROAST_OK ? st : split_finish(p, (unsigned)wide.parts, a.I, a.H, s);
+    p.G = nullptr;
+  }
   dim3 grid((unsigned)cdiv(a.H, kBN), (unsigned)cdiv(a.I, kBM), 1);
   split_setup(&p, &grid, a.O, x3_dx_splits(a), parts);
   if (grid.z == 1 && a.O % BK == 0 && narrow_pays(cdiv(a.I, kBM), a.H)) {
@@ -1578,6 +1598,13 @@ roast_status x3_mm_bwd_dM(const MMArgs& a, const float* X, int64_t ldx, const fl
   if (st != ROAST_OK) return st;
   st = split_rows(dY, a.I, a.O, ldy, Gp, s);
   if (st != ROAST_OK) return st;
+  const WidePlan wide = wide_dm_plan(a, 0, true);
+  if (wide.bm) {
+    int begin[kWideParts + 1] = {};
+    uneven_parts(a.I, wide.parts, begin);
+    st = wide_mm_dM(a, wide, Xp, pad8(a.H), a.I * pad8(a.H), Gp, pad8(a.O), a.I * pad8(a.O), true, dM, nullptr, begin, s);
+    if (st != ROAST_ERR_UNSUPPORTED) return st;
+  }
   const int64_t tiles = cdiv(a.H, kBM) * cdiv(a.O, kBN);
   const int splits = dm_pick_splits(tiles, 6 * a.I, a.H * a.O);
   int64_t rows = cdiv(a.I, splits);

@@ -522,7 +522,7 @@ __global__ __launch_bounds__(512, 2) void k_roast_wide(WideArgs p) {
   // the last step of a contraction length that is not a multiple of 64: zeros
   auto cut_b = [&](auto KIND, auto KS) {
     constexpr int ks = decltype(KS)::value;
-    if constexpr (decltype(KIND)::value != 2) return;   // (the last step of all)
+    if constexpr (decltype(KIND)::value < 2) return;   // (LAST, TAIL)
     const int rem = k_end - p0.k;                  // contraction indices left from the start of this step
     if (rem < BK) {
       const int cnt = rem - (32 * ks + 8 * (lane_id() >> 4));
@@ -614,8 +614,8 @@ __global__ __launch_bounds__(512, 2) void k_roast_wide(WideArgs p) {
   };
   // The kinds of step: FIRST after a block of a strip has been stored (its stores are younger than loads in
   // flight: the waits have to allow for them), LAST of all (nothing is read or loaded ahead, and it alone can be cut
-  // short), or neither.
-  enum { MID = 0, FIRST = 1, LAST = 2 };
+  // short; X3: and the five pairs before it, TAIL), or none of these.
+  enum { MID = 0, FIRST = 1, LAST = 2, TAIL = 3 };
   auto wait_loads = [&](auto KIND, auto N) {
     constexpr int n = decltype(N)::value + (decltype(KIND)::value == FIRST ? NST : 0);
     static_assert(n < 64, "vmcnt has six bits");
@@ -785,8 +785,10 @@ __global__ __launch_bounds__(512, 2) void k_roast_wide(WideArgs p) {
     };
     int t = 0;
     for (int blk = 0;; ++blk) {
-      const int end = STRIPS && blk < NB - 1 ? (blk + 1) * KQ : KT - 1;
+      const int end = X3 ? KT - 6 : STRIPS && blk < NB - 1 ? (blk + 1) * KQ : KT - 1;
       for (; t < end; ++t) step(t, std::integral_constant<int, MID>{});
+      if constexpr (X3)
+        for (; t < KT - 1; ++t) step(t, std::integral_constant<int, TAIL>{});
       if constexpr (!STRIPS) break;
       if (blk >= NB - 1) break;
       store_bf16(n0 + BN * blk + wn * WTN, std::true_type{});        // a block that another follows (a strip's blocks have two steps at least)
@@ -892,9 +894,7 @@ roast_status launch(const WideArgs& p, hipStream_t s) {
 
 template <int MODE, bool X3, bool NEG>
 roast_status launch_block(const WideArgs& p, int bm, int bn, hipStream_t s) {
-  if constexpr (!(MODE == MODE_DM && X3)) {       // (its registers do not suffice)
-    if (bm == 256 && bn == 256) return launch<MODE, 256, 256, X3, NEG>(p, s);
-  }
+  if (bm == 256 && bn == 256) return launch<MODE, 256, 256, X3, NEG>(p, s);
   if (bm == 256 && bn == 192) return launch<MODE, 256, 192, X3, NEG>(p, s);
   if (bm == 256 && bn == 128) return launch<MODE, 256, 128, X3, NEG>(p, s);
   if (bm == 128 && bn == 192) return launch<MODE, 128, 192, X3, NEG>(p, s);
@@ -950,7 +950,7 @@ WidePlan plan_hashed(int which, const MMArgs& a, int max_parts, bool x3) {
       // (a split of what fills the chip anyway only adds work)
       for (int parts = 1; parts <= max_parts && (parts == 1 || (t == 1 && blocks < 256.0 && blocks * parts <= 512.0)); ++parts) {
         const int64_t steps = cdiv(cdiv(K, parts), BK);
-        if (parts > 1 && (steps < 2 || cdiv(K, steps * BK) != parts)) continue;
+        if (parts > 1 && (steps * pairs < 2 || cdiv(K, steps * BK) != parts)) continue;
         if ((cdiv(steps * BK, zk) + 1) * tn > table_entries(b.bm, b.bn)) continue;
         const double wgs = blocks * parts;
         const double step = b.step + b.busy * std::min(wgs / 256.0, 1.0);
@@ -977,7 +977,7 @@ WidePlan plan_dm(const MMArgs& a, int parts, bool x3) {
     const int64_t tiles = cdiv(a.H, b.bm) * cdiv(a.O, b.bn);
     for (int q = parts > 0 ? parts : 1; q <= (parts > 0 ? parts : kWideParts); ++q) {
       const int64_t steps = cdiv(cdiv(a.I, q), BK);
-      if (parts == 0 && q > 1 && (steps < 2 || cdiv(a.I, steps * BK) != q)) continue;
+      if (parts == 0 && q > 1 && (steps * pairs < 2 || cdiv(a.I, steps * BK) != q)) continue;
       double cost = rounds_of((double)(tiles * q)) * ((double)(steps * pairs) * b.dm_step + b.dm_fixed);
       // rows of tiles narrower than a wave's 64 columns break the adds into more pieces; adds to one address
       // (|M| far smaller than the layer) complete 25 ns apart

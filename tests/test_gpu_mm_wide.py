@@ -1,4 +1,4 @@
-"""GPU parity of the wide matrix-core kernels (tiles that are multiples of 32, a bf16 shadow of M) where
+"""GPU parity of the wide matrix-core kernels (tiles that are multiples of 32; a bf16 shadow of M, or fp32 planes) where
 their blocks, strips, splits and steps end: rows, columns and contraction lengths around the block edges,
 one contraction step, ragged last steps, every tile extent, odd and even tile bases."""
 import numpy as np
@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 from paper_2207_10702_amd import workloads as wl
-from tests.util import BF16_TOL, rel_err, to_dev, to_host_f64
+from tests.util import BF16_TOL, F32_TOL, rel_err, to_dev, to_host_f64
 
 pytestmark = pytest.mark.gpu
 
@@ -70,3 +70,27 @@ def test_wide_kernels_match_oracle(roast, shape, pad):
     torch.cuda.synchronize()
     ref = oracle.mm_bwd_dm(h, 2, Z1, Z2, m, float(np.float32(0.43)), Xo, dYo)
     assert rel_err(to_host_f64(dM), ref) <= 1e-4
+
+
+@pytest.mark.parametrize("shape", [s for s in SHAPES if s[5] < 1 << 22])
+def test_wide_plane_products_match_oracle(roast, shape):
+    I, H, O, Z1, Z2, m = shape
+    rng = np.random.default_rng(2 * I + 7 * H + O)
+    M = wl.draw_m(rng, m, ("normal", 0.05))
+    X = rng.standard_normal((I, H)).astype(np.float32)
+    dY = rng.standard_normal((I, O)).astype(np.float32)
+    h = wl.draw_hash(rng, use_sign=True, align=1)
+    lam = np.float32(0.43)
+    d = roast.mm_desc(H, O, Z1, Z2, m, 2, lam, h)
+    Md, Xd, dYd = to_dev(M), to_dev(X), to_dev(dY)
+    ws = lambda n: torch.full((max(n, 16),), 0xFF, dtype=torch.uint8, device="cuda")  # noqa: E731
+    Y, dX, dM = torch.empty((I, O), device="cuda"), torch.empty((I, H), device="cuda"), torch.zeros(m, device="cuda")
+    roast.roast_mm_fwd(d, Xd, Md, Y, ws=ws(roast.roast_mm_fwd_workspace(d, torch.float32, I)))
+    roast.roast_mm_bwd_dx(d, dYd, Md, dX, ws=ws(roast.roast_mm_bwd_dx_workspace(d, torch.float32, I)))
+    roast.roast_mm_bwd_dM(d, Xd, dYd, dM, roast.ROAST_REDUCE_ATOMIC, ws(roast.roast_mm_bwd_dM_workspace_f32(d, I)))
+    torch.cuda.synchronize()
+    W = oracle.materialize_w(h, 2, H, O, Z1, Z2, float(lam), M)
+    Xo, dYo = X.astype(np.float64), dY.astype(np.float64)
+    assert rel_err(to_host_f64(Y), oracle.mm_fwd(Xo, W)) <= F32_TOL
+    assert rel_err(to_host_f64(dX), oracle.mm_bwd_dx(dYo, W)) <= F32_TOL
+    assert rel_err(to_host_f64(dM), oracle.mm_bwd_dm(h, 2, Z1, Z2, m, float(lam), Xo, dYo)) <= F32_TOL
