@@ -142,7 +142,7 @@ constexpr int lds_operands(int bm, int bn) { return lds_stages(bm, bn) * (bm + b
 constexpr int table_entries(int bm, int bn) { return (160 * 1024 - lds_operands(bm, bn)) / 4; }
 
 template <int MODE, int BM, int BN, bool X3, bool NEG>
-__global__ __launch_bounds__(512, 2) void k_roast_wide(WideArgs p) {
+__global__ __launch_bounds__(512, 2) void k_roast_mfma_wide(WideArgs p) {
   constexpr int WM = (BM == 256 && BN == 128) ? 4 : 2, WN = 8 / WM;
   constexpr int WTM = BM / WM, WTN = BN / WN;     // rows, columns of a wave
   constexpr int PH = WTM == 128 ? 4 : 2;          // phases of a step: (row halves) x (two k halves), or the k halves alone
@@ -519,8 +519,10 @@ __global__ __launch_bounds__(512, 2) void k_roast_wide(WideArgs p) {
       }
     }
   };
-  // the last step of a contraction length that is not a multiple of 64: zeros
-  auto cut_b = [&](auto KIND, auto KS) {
+  // the last step of a contraction length that is not a multiple of 64: zeros, in the weight fragments alone (the
+  // activations they meet are of the same row), and in both of dM's, where an infinity of the last token
+  // times a zero would be a NaN that the sum does not have
+  auto cut = [&](auto KIND, auto KS) {
     constexpr int ks = decltype(KS)::value;
     if constexpr (decltype(KIND)::value < 2) return;   // (LAST, TAIL)
     const int rem = k_end - p0.k;                  // contraction indices left from the start of this step
@@ -531,6 +533,10 @@ __global__ __launch_bounds__(512, 2) void k_roast_wide(WideArgs p) {
         const uint32_t keep = cnt >= 2 * d + 2 ? 0xffffffffu : (cnt == 2 * d + 1 ? 0x0000ffffu : 0u);
 #pragma unroll
         for (int j = 0; j < NJ; ++j) bf[ks][j][d] &= keep;
+        if constexpr (MODE == MODE_DM) {
+#pragma unroll
+          for (int i = 0; i < MI; ++i) af[ks][i][d] &= keep;
+        }
       }
     }
   };
@@ -640,7 +646,7 @@ __global__ __launch_bounds__(512, 2) void k_roast_wide(WideArgs p) {
     asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(LAB));
     tie_a(I0{});
     tie_b(I0{});
-    cut_b(KIND, I0{});
+    cut(KIND, I0{});
     wait_loads(KIND, std::integral_constant<int, (MORE ? 3 : 2) + BI>{});     // A quarters 2, 3 of this step have landed
     __builtin_amdgcn_s_barrier();
     products(I0{}, I1{}, [&] {
@@ -655,7 +661,7 @@ __global__ __launch_bounds__(512, 2) void k_roast_wide(WideArgs p) {
     tie_a(I1{});
     tie_b(I1{});
     if constexpr (MORE) tie_entries();
-    cut_b(KIND, I1{});
+    cut(KIND, I1{});
     __builtin_amdgcn_s_barrier();
     products(I1{}, I2{}, [&] {
       if constexpr (MORE) {
@@ -673,6 +679,7 @@ __global__ __launch_bounds__(512, 2) void k_roast_wide(WideArgs p) {
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(LA));
     tie_a(I0{});
+    if constexpr (MODE == MODE_DM) cut(KIND, I0{});
     if constexpr (MORE) wait_loads(KIND, std::integral_constant<int, 5>{});          // B and A quarters 0, 1 of step t+1 have landed
     __builtin_amdgcn_s_barrier();
     products(I2{}, I2{}, [&] {
@@ -691,6 +698,7 @@ __global__ __launch_bounds__(512, 2) void k_roast_wide(WideArgs p) {
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(MORE ? LAB : 0));
     tie_a(I1{});
+    if constexpr (MODE == MODE_DM) cut(KIND, I1{});
     __builtin_amdgcn_s_barrier();
     products(I3{}, std::integral_constant<int, MORE ? 0 : 2>{}, [&] {
       if constexpr (MORE) {
@@ -716,7 +724,7 @@ __global__ __launch_bounds__(512, 2) void k_roast_wide(WideArgs p) {
     asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(LAB));
     tie_a(I0{});
     tie_b(I0{});
-    cut_b(KIND, I0{});
+    cut(KIND, I0{});
     if constexpr (MORE) wait_loads(KIND, std::integral_constant<int, AQ + BI>{});    // step t+1 has landed
     __builtin_amdgcn_s_barrier();
     Pos p3 = p2;
@@ -740,7 +748,7 @@ __global__ __launch_bounds__(512, 2) void k_roast_wide(WideArgs p) {
     tie_a(I1{});
     tie_b(I1{});
     if constexpr (MORE) tie_entries();
-    cut_b(KIND, I1{});
+    cut(KIND, I1{});
     __builtin_amdgcn_s_barrier();
     products(I1{}, std::integral_constant<int, MORE ? 0 : 2>{}, [&] {
       if constexpr (MORE) {
@@ -883,12 +891,12 @@ roast_status launch(const WideArgs& p, hipStream_t s) {
   static_assert(smem <= 160 * 1024 && 8 * 16 * (64 * 4 + 16) <= lds_operands(BM, BN), "LDS budget");
   static std::atomic<bool> configured{false};   // per instantiation; a race between host threads only repeats the call
   if (!configured.load(std::memory_order_acquire)) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_roast_wide<MODE, BM, BN, X3, NEG>),
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_roast_mfma_wide<MODE, BM, BN, X3, NEG>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess)
       return ROAST_ERR_HIP;
     configured.store(true, std::memory_order_release);
   }
-  hipLaunchKernelGGL((k_roast_wide<MODE, BM, BN, X3, NEG>), dim3((unsigned)((total + 7) / 8 * 8)), dim3(512), smem, s, p);
+  hipLaunchKernelGGL((k_roast_mfma_wide<MODE, BM, BN, X3, NEG>), dim3((unsigned)((total + 7) / 8 * 8)), dim3(512), smem, s, p);
   return hip_status(hipGetLastError());
 }
 

@@ -94,3 +94,21 @@ def test_wide_plane_products_match_oracle(roast, shape):
     assert rel_err(to_host_f64(Y), oracle.mm_fwd(Xo, W)) <= F32_TOL
     assert rel_err(to_host_f64(dX), oracle.mm_bwd_dx(dYo, W)) <= F32_TOL
     assert rel_err(to_host_f64(dM), oracle.mm_bwd_dm(h, 2, Z1, Z2, m, float(lam), Xo, dYo)) <= F32_TOL
+
+
+@pytest.mark.parametrize("shape", [(67, 128, 128), (1027, 768, 1536), (4099, 4096, 4096)])
+def test_infinity_in_the_last_token_stays_an_infinity(roast, shape):
+    """A ragged number of tokens: what fills the last step meets no infinity of the last token.  One tile
+    for all (|M| = Z1 * Z2), no signs, dY > 0: the row of that infinity is +inf, the rest is finite."""
+    I, H, O = shape
+    h = wl.draw_hash(np.random.default_rng(I), use_sign=False, align=1)
+    d = roast.mm_desc(H, O, 128, 128, 128 * 128, 0, 1.0, h)
+    g = torch.Generator(device="cuda").manual_seed(I)
+    X = torch.randn((I, H), generator=g, device="cuda", dtype=torch.bfloat16)
+    dY = torch.rand((I, O), generator=g, device="cuda").add_(0.5).bfloat16()
+    X[I - 1, 5] = float("inf")
+    dM = torch.zeros(128 * 128, device="cuda")
+    roast.roast_mm_bwd_dM(d, X, dY, dM)
+    dM = dM.view(128, 128).cpu()
+    assert torch.all(dM[5] == float("inf"))
+    assert torch.all(torch.isfinite(dM[torch.arange(128) != 5]))
