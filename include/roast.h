@@ -222,6 +222,8 @@ roast_status roast_mm_bwd_dx_ws(const roast_mm_desc* d, roast_dtype dt, int64_t 
  * bf16 shadow and no workspace.  This is Algorithm 1's loop order seen from one workgroup: a fixed
  * row block i, the column blocks j of its strip in turn, the contraction k innermost.  1 = one block
  * per workgroup (also for shapes that take other kernels); 0 = invalid descriptor, I or `which`.
+ * It speaks of the 128-column kernels; shapes with tiles that are multiples of 32 run on wider blocks
+ * when there is a shadow, and choose block and strip for themselves.
  * For tests (which must know that a shape exercises the strip path) and for tuning.
  */
 int roast_mm_strip_blocks(const roast_mm_desc* d, int64_t I, int which);

@@ -313,9 +313,6 @@ roast_status launch_embed(const EmbedArgs& a, const int64_t* rows, const uint32_
   const int per_lane = vec4 ? 4 : 1;
   int lpi_log2 = 0;
   while ((1 << lpi_log2) < 64 && (int64_t)(1 << lpi_log2) * per_lane < a.Z) ++lpi_log2;
-  // forward over an M that does not fit one XCD's L2 (4 MiB): four slices (measured on a 5 MiB M:
-  // 171 us unsliced, 158 / 144 / 189 us with 2 / 4 / 8 slices -- every slice hashes all lookups),
-  // eight once a quarter is too large; not for small calls, nor once even an eighth does not fit
   // Lookups per wave: 64 (one per lane) once the call fills the chip with full waves; below that fewer,
   // so that a small call spreads over up to 8192 waves (32 per CU) instead of walking 64 lookups'
   // chunks one group after the other in a few waves -- but never fewer than one step of the wave
@@ -324,6 +321,9 @@ roast_status launch_embed(const EmbedArgs& a, const int64_t* rows, const uint32_
   while (rows_wave > 1 && (a.N + rows_wave / 2 - 1) / (rows_wave / 2) <= 8192 && (rows_wave / 2) * a.C >= (64 >> lpi_log2)) rows_wave /= 2;
   const int64_t waves = (a.N + rows_wave - 1) / rows_wave;
   int64_t blocks = (waves + 3) / 4;
+  // forward over an M that does not fit one XCD's L2 (4 MiB): four slices (measured on a 5 MiB M:
+  // 171 us unsliced, 158 / 144 / 189 us with 2 / 4 / 8 slices -- every slice hashes all lookups),
+  // eight once a quarter is too large; not for small calls, nor once even an eighth does not fit
   int slices = 1;
   if (!BWD && vec4 && a.N * a.C >= 65536) {
     const int64_t bytes = a.m_size * 4, fit = 3584 * 1024;

@@ -1,6 +1,8 @@
 // bf16 MFMA kernels for ROAST-MM on gfx950 (Algorithm 1 and the Section 4.3 gradients of
-// arXiv 2207.10702): forward Y = X*W, dX = dY*W^T and the per-tile products of dM = scatter(X^T*dY),
-// with W recovered from M tile by tile and never written to memory.
+// arXiv 2207.10702), for the shapes that the wide blocks of roast_mm_wide.hip do not take (no copy of
+// M, tiles that are no multiples of 32, per-element signs), and the dispatch between the two:
+// forward Y = X*W, dX = dY*W^T and the per-tile products of dM = scatter(X^T*dY), with W recovered
+// from M tile by tile and never written to memory.
 //
 // One workgroup computes a BM x BN = 256 x 128 block of the output with specialised waves: the
 // first NC waves are consumers, each owning a (BM/WGM) x (BN/WGN) sub-block in fp32 accumulators and
@@ -14,7 +16,7 @@
 //
 // Both operands sit in LDS as [row][k] with 128-byte rows whose 16-byte chunks are XOR-swizzled,
 // so a lane fetches the 8 contraction values of its row with one conflict-free ds_read_b128
-// (transposing LDS reads were measured at a quarter of that bandwidth).  How an operand gets there:
+// (see roast_mm_wide.hip for the transposing LDS reads).  How an operand gets there:
 //   forward: X rows are contraction-contiguous already: global_load_lds copies them straight into
 //            LDS (three stages; no registers, no ds_write), each lane fetching the chunk the swizzle
 //            wants at its LDS slot.  The hashed weight tile (contiguous along O) is loaded as 8(k) x
