@@ -229,9 +229,15 @@ __global__ __launch_bounds__(512, 2) void k_roast_mfma_wide(WideArgs p) {
   // ---- A tile.  Quarter q = 64 output rows, 8 KiB of LDS, one instruction per wave: [row][64 k] with the
   // wave's 8 rows, or (TA) [k][64 rows] with the wave's 8 k-rows.  Lane: row (k-row) lane >> 3, chunk a_ch.
   const int lr = lane >> 3;
+  // ... of rows along the contraction: one ds_read_b128 takes 16 rows by 4 chunks, 16 lanes a clock, of which
+  // half are rows 0-3 and 12-15 at one chunk and half rows 4-11 at the next (or the other way round).  With
+  // row ^ (row >> 3) each such clock met every bank twice: 4 clocks more per read, a third to a half of the
+  // LDS's busy time (SQ_LDS_BANK_CONFLICT 12288 of 30388 clocks per CU, 8192x768x3072); with this, none.
+  // (The products hide most of it: 512x2048x2048 18.77 -> 18.68 us, 16384x4096x16384 1674 -> 1667, 8192x768x3072 40.1 -> 40.2.)
+  auto swzRow = [](int r) { return (r >> 1) & 7; };
   auto swz64 = [](int k) { return ((k >> 1) & 1) | (((k >> 3) & 1) << 1); };        // 32-byte chunk permutation of 128-byte k-rows
   auto swzBN = [](int k) { return (k & 3) | (((k >> 3) & 1) << 2); };               // ... of k-rows of 256 bytes and more
-  const int a_ch = TA ? ((lane & 7) ^ (2 * swz64(8 * wave + lr))) : ((lane & 7) ^ lr ^ (wave & 1));
+  const int a_ch = TA ? ((lane & 7) ^ (2 * swz64(8 * wave + lr))) : ((lane & 7) ^ swzRow(8 * wave + lr));
   // constant part of the lane's offset: !TA: its row (rows beyond the last one repeat it, they are not
   // stored); TA: its columns (clamped likewise)
   uint32_t a_fix[AQ];
@@ -282,7 +288,7 @@ __global__ __launch_bounds__(512, 2) void k_roast_mfma_wide(WideArgs p) {
   for (int v = 0; v < BV; ++v) {
     if constexpr (TB && ROWS) b_n[v] = min(n0 + 8 * ((lane % CPR) ^ (2 * swzBN(8 * wave + v * RPI + lane / CPR))), Ndim - 8);
     else if constexpr (TB) b_n[v] = 8 * ((lane & 7) ^ (2 * swz64(8 * wave + lr)));
-    else b_n[v] = 8 * ((lane & 7) ^ lr ^ ((wave * BI + v) & 1));
+    else b_n[v] = 8 * ((lane & 7) ^ swzRow(8 * (wave * BI + v) + lr));
   }
   const uint32_t tab = sbase + NS * STAGE;
   // FWD: table column and offset inside the tile, in bytes, of the lane's chunk
@@ -428,7 +434,7 @@ __global__ __launch_bounds__(512, 2) void k_roast_mfma_wide(WideArgs p) {
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
   // k-contiguous operand: lane reads 8 k of row lane & 15, chunk (lane >> 4) + 4*ks; transposed: see lds_read16_t
-  const uint32_t l_row = ((uint32_t)lane & 7) ^ (((uint32_t)lane >> 3) & 1);
+  const uint32_t l_row = (uint32_t)swzRow(lane);
   const int tk = 8 * (lane >> 4) + ((lane & 15) >> 2);
   constexpr int AR = TA ? SUB : 2, BR = TB ? NJ : 2;
   uint32_t a_rd[AR], b_rd[BR];                     // by sub-row fragment / column fragment, or by k half
