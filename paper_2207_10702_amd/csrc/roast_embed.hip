@@ -756,11 +756,11 @@ roast_status bucket_run(const EmbedArgs& a, const BucketPlan& p, const int64_t* 
   return hip_status(hipGetLastError());
 }
 
-// Below about 2.5 M values the direct adds (0.2 T/s: 12 us) are done before the three kernels of the
-// pipeline are (62 400 chunks of 32: 18 against 23 us, 104 000: 29 against 27); the fixed-point mode's
-// direct kernel hashes every element, so there the line stays lower.
-inline bool bucket_worthwhile(const BucketPlan& p, int64_t z, bool fixed, const float* dOut) {
-  return p.ok && p.n_items >= 65536 && (fixed || p.n_items * z >= 2500000) && ((uintptr_t)dOut & 15) == 0;
+// From 65536 chunks on.  (The direct adds would be as fast a little beyond that -- 104 000 chunks of 32
+// take 27 us routed and 29 direct -- but they sum in fp32, a slot that a popular row adds to thousands of times
+// included, where the routed gradient sums in fp64 and rounds once per flush.)
+inline bool bucket_worthwhile(const BucketPlan& p, const float* dOut) {
+  return p.ok && p.n_items >= 65536 && ((uintptr_t)dOut & 15) == 0;
 }
 
 struct DetLayoutE {
@@ -784,7 +784,7 @@ roast_status embed_bwd_atomic_launch(const EmbedArgs& a, const int64_t* rows, co
                                      const float* dOut, float* dM, void* ws, size_t ws_bytes, hipStream_t s) {
   const BucketPlan p = bucket_plan(a);
   // small problems, odd shapes, or no workspace: plain atomics straight into dM
-  if (!bucket_worthwhile(p, a.Z, false, dOut) || ws == nullptr || ws_bytes < p.total)
+  if (!bucket_worthwhile(p, dOut) || ws == nullptr || ws_bytes < p.total)
     return launch_embed<true>(a, rows, tables, nullptr, nullptr, dOut, dM, s);
   return bucket_run<false>(a, p, rows, tables, dOut, dM, (char*)ws, 0, nullptr, nullptr, s);
 }
@@ -816,7 +816,7 @@ roast_status embed_bwd_det_run(const EmbedArgs& a, const int64_t* rows, const ui
   hipLaunchKernelGGL(k_embed_absmax, dim3((unsigned)ab), dim3(256), 0, s, dOut, n_grad, fs);
   const BucketPlan p = bucket_plan(a);
   roast_status st;
-  if (bucket_worthwhile(p, a.Z, true, dOut)) {
+  if (bucket_worthwhile(p, dOut)) {
     st = bucket_run<true>(a, p, rows, tables, dOut, dM, base + l.bucket_off, pbits, fs, acc, s);
   } else {
     const int64_t blocks = (n_el + 255) / 256;

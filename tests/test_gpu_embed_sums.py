@@ -1,0 +1,42 @@
+"""Precision and extent of the routed lookup gradient (65536 chunks and more, with a workspace): partial sums
+are fp64, rounded to fp32 only when a workgroup hands them on.  Scale 1, so that every addend is exact and the
+fp64 oracle shows the rounding of the sums alone."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2207_10702_amd import workloads as wl
+from tests.util import to_dev, to_host_f64
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+ULP = 2.0 ** -24                                  # half a unit of the last place of an fp32 value in [1, 2)
+
+
+def gradient(roast, h, D, Z, m_size, rows, tables, dOut):
+    d = roast.embed_desc(D, Z, m_size, 1.0, h)
+    ws = torch.empty(roast.roast_embed_bwd_workspace(d, len(rows), roast.ROAST_REDUCE_ATOMIC), dtype=torch.uint8, device="cuda")
+    dM = torch.zeros(m_size, device="cuda")
+    roast.roast_embed_bwd(d, to_dev(rows), to_dev(tables), to_dev(dOut), dM, roast.ROAST_REDUCE_ATOMIC, ws)
+    return to_host_f64(dM)
+
+
+@pytest.mark.parametrize("N,D,Z", [(65_536, 32, 32), (78_000, 32, 32), (150_000, 16, 16), (80_000, 4, 4)])
+def test_a_popular_row_keeps_its_digits(roast, N, D, Z):
+    """One row has far more lookups than others, as many as the list of its bucket has room for: its slots collect
+    more than ten thousand addends of one sign.  A slot's sum is rounded at most twice per 8192 chunks of a bucket (the
+    partial sum, the add), in at most two buckets."""
+    m_size = 50_021
+    rng = np.random.default_rng(N)
+    h = wl.draw_hash(rng, use_sign=True, align=1)
+    mean = N * (D // Z) / -(-m_size // 4096)      # chunks per bucket; a list holds twice that and 8192
+    rows = np.where(rng.random(N) < 0.8 * (mean + 8192) / N, 7, rng.integers(0, 1 << 33, N)).astype(np.int64)
+    tables = np.full(N, 3, dtype=np.uint32)
+    dOut = rng.uniform(0.5, 1.5, (N, D)).astype(np.float32)
+    ref = oracle.embed_bwd(h, D, Z, m_size, 1.0, rows, tables, dOut)
+    mass = oracle.embed_bwd(dict(h, use_sign=0), D, Z, m_size, 1.0, rows, tables, dOut)     # sum of |addends|
+    got = gradient(roast, h, D, Z, m_size, rows, tables, dOut)
+    roundings = 2 * 2 * np.ceil((2 * mean + 8192) / 8192)
+    assert np.all(np.abs(got - ref) <= roundings * ULP * mass)
