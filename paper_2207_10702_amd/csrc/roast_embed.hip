@@ -353,14 +353,14 @@ roast_status launch_embed(const EmbedArgs& a, const int64_t* rows, const uint32_
 //              is added straight into dM with global atomics instead (rare: only under extreme skew).
 //   2. accum:  one workgroup per (bucket, list segment) zeroes an fp64 LDS image of its R (+Z)
 //              slots, adds its chunks of dOut into it with LDS atomics, and flushes the image to dM
-//              with global atomics -- R adds per workgroup instead of Z adds per chunk.
+//              with global atomics -- R adds per workgroup instead of Z adds per chunk.  Where segments are
+//              short, it flushes to fp64 sums of the bucket behind the entries of its list.
+//   3. sums:   (short segments) the fp64 sums are added to dM.
 // Needs Z % 4 == 0, D % Z == 0, C <= kMaxC, |M| < 2^31 and at most kMaxBuckets buckets of at most
 // kMaxR slots; other shapes use the direct atomic kernel above.
-// Values per accumulate workgroup (kSegValues / Z chunks).  A short segment costs one more flush of the
-// image (4096 adds), a long one leaves a few workgroups running at the end, and with small batches
-// too few workgroups altogether: 1024 against 8192 chunks of 32 took 230 against 249 us on 6.8 M chunks
-// over 313 buckets and 70 against 93 us (pooled, both passes) on 0.85 M.
-constexpr int kSegValues = 32768;
+constexpr int kSeg = 8192;          // chunks per accumulate workgroup whose sum goes to dM as one fp32 add per slot
+constexpr int kSumValues = 40960;   // values per accumulate workgroup where the sums of a bucket meet in fp64 first
+constexpr int kFixedValues = 65536; // ... and in the fixed-point mode, where they meet in 64-bit integers
 constexpr int kListSlack = 8192;    // list capacity beyond twice the mean load
 constexpr int kAccThreads = 256;
 constexpr int kMaxBuckets = 2048;
@@ -389,7 +389,7 @@ inline BucketPlan bucket_plan(const EmbedArgs& a) {
   p.r_log2 = r;
   p.nb = (int)((a.m_size + (1ll << r) - 1) >> r);
   if (p.nb > kMaxBuckets) { p.ok = false; return p; }
-  // twice the mean load plus one segment: uniform hashing stays far below, skewed ids mostly too
+  // twice the mean load and some: uniform hashing stays far below, skewed ids mostly too
   p.cap = (uint32_t)(2 * (p.n_items / p.nb) + kListSlack);
   auto up = [](size_t v) { return (v + 255) / 256 * 256; };
   size_t o = 0;
@@ -397,6 +397,64 @@ inline BucketPlan bucket_plan(const EmbedArgs& a) {
   p.list_off = o;   o += up((size_t)p.nb * p.cap * 8);
   p.total = o;
   return p;
+}
+
+// How an accumulate launch shares out the lists: segments of seg_len chunks, at most `most` of them to a bucket.
+// sums: a bucket of more than one segment adds them up in fp64, in the last R + Z entries of its list.
+//
+// Every fp32 add to dM rounds, so there is one per slot and kSeg chunks of a bucket (or one in all, sums).  Segments of
+// 1024 chunks of 32, each added to dM in fp32, were faster -- 231 against 248 us on 6.8 M chunks over 313 buckets, 71
+// against 81 (pooled, both passes) on 0.85 M -- but rounded a slot's sum eight times as often.
+// With kSeg and a mean load below it most buckets are one workgroup, and the fullest ones, twice the mean, run on alone
+// while other CUs idle; that is where sums pay, down to two segments to a bucket and unless there are buckets enough (1024: four
+// for every CU, all it holds) for it to even out: 94 -> 84 us on those 0.85 M chunks, 107 000 chunks of 1024 400 -> 150,
+// but 6.8 M chunks (loads beyond kSeg) 254 -> 260 and 0.31 M (one segment) 39 -> 42.
+// Fixed point is exact however it is cut: 65536 values each, 113 us on 1.04 M chunks, 127 with kSeg.
+// A list has room for twice its mean load and kListSlack, so `most` segments of seg_len may be too few for a long one:
+// its segments are longer then.  (Grids for full lists of short segments would be nearly all empty for a large Z.)
+struct AccPlan {
+  int r_log2, nb;
+  uint32_t cap, seg_len, most;
+  bool sums;
+};
+inline AccPlan acc_plan(const EmbedArgs& a, const BucketPlan& p, bool fixed) {
+  AccPlan k{p.r_log2, p.nb, p.cap, (uint32_t)kSeg, 0, false};
+  const int64_t mean = p.n_items / p.nb;
+  if (fixed) {
+    k.seg_len = (uint32_t)std::min(kSeg, kFixedValues / a.Z);
+  } else if (mean <= kSeg && mean * a.Z >= 65536 && p.nb < 1024) {
+    k.sums = true;
+    k.seg_len = (uint32_t)std::min(kSeg, kSumValues / a.Z);
+  }
+  const uint32_t segs = (p.cap + k.seg_len - 1) / k.seg_len;
+  k.most = fixed || k.sums ? (uint32_t)std::min<int64_t>(segs, 2 * (mean / k.seg_len) + 8) : segs;
+  return k;
+}
+struct Segment {
+  uint32_t first, end;   // of the list; none: first >= end
+  bool sums;
+};
+__device__ inline Segment segment_of(const AccPlan& k, uint32_t count, int span, uint32_t seg) {
+  count = min(count, k.cap);
+  Segment r;
+  r.sums = k.sums && count > k.seg_len && count + (uint32_t)span <= k.cap;   // (a list too full for them, extreme skew, goes to dM by kSeg)
+  const uint32_t len = k.sums && !r.sums ? (uint32_t)kSeg : max(k.seg_len, (count + k.most - 1) / k.most);
+  r.first = seg * len;
+  r.end = min(count, r.first + len);
+  return r;
+}
+// the sums of bucket b, slots + Z of them
+__device__ inline double* sums_of(const AccPlan& k, uint2* list, int b, int span) {
+  return reinterpret_cast<double*>(list + (size_t)(b + 1) * k.cap - span);
+}
+
+// cursors, and the places of the sums (a list that runs into its own has none)
+__global__ __launch_bounds__(256) void k_embed_route_init(AccPlan k, int span, uint32_t* __restrict__ cursor, uint2* __restrict__ list) {
+  const int b = blockIdx.x;
+  if (threadIdx.x == 0) cursor[b] = 0u;
+  if (!k.sums) return;
+  double* sums = sums_of(k, list, b, span);
+  for (int i = threadIdx.x; i < span; i += 256) sums[i] = 0.0;
 }
 
 __global__ __launch_bounds__(256) void k_embed_zero(uint32_t* __restrict__ p, int64_t n) {
@@ -599,8 +657,7 @@ __global__ __launch_bounds__(kRouteThreads) void k_embed_route(EmbedArgs a, int 
 }
 
 template <bool FIXED>
-__global__ __launch_bounds__(kAccThreads) void k_embed_accum(EmbedArgs a, int r_log2, uint32_t cap, int nb, uint32_t seg_len,
-                                                     const uint32_t* __restrict__ cursor, const uint2* __restrict__ list,
+__global__ __launch_bounds__(kAccThreads) void k_embed_accum(EmbedArgs a, AccPlan k, const uint32_t* __restrict__ cursor, uint2* __restrict__ list,
                                                      const float* __restrict__ dOut, float* __restrict__ dM, int pbits,
                                                      const FixedScale* fs, unsigned long long* __restrict__ acc) {
   // fp64 image: LDS fp32 atomic adds were measured ~20x slower than fp64 ones on this chip.
@@ -612,15 +669,15 @@ __global__ __launch_bounds__(kAccThreads) void k_embed_accum(EmbedArgs a, int r_
   if constexpr (FIXED) scale = fixed_scale(fs, a.lambda, pbits);
   // Workgroup numbers run over the buckets first: the lists have room for about twice their mean load,
   // so most of the later segments are empty, and with the segments of a bucket next to one another
-  // the occupied ones would be every 2nd or 4th workgroup -- all on the same few XCDs.
-  const int b = blockIdx.x % nb, seg = blockIdx.x / nb;
-  const uint32_t count = min(cursor[b], cap);
-  const uint32_t first = (uint32_t)seg * seg_len;
-  if (first >= count) return;
-  const uint32_t end = min(count, first + seg_len);
-  const uint2* lst = list + (size_t)b * cap;
-  const int R = 1 << r_log2, span = R + a.Z;
-  const int64_t slot0 = (int64_t)b << r_log2;
+  // the occupied ones would be every 2nd or 4th workgroup -- all on the same few XCDs.  Last segments come
+  // first: those of the fullest buckets start before the chip is full (6.8 M chunks: 254 -> 248 us).
+  const int b = blockIdx.x % k.nb;
+  const int R = 1 << k.r_log2, span = R + a.Z;
+  const Segment sg = segment_of(k, cursor[b], span, k.most - 1 - blockIdx.x / k.nb);
+  const uint32_t first = sg.first, end = sg.end;
+  if (first >= end) return;
+  const uint2* lst = list + (size_t)b * k.cap;
+  const int64_t slot0 = (int64_t)b << k.r_log2;
   for (int i = threadIdx.x; i < span; i += kAccThreads) img[i] = img_t(0);
   __syncthreads();
   const int lpi = a.Z / 4;                       // lanes per chunk
@@ -695,14 +752,37 @@ __global__ __launch_bounds__(kAccThreads) void k_embed_accum(EmbedArgs a, int r_
   }
   }
   __syncthreads();
+  double* sums = sums_of(k, list, b, span);
   for (int i = threadIdx.x; i < span; i += kAccThreads) {
     if constexpr (FIXED) {
       const unsigned long long v = img[i];
       if (v != 0ull && slot0 + i < a.m_size) atomicAdd(acc + slot0 + i, v);
     } else {
-      const float v = (float)img[i];
-      if (v != 0.f && slot0 + i < a.m_size) unsafeAtomicAdd(dM + slot0 + i, v);
+      if (sg.sums) {
+        if (img[i] != 0.0) unsafeAtomicAdd(sums + i, img[i]);
+      } else {
+        const float v = (float)img[i];
+        if (v != 0.f && slot0 + i < a.m_size) unsafeAtomicAdd(dM + slot0 + i, v);
+      }
     }
+  }
+}
+
+// dM += the sums of the buckets that have them; 1024 slots of one bucket per workgroup.  (Adds of another
+// stream's call to the same dM may be under way.)
+__global__ __launch_bounds__(256) void k_embed_add_sums(EmbedArgs a, AccPlan k, const uint32_t* __restrict__ cursor,
+                                                        uint2* __restrict__ list, float* __restrict__ dM) {
+  const int64_t slot0 = (int64_t)blockIdx.x * 1024;
+  const int R = 1 << k.r_log2, span = R + a.Z;
+  const int b = (int)(slot0 >> k.r_log2), at = (int)(slot0 & (R - 1));
+  const bool own = segment_of(k, cursor[b], span, 0).sums;
+  const bool before = at == 0 && b > 0 && segment_of(k, cursor[b - 1], span, 0).sums;   // (Z <= 1024: its last Z slots are this bucket's first)
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int i = j * 256 + threadIdx.x;
+    double sum = own ? sums_of(k, list, b, span)[at + i] : 0.0;
+    if (before && i < a.Z) sum += sums_of(k, list, b - 1, span)[R + i];
+    if (sum != 0.0 && slot0 + i < a.m_size) unsafeAtomicAdd(dM + slot0 + i, (float)sum);
   }
 }
 
@@ -727,7 +807,9 @@ roast_status bucket_run(const EmbedArgs& a, const BucketPlan& p, const int64_t* 
                         unsigned long long* acc, hipStream_t s) {
   uint32_t* cursor = (uint32_t*)(base + p.cursor_off);
   uint2* list = (uint2*)(base + p.list_off);
-  hipLaunchKernelGGL(k_embed_zero, dim3((p.nb + 255) / 256), dim3(256), 0, s, cursor, (int64_t)p.nb);
+  const AccPlan k = acc_plan(a, p, FIXED);
+  const int span = (1 << p.r_log2) + a.Z;
+  hipLaunchKernelGGL(k_embed_route_init, dim3((unsigned)p.nb), dim3(256), 0, s, k, span, cursor, list);
   // Chunks per route workgroup: 8192 (long runs per bucket, few reservations) once that leaves a
   // workgroup for every CU, fewer for smaller batches (0.85 M chunks: 2048 instead of 8192, -9 us).
   int items = kRouteItems;
@@ -748,11 +830,10 @@ roast_status bucket_run(const EmbedArgs& a, const BucketPlan& p, const int64_t* 
   }
   hipLaunchKernelGGL(k_embed_route<FIXED>, dim3((unsigned)((a.N + rows_wg - 1) / rows_wg)), dim3(kRouteThreads), lds_route, s, a,
                      p.r_log2, p.nb, p.cap, walk_ok(a), items, rows, tables, cursor, list, dOut, dM, pbits, fs, acc);
-  const int seg_len = kSegValues / a.Z;
-  const int segs = (int)((p.cap + seg_len - 1) / seg_len);
-  const size_t lds = ((size_t)(1 << p.r_log2) + a.Z) * 8;
-  hipLaunchKernelGGL(k_embed_accum<FIXED>, dim3((unsigned)(p.nb * segs)), dim3(kAccThreads), lds, s, a, p.r_log2, p.cap, p.nb,
-                     (uint32_t)seg_len, cursor, list, dOut, dM, pbits, fs, acc);
+  hipLaunchKernelGGL(k_embed_accum<FIXED>, dim3((unsigned)p.nb * k.most), dim3(kAccThreads), (size_t)span * 8, s, a, k, cursor, list, dOut,
+                     dM, pbits, fs, acc);
+  if (k.sums)
+    hipLaunchKernelGGL(k_embed_add_sums, dim3((unsigned)((a.m_size + 1023) / 1024)), dim3(256), 0, s, a, k, cursor, list, dM);
   return hip_status(hipGetLastError());
 }
 

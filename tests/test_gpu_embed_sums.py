@@ -40,3 +40,55 @@ def test_a_popular_row_keeps_its_digits(roast, N, D, Z):
     got = gradient(roast, h, D, Z, m_size, rows, tables, dOut)
     roundings = 2 * 2 * np.ceil((2 * mean + 8192) / 8192)
     assert np.all(np.abs(got - ref) <= roundings * ULP * mass)
+
+
+@pytest.mark.parametrize("N,D,Z,m_size", [
+    (65_536, 32, 32, 200_003),      # 1337 chunks to a bucket: one segment
+    (65_536, 32, 32, 50_021),       # 5041: several, their sums meet in fp64
+    (60_001, 64, 16, 190_000),
+    (20_000, 512, 128, 300_000),
+    (40_000, 512, 256, 600_000),    # one or two segments
+    (66_000, 1024, 1024, 500_000),  # chunks as long as a quarter of a bucket
+])
+def test_a_slot_is_rounded_once(roast, N, D, Z, m_size):
+    """No bucket has more than 8192 chunks, and dM is zero before: the gradient of a slot is the fp64 sum, rounded to
+    fp32 once (twice, and added, where the chunks of two buckets meet: a bucket's first Z slots)."""
+    rng = np.random.default_rng(N + Z)
+    h = wl.draw_hash(rng, use_sign=True, align=1)
+    rows = np.where(rng.random(N) < 1800 / N, 7, rng.integers(0, 1 << 33, N)).astype(np.int64)
+    tables = np.full(N, 3, dtype=np.uint32)
+    dOut = rng.uniform(0.5, 1.5, (N, D)).astype(np.float32)
+    off, _ = roast.roast_chunk_index_device(roast.embed_desc(D, Z, m_size, 1.0, h), to_dev(rows), to_dev(tables))
+    load = np.bincount(off.cpu().numpy().reshape(-1) >> 12, minlength=-(-m_size // 4096))
+    assert load.max() <= 8192
+    ref = oracle.embed_bwd(h, D, Z, m_size, 1.0, rows, tables, dOut)
+    mass = oracle.embed_bwd(dict(h, use_sign=0), D, Z, m_size, 1.0, rows, tables, dOut)
+    err = np.abs(gradient(roast, h, D, Z, m_size, rows, tables, dOut) - ref)
+    half = 0.5 * np.spacing(np.abs(ref).astype(np.float32)).astype(np.float64)
+    exact = 2.0 ** -40 * mass                       # the fp64 sums of either side, thousands of addends
+    inside = np.arange(m_size) % 4096 >= Z
+    assert np.all(err[inside] <= half[inside] + exact[inside])
+    assert np.all(err <= 3 * ULP * mass + exact)
+
+
+def test_gradients_of_two_streams_into_one_array(roast):
+    """Calls on different streams may add to one dM at the same time: nothing is lost."""
+    N, D, Z, m_size = 65_536, 32, 32, 50_021
+    rng = np.random.default_rng(5)
+    h = wl.draw_hash(rng, use_sign=True, align=1)
+    d = roast.embed_desc(D, Z, m_size, 1.0, h)
+    dM = torch.zeros(m_size, device="cuda")
+    streams, held, ref = [torch.cuda.Stream() for _ in range(2)], [], 0.0
+    for _ in streams:
+        rows, tables = rng.integers(0, 1 << 33, N), np.zeros(N, dtype=np.uint32)
+        dOut = rng.integers(-4, 5, (N, D)).astype(np.float32)                # whole numbers: exact in any order
+        ref = ref + 3 * oracle.embed_bwd(h, D, Z, m_size, 1.0, rows, tables, dOut)
+        ws = torch.empty(roast.roast_embed_bwd_workspace(d, N, roast.ROAST_REDUCE_ATOMIC), dtype=torch.uint8, device="cuda")
+        held.append((to_dev(rows), to_dev(tables), to_dev(dOut), ws))
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for s, (rows, tables, dOut, ws) in zip(streams, held):
+            with torch.cuda.stream(s):
+                roast.roast_embed_bwd(d, rows, tables, dOut, dM, roast.ROAST_REDUCE_ATOMIC, ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_host_f64(dM), ref)
