@@ -1339,7 +1339,7 @@ int mfma_dx_strip(const MMArgs& a, bool shadow) {
   return pick_ntile(cdiv(a.I, kBM), a.H, a.Z1, a.O / BK, a.nTy);
 }
 
-// (the same with and without a shadow, so that both give the same sums)
+// (the same with and without a shadow, so that both give the same sums; see parts_for_both in roast_mm_wide.hip)
 int mfma_fwd_splits(const MMArgs& a) {
   const WidePlan w = wide_fwd_plan(a, kWideParts, false);
   if (w.bm) return w.parts;

@@ -947,14 +947,37 @@ double rounds_of(double wgs) {                     // of 256 workgroups; a last 
   return r <= 1.0 ? 1.0 : 0.63 * std::ceil(r) + 0.37 * r;
 }
 
+// A call without a copy of M runs on the 256 x 128 kernel, in as many parts (both give the same sums).  Where the number
+// that is best here costs that kernel over a tenth more than its own best, the one with the least
+// time of both together, among those close to the best here: within 7 %, or, if the best is no split at all, 5 % less
+// half a microsecond (a first split is a launch more, which the model sees too small on short calls: 168 x 392 x 552
+// would go from 11.2 to 13.3 us with a copy).  With a copy and without, by the best here and by this rule:
+// 64 x 4096 x 4096 17.9 and 27.4 -> 17.4 and 19.7 us, 126 x 5480 x 4264 22.2 and 43.6 -> 22.4 and 29.3,
+// 1024 x 2048 x 2048 25.1 and 34.9 -> 25.4 and 28.6.
+int parts_for_both(int64_t I, int64_t N, int64_t K, const double* cost_of, int best) {
+  const int64_t tiles = cdiv(N, 128) * cdiv(I, 256);
+  double narrow[kWideParts + 1], least = 1e300;
+  for (int parts = 1; parts <= kWideParts; ++parts) {
+    narrow[parts] = (double)cdiv(tiles * parts, 256) * (0.95 * (double)cdiv(cdiv(K, parts), BK) + 4.0) +
+                    (parts > 1 ? 4.0 + (double)parts * (double)I * (double)N * 4.0 / 3.0e6 : 0.0);
+    least = std::min(least, narrow[parts]);
+  }
+  if (narrow[best] <= 1.1 * least) return best;
+  const double limit = best == 1 ? 1.05 * cost_of[1] - 0.5 : 1.07 * cost_of[best];
+  for (int parts = 1; parts <= kWideParts; ++parts)
+    if (cost_of[parts] <= limit && cost_of[parts] + narrow[parts] < cost_of[best] + narrow[best]) best = parts;
+  return best;
+}
+
 // which: MODE_FWD / MODE_DX; max_parts == 1: no workspace for a split
 WidePlan plan_hashed(int which, const MMArgs& a, int max_parts, bool x3) {
-  WidePlan best{};
-  if (!hashed_ok(a)) return best;
+  if (!hashed_ok(a)) return {};
   const int64_t N = which == MODE_FWD ? a.O : a.H, K = which == MODE_FWD ? a.H : a.O;
   const int64_t zn = which == MODE_FWD ? a.Z2 : a.Z1, zk = which == MODE_FWD ? a.Z1 : a.Z2;
   const int pairs = x3 ? 6 : 1;
-  double best_cost = 1e300;
+  WidePlan of[kWideParts + 1];                     // the fastest launch with each number of parts
+  double cost_of[kWideParts + 1];
+  std::fill(cost_of, cost_of + kWideParts + 1, 1e300);
   for (const Block& b : kBlocks) {
     for (int64_t t = 1; t <= 4; ++t) {
       // a strip: whole blocks of whole tiles, no ragged step, two steps to a block at least
@@ -970,14 +993,17 @@ WidePlan plan_hashed(int which, const MMArgs& a, int max_parts, bool x3) {
         const double step = b.step + b.busy * std::min(wgs / 256.0, 1.0);
         double cost = rounds_of(wgs) * ((double)(steps * t * pairs) * step + b.fixed + b.more * (double)(t - 1));
         if (parts > 1) cost += 3.8 + (double)parts * (double)a.I * (double)N * 4.0 / 3.0e6;   // the pass over the partial outputs
-        if (cost < best_cost) {
-          best_cost = cost;
-          best = {b.bm, b.bn, (int)t, parts, (int)(steps * BK)};
+        if (cost < cost_of[parts]) {
+          cost_of[parts] = cost;
+          of[parts] = {b.bm, b.bn, (int)t, parts, (int)(steps * BK)};
         }
       }
     }
   }
-  return best;
+  int best = (int)(std::min_element(cost_of + 1, cost_of + max_parts + 1) - cost_of);
+  if (cost_of[best] == 1e300) return {};
+  if (!x3 && max_parts > 1) best = parts_for_both(a.I, N, K, cost_of, best);
+  return of[best];
 }
 
 // parts > 0: the number of parts is given (and the products go to a workspace)

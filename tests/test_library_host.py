@@ -112,3 +112,14 @@ def test_strip_diagnostic_on_config_shapes_and_bad_arguments():
     assert roast.roast_mm_strip_blocks(d, 0, 0) == 0 and roast.roast_mm_strip_blocks(d, 8192, 2) == 0
     bad = roast.mm_desc(768, 3072, 64, 64, 100, 1, np.float32(1.0), h)   # |M| smaller than a tile
     assert roast.roast_mm_strip_blocks(bad, 8192, 0) == 0
+
+
+@pytest.mark.parametrize("I,H,O", [(16, 4096, 4096), (64, 4096, 4096), (1024, 2048, 2048), (25, 5224, 2608), (126, 5480, 4264), (4096, 2048, 512)])
+def test_parts_of_a_split_suit_the_kernel_without_a_copy_too(I, H, O):
+    """bf16 forward with a workspace: calls with and without the copy of M run in the same number of parts.  The
+    256 x 128 blocks that the latter run on fill the chip (none of them alone leaves it idle), and wait for no second round."""
+    import torch
+    d = binding.mm_desc(H, O, 64, 64, 1 << 20, 0, np.float32(1.0), wl.draw_hash(np.random.default_rng(2)))
+    parts = max(binding.roast_mm_fwd_workspace(d, torch.bfloat16, I) // (4 * I * O), 1)
+    blocks = -(-I // 256) * -(-O // 128) * parts
+    assert 128 <= blocks <= 256
