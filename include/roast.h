@@ -193,12 +193,12 @@ roast_status roast_mm_bwd_dx(const roast_mm_desc* d, roast_dtype dt, int64_t I, 
  * reused by the next call on the same stream.  Results are deterministic for a fixed shape.
  */
 /*
- * fp32 calls only: the three bfloat16 planes of M (each in the layout of the bf16 shadow), made once
+ * fp32 calls only: the three bfloat16 planes of M (two copies of each, the second shifted by one element), made once
  * per update of M and passed as `M_bf16` to fp32 roast_mm_fwd_ws / roast_mm_bwd_dx_ws calls, which
  * otherwise rebuild them in their workspace on every call (a pass over |M|).
  * NOTE: the `M_bf16` argument therefore names a different buffer per dtype -- ROAST_BF16 calls take
  * the shadow (roast_m_shadow_bytes), ROAST_F32 calls with a workspace take the planes
- * (roast_m_planes_bytes, three times as large).  The C-ABI carries no size for it and cannot tell
+ * (roast_m_planes_bytes, larger).  The C-ABI carries no size for it and cannot tell
  * them apart: passing a shadow to an fp32 call makes the kernels read past its end.  NULL is always
  * safe.
  * planes: DEVICE buffer of roast_m_planes_bytes(m_size) bytes, 16-byte aligned, owned by the caller.

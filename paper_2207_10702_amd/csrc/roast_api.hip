@@ -1,6 +1,5 @@
 // C-ABI entry points: argument validation on the host, then dispatch to the kernels.
 // Nothing here allocates device memory or synchronises.
-#include <algorithm>
 #include "roast.h"
 #include "roast_internal.hpp"
 
@@ -112,10 +111,7 @@ size_t roast_m_shadow_bytes(int64_t m_size) {
   return m_size > 0 ? (size_t)(shadow_copies(m_size) * shadow_stride(m_size)) * 2 : 0;
 }
 
-// (three shadows' worth, as the header says, also where the shadow of a small M has copies the planes do not use)
-size_t roast_m_planes_bytes(int64_t m_size) {
-  return m_size > 0 ? std::max(m_planes_bytes(m_size), 3 * roast_m_shadow_bytes(m_size)) : 0;
-}
+size_t roast_m_planes_bytes(int64_t m_size) { return m_size > 0 ? m_planes_bytes(m_size) : 0; }
 
 roast_status roast_m_planes_bf16(const float* M, int64_t m_size, void* planes, void* stream) {
   drop_stale_error();

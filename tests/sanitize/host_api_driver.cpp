@@ -66,7 +66,7 @@ int main() {
     roast_optim_desc o{ROAST_OPT_ADAM, 1e-3f, 0.f, 0.9f, 0.999f, 1e-8f, 0, 1};
     bad += roast_optim_step(&o, 16, &x, &x, &x, &x, nullptr, nullptr) != ROAST_ERR_ARG;   // step < 1
     bad += roast_m_shadow_bytes(47185) < 2 * 2 * 47185;
-    bad += roast_m_planes_bytes(47185) < 3 * roast_m_shadow_bytes(47185);
+    bad += roast_m_planes_bytes(47185) < 3 * 2 * 2 * 47185;
     bad += roast_m_shadow_bf16(&x, -1, &x, nullptr) != ROAST_ERR_ARG;
   }
   for (int s = 0; s <= 7; ++s) bad += roast_status_string((roast_status)s) == nullptr;

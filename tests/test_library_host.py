@@ -123,3 +123,9 @@ def test_parts_of_a_split_suit_the_kernel_without_a_copy_too(I, H, O):
     parts = max(binding.roast_mm_fwd_workspace(d, torch.bfloat16, I) // (4 * I * O), 1)
     blocks = -(-I // 256) * -(-O // 128) * parts
     assert 128 <= blocks <= 256
+
+
+@pytest.mark.parametrize("m", [1, 63, 64, 47185, 4 << 20, (4 << 20) + 1, 64 << 20])
+def test_planes_take_what_they_use(m):
+    """Three planes of two bf16 copies each, padded to 64 elements, whatever copies the shadow of an M of that size has."""
+    assert binding.roast_m_planes_bytes(m) == 3 * 2 * 2 * ((m + 1 + 63) // 64 * 64)
