@@ -92,6 +92,8 @@ __device__ inline int lds_off(int row, int chunk) {
   return row * 128 + (((chunk ^ row ^ (row >> 3)) & 7) << 4);
 }
 
+__device__ const uint16_t kZeroPiece[8] __attribute__((aligned(16))) = {};   // what lies beyond a ragged contraction length
+
 struct KernArgs {
   MMArgs a;
   const uint16_t* A;   // FWD: X, DX: dY, DM: X
@@ -458,15 +460,15 @@ __global__ __launch_bounds__((WGM * WGN + 8) * 64) void k_roast_mfma(KernArgs p)
         const int64_t pl = X3 ? step_asel(st) * p.a_plane : 0;
         char* dst = a_stage(step) + (wave - NC) * (BM / 4) * 128;
         // A ragged contraction length (a multiple of 8, not of 64): the 16-byte pieces of the last
-        // step that lie beyond it are fetched from the start of the row instead (any finite value
-        // will do: the weight rows they meet are staged as zeros).  ch(q) = ch(0) ^ q, see above.
+        // step that lie beyond it are zeros (the weight rows they meet are staged as zeros too, but
+        // whatever else is in the row may be an infinity).  ch(q) = ch(0) ^ q, see above.
         const bool ragged = RAGK && kk + BK > k_end;
         const int ch0 = (lane ^ (lane >> 3)) & 7;
 #pragma unroll
         for (int q = 0; q < Ctx::A_LOADS; ++q) {
           const int ch8 = 8 * (ch0 ^ (q & 7));
-          const int64_t koff = (RAGK && ragged && kk + ch8 >= k_end) ? pl - ch8 : pl + kk;
-          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(c.a_ptr[q] + koff),
+          const uint16_t* src = (RAGK && ragged && kk + ch8 >= k_end) ? kZeroPiece : c.a_ptr[q] + (pl + kk);
+          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                            (__attribute__((address_space(3))) void*)(dst + q * 1024), 16, 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);

@@ -262,7 +262,7 @@ __global__ __launch_bounds__(512, 2) void k_roast_mfma_wide(WideArgs p) {
     AStep r;
     const int64_t pl = X3 ? asel(s) * p.a_plane : 0;
     if constexpr (!TA) {
-      // pieces beyond a ragged contraction length come from the start of the row (the weights they meet are zeroed)
+      // pieces beyond a ragged contraction length come from the start of the row (and are zeroed, see cut)
       const int kc = s.k + 8 * a_ch;
       r.off = kc < k_end ? 2u * (uint32_t)kc : 0u;
       r.base = pl;
@@ -525,9 +525,11 @@ __global__ __launch_bounds__(512, 2) void k_roast_mfma_wide(WideArgs p) {
       }
     }
   };
-  // the last step of a contraction length that is not a multiple of 64: zeros, in the weight fragments alone (the
-  // activations they meet are of the same row), and in both of dM's, where an infinity of the last token
-  // times a zero would be a NaN that the sum does not have
+  // the last step of a contraction length that is not a multiple of 64: zeros, in the fragments of both operands, since
+  // what was loaded there (the start of the row, the last token again) may be an infinity, which times a zero would
+  // be a NaN that the sum does not have (fp32 planes: the weights' alone, an infinity makes a NaN in any case, of its
+  // zero planes)
+  constexpr bool CUT_A = MODE == MODE_DM || !X3;
   auto cut = [&](auto KIND, auto KS) {
     constexpr int ks = decltype(KS)::value;
     if constexpr (decltype(KIND)::value < 2) return;   // (LAST, TAIL)
@@ -539,7 +541,7 @@ __global__ __launch_bounds__(512, 2) void k_roast_mfma_wide(WideArgs p) {
         const uint32_t keep = cnt >= 2 * d + 2 ? 0xffffffffu : (cnt == 2 * d + 1 ? 0x0000ffffu : 0u);
 #pragma unroll
         for (int j = 0; j < NJ; ++j) bf[ks][j][d] &= keep;
-        if constexpr (MODE == MODE_DM) {
+        if constexpr (CUT_A) {
 #pragma unroll
           for (int i = 0; i < MI; ++i) af[ks][i][d] &= keep;
         }
@@ -685,7 +687,7 @@ __global__ __launch_bounds__(512, 2) void k_roast_mfma_wide(WideArgs p) {
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(LA));
     tie_a(I0{});
-    if constexpr (MODE == MODE_DM) cut(KIND, I0{});
+    if constexpr (CUT_A) cut(KIND, I0{});
     if constexpr (MORE) wait_loads(KIND, std::integral_constant<int, 5>{});          // B and A quarters 0, 1 of step t+1 have landed
     __builtin_amdgcn_s_barrier();
     products(I2{}, I2{}, [&] {
@@ -704,7 +706,7 @@ __global__ __launch_bounds__(512, 2) void k_roast_mfma_wide(WideArgs p) {
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(MORE ? LAB : 0));
     tie_a(I1{});
-    if constexpr (MODE == MODE_DM) cut(KIND, I1{});
+    if constexpr (CUT_A) cut(KIND, I1{});
     __builtin_amdgcn_s_barrier();
     products(I3{}, std::integral_constant<int, MORE ? 0 : 2>{}, [&] {
       if constexpr (MORE) {

@@ -112,3 +112,27 @@ def test_infinity_in_the_last_token_stays_an_infinity(roast, shape):
     dM = dM.view(128, 128).cpu()
     assert torch.all(dM[5] == float("inf"))
     assert torch.all(torch.isfinite(dM[torch.arange(128) != 5]))
+
+
+@pytest.mark.parametrize("H,O,Z1,Z2", [(72, 200, 32, 32), (200, 72, 128, 32),       # 32: wide blocks with a copy of M
+                                       (1096, 520, 64, 64), (520, 1096, 64, 64),    # (a contraction of several parts, with a workspace)
+                                       (72, 200, 8, 8),                             # blocks of 128 columns, with and without a copy
+                                       (72, 200, 5, 3)])                            # element by element
+def test_infinity_in_a_row_stays_an_infinity(roast, H, O, Z1, Z2):
+    """A ragged contraction: what fills the last step of forward / dX meets no infinity of the row.  No signs and
+    M > 0: the row of that infinity is +inf, the others are finite."""
+    I, m = 300, Z1 * Z2 + 1
+    h = wl.draw_hash(np.random.default_rng(H), use_sign=False, align=1)
+    d = roast.mm_desc(H, O, Z1, Z2, m, 0, 1.0, h)
+    g = torch.Generator(device="cuda").manual_seed(H)
+    M = torch.rand(m, generator=g, device="cuda") + 0.5
+    Mb = roast.roast_m_shadow_bf16(M)
+    for n, call, want in ((H, roast.roast_mm_fwd, roast.roast_mm_fwd_workspace), (O, roast.roast_mm_bwd_dx, roast.roast_mm_bwd_dx_workspace)):
+        A = torch.randn((I, n), generator=g, device="cuda").bfloat16()
+        A[3, 5] = float("inf")                                                      # in the row's first piece
+        A[299, n - 1] = float("inf")                                                # in its last
+        for copy in (None, Mb):
+            for ws in (None, torch.empty(max(want(d, torch.bfloat16, I), 16), dtype=torch.uint8, device="cuda")):
+                R = call(d, A, M, M_bf16=copy, ws=ws).cpu()
+                assert torch.all(R[[3, 299]] == float("inf"))
+                assert torch.all(torch.isfinite(R[[r for r in range(I) if r not in (3, 299)]]))
