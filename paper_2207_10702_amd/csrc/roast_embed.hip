@@ -417,12 +417,13 @@ struct AccPlan {
   uint32_t cap, seg_len, most;
   bool sums;
 };
-inline AccPlan acc_plan(const EmbedArgs& a, const BucketPlan& p, bool fixed) {
+// The sums are added to with 64-bit atomics, so a list that is not 8-byte aligned (a workspace at a multiple of 4) has none.
+inline AccPlan acc_plan(const EmbedArgs& a, const BucketPlan& p, bool fixed, const void* list) {
   AccPlan k{p.r_log2, p.nb, p.cap, (uint32_t)kSeg, 0, false};
   const int64_t mean = p.n_items / p.nb;
   if (fixed) {
     k.seg_len = (uint32_t)std::min(kSeg, kFixedValues / a.Z);
-  } else if (mean <= kSeg && mean * a.Z >= 65536 && p.nb < 1024) {
+  } else if (mean <= kSeg && mean * a.Z >= 65536 && p.nb < 1024 && ((uintptr_t)list & 7) == 0) {
     k.sums = true;
     k.seg_len = (uint32_t)std::min(kSeg, kSumValues / a.Z);
   }
@@ -807,7 +808,7 @@ roast_status bucket_run(const EmbedArgs& a, const BucketPlan& p, const int64_t* 
                         unsigned long long* acc, hipStream_t s) {
   uint32_t* cursor = (uint32_t*)(base + p.cursor_off);
   uint2* list = (uint2*)(base + p.list_off);
-  const AccPlan k = acc_plan(a, p, FIXED);
+  const AccPlan k = acc_plan(a, p, FIXED, list);
   const int span = (1 << p.r_log2) + a.Z;
   hipLaunchKernelGGL(k_embed_route_init, dim3((unsigned)p.nb), dim3(256), 0, s, k, span, cursor, list);
   // Chunks per route workgroup: 8192 (long runs per bucket, few reservations) once that leaves a

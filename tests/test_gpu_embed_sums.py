@@ -71,6 +71,24 @@ def test_a_slot_is_rounded_once(roast, N, D, Z, m_size):
     assert np.all(err <= 3 * ULP * mass + exact)
 
 
+def test_a_workspace_at_any_multiple_of_four_bytes(roast):
+    """Sums of a bucket are added to in 64-bit atomics, which only take addresses that are multiples of 8: a workspace
+    that is not has none.  Whole numbers: exact either way."""
+    N, D, Z, m_size = 65_536, 32, 32, 50_021
+    rng = np.random.default_rng(6)
+    h = wl.draw_hash(rng, use_sign=True, align=1)
+    d = roast.embed_desc(D, Z, m_size, 1.0, h)
+    rows, tables = rng.integers(0, 1 << 33, N), np.zeros(N, dtype=np.uint32)
+    dOut = rng.integers(-4, 5, (N, D)).astype(np.float32)
+    ref = oracle.embed_bwd(h, D, Z, m_size, 1.0, rows, tables, dOut)
+    need = roast.roast_embed_bwd_workspace(d, N, roast.ROAST_REDUCE_ATOMIC)
+    ws = torch.empty(need + 16, dtype=torch.uint8, device="cuda")
+    for at in (0, 4, 8, 12):
+        dM = torch.zeros(m_size, device="cuda")
+        roast.roast_embed_bwd(d, to_dev(rows), to_dev(tables), to_dev(dOut), dM, roast.ROAST_REDUCE_ATOMIC, ws[at:at + need])
+        assert np.array_equal(to_host_f64(dM), ref), at
+
+
 def test_gradients_of_two_streams_into_one_array(roast):
     """Calls on different streams may add to one dM at the same time: nothing is lost."""
     N, D, Z, m_size = 65_536, 32, 32, 50_021
