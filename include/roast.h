@@ -223,10 +223,24 @@ roast_status roast_mm_bwd_dx_ws(const roast_mm_desc* d, roast_dtype dt, int64_t 
  * row block i, the column blocks j of its strip in turn, the contraction k innermost.  1 = one block
  * per workgroup (also for shapes that take other kernels); 0 = invalid descriptor, I or `which`.
  * It speaks of the 128-column kernels; shapes with tiles that are multiples of 32 run on wider blocks
- * when there is a shadow, and choose block and strip for themselves.
+ * when there is a shadow (roast_mm_wide_blocks).
  * For tests (which must know that a shape exercises the strip path) and for tuning.
  */
 int roast_mm_strip_blocks(const roast_mm_desc* d, int64_t I, int which);
+
+/* A launch on the wide blocks: rows x columns of the output block, consecutive column blocks of a workgroup, parts of
+ * the contraction. */
+typedef struct {
+  int32_t rows, columns, strip, parts;
+} roast_mm_blocks;
+
+/*
+ * The same for the wide blocks: what roast_mm_fwd (which = 0) or roast_mm_bwd_dx (1) launch with a copy of M (fp32: with a
+ * workspace), or roast_mm_bwd_dM (2; ATOMIC, bf16 without a workspace, fp32 with one).  workspace: 1 if a forward / dX
+ * call has one, else 0.  1 and *out when they take the shape; 0 and zeros in *out when it runs on other kernels or the
+ * descriptor, I, `dt`, `which` or `out` is invalid.
+ */
+int roast_mm_wide_blocks(const roast_mm_desc* d, roast_dtype dt, int64_t I, int which, int workspace, roast_mm_blocks* out);
 
 /* Bytes of workspace roast_mm_bwd_dM can use for these sizes and mode (0 = none).
  * DETERMINISTIC: required.  ATOMIC: optional -- with it (bf16 path, contraction split over several

@@ -151,6 +151,17 @@ int roast_mm_strip_blocks(const roast_mm_desc* d, int64_t I, int which) {
   return which == 0 ? mfma_fwd_strip(a, true) : mfma_dx_strip(a, true);
 }
 
+int roast_mm_wide_blocks(const roast_mm_desc* d, roast_dtype dt, int64_t I, int which, int workspace, roast_mm_blocks* out) {
+  if (!out) return 0;
+  *out = roast_mm_blocks{0, 0, 0, 0};
+  MMArgs a;
+  if (make_mm_args(d, I, &a) != ROAST_OK || I <= 0 || !dtype_ok(dt) || which < 0 || which > 2) return 0;
+  const WidePlan w = mm_wide_plan(a, dt == ROAST_F32, which, workspace != 0);
+  if (w.bm == 0) return 0;
+  *out = roast_mm_blocks{w.bm, w.bn, w.nblk, w.parts};
+  return 1;
+}
+
 roast_status roast_mm_fwd_ws(const roast_mm_desc* d, roast_dtype dt, int64_t I, const void* X, int64_t ldx,
                              const float* M, const void* M_bf16, void* Y, int64_t ldy, void* workspace,
                              size_t workspace_bytes, void* stream) {

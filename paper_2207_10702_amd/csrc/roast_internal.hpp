@@ -154,6 +154,8 @@ constexpr int kWideParts = 16;
 WidePlan wide_fwd_plan(const MMArgs& a, int max_parts, bool x3);   // max_parts: 1 where no workspace is given, else kWideParts
 WidePlan wide_dx_plan(const MMArgs& a, int max_parts, bool x3);
 WidePlan wide_dm_plan(const MMArgs& a, int parts, bool x3);        // parts == 0: atomic adds, any number of parts
+// what a call with a copy of M runs on (which: 0 forward, 1 dX, 2 dM with atomic adds), for the diagnostic
+WidePlan mm_wide_plan(const MMArgs& a, bool f32, int which, bool workspace);
 roast_status wide_mm(int which, const MMArgs& a, const WidePlan& plan, const uint16_t* A, int64_t lda, int64_t a_plane,
                      const uint16_t* Mb, bool x3, uint16_t* C, float* C32, int64_t ldc, float* ws, hipStream_t s);
 roast_status wide_mm_dM(const MMArgs& a, const WidePlan& plan, const uint16_t* X, int64_t ldx, int64_t a_plane, const uint16_t* dY,

@@ -1623,4 +1623,12 @@ roast_status x3_mm_bwd_dM(const MMArgs& a, const float* X, int64_t ldx, const fl
   return launch<MODE_DM, kBM, kBN, 4, 2, false, true>(p, grid, s);
 }
 
+WidePlan mm_wide_plan(const MMArgs& a, bool f32, int which, bool workspace) {
+  if (f32 && !(which == 2 ? x3_dm_ok(a) : workspace && (which == 0 ? x3_fwd_ok(a) : x3_dx_ok(a)))) return {};
+  if (!f32 && !(which == 2 ? a.H >= kBM / 32 && a.O >= kBN / 32 : mfma_elem_ok(a))) return {};
+  if (which == 2) return wide_dm_plan(a, 0, f32);
+  const int parts = workspace ? kWideParts : 1;
+  return which == 0 ? wide_fwd_plan(a, parts, f32) : wide_dx_plan(a, parts, f32);
+}
+
 }  // namespace roast

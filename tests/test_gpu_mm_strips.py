@@ -1,9 +1,10 @@
-"""GPU parity of the strip launches of the bf16 forward and dX products: where short blocks would
+"""GPU parity of the strip launches of the 128-column bf16 forward and dX products: where short blocks would
 queue for the CUs, one workgroup computes several consecutive 128-column blocks as one run of
 contraction steps and stores the inner ones through a small staging area.  Same oracle, same bf16 bar
 as the plain calls; the shapes are chosen so that strips of 2, 3 and 4 blocks form (checked through the
-library's diagnostic), with ragged row counts, padded leading dimensions, tile shapes from 8 to 128
-and both weight sources (bf16 shadow, fp32 M)."""
+library's diagnostics), with ragged row counts, padded leading dimensions and tile shapes from 8 to 128.
+Weights from fp32 M run on these strips whatever the tiles; weights from the bf16 shadow do where a
+tile extent is no multiple of 32, and on the wide blocks (tests/test_gpu_mm_wide.py) else."""
 import numpy as np
 import pytest
 
@@ -24,6 +25,12 @@ SHAPES = [
     (2048, 256, 8192, 16, 8, 9000, 2, 1),        # 512 blocks -> strips of 2; 16 hash tiles per block
     (2048, 8192, 256, 8, 16, 9000, 1, 2),
     (1800, 64, 24576, 64, 128, 70000, 3, 1),     # one contraction step per block, 1536 blocks -> 512 strips of 3
+    # from the shadow too
+    (2048, 128, 16384, 16, 64, 60000, 4, 1),
+    (2048, 16384, 128, 64, 16, 60000, 1, 4),
+    (2048, 128, 16384, 64, 8, 60000, 4, 1),
+    (2000, 192, 12288, 8, 128, 50000, 3, 1),
+    (2000, 12288, 192, 128, 8, 50000, 1, 3),
 ]
 
 
@@ -39,6 +46,8 @@ def test_strip_launches_match_oracle(roast, shape, pad):
     lam = np.float32(0.37)
     d = roast.mm_desc(H, O, Z1, Z2, m, 5, lam, h)
     assert roast.roast_mm_strip_blocks(d, I, 0) == tf and roast.roast_mm_strip_blocks(d, I, 1) == tx
+    for which in (0, 1):                                    # where the call with the shadow runs
+        assert (roast.roast_mm_wide_blocks(d, torch.bfloat16, I, which) is None) == (Z1 % 32 != 0 or Z2 % 32 != 0)
     Md = to_dev(M)
     Mb = roast.roast_m_shadow_bf16(Md)
     Xd = torch.zeros((I, H + pad), dtype=torch.bfloat16, device="cuda")[:, :H]

@@ -21,15 +21,55 @@ SHAPES = [
     (255, 128, 128, 128, 128, 16384),      # |M| == one tile: every tile at base 0
     (300, 1096, 520, 32, 96, 30000),       # contraction split (with a workspace), ragged last part
     (8200, 520, 776, 64, 64, 47185),       # many rows: uneven dM parts
-    (2100, 192, 6144, 64, 64, 33333),      # strips
+    (2100, 192, 6144, 64, 64, 33333),      # 256 x 256 blocks, ragged rows
     (2100, 6144, 192, 64, 64, 33333),
-    (5000, 1024, 4096, 128, 64, 100003),   # 256 x 256 blocks, ragged rows
+    (5000, 1024, 4096, 128, 64, 100003),   # 256 x 192 blocks
+    (509, 1344, 5632, 128, 64, 100003),    # dM: 256 x 256 blocks
+    (516, 1664, 4672, 128, 128, 100003),   # fp32 dM: 256 x 192
+    (3747, 128, 4608, 128, 64, 100003),    # strips, ragged rows
+    (3747, 4608, 128, 64, 128, 100003),
+    (1585, 128, 14592, 64, 64, 100003),
+    (6958, 128, 3456, 32, 64, 100003),
+    (5855, 5760, 128, 64, 128, 100003),
     # |M| beyond 4 Mi: the shadow has no negated copies
     (129, 72, 200, 64, 32, 5000001),
     (300, 1096, 520, 32, 96, 4300000),
     (2100, 192, 6144, 64, 64, 4300001),
     (5000, 1024, 4096, 128, 64, 4300001),
+    (3747, 128, 4608, 128, 64, 4300001),
+    (1585, 14592, 128, 64, 64, 4300001),
+    (6958, 3456, 128, 64, 32, 4300001),
+    (5855, 128, 5760, 128, 64, 4300001),
 ]
+
+FWD, DX, DM = 0, 1, 2
+BF16, F32 = torch.bfloat16, torch.float32
+# What some of them are there for: (I, H, O) -> (which product, type, workspace given, (rows, columns, strip, parts))
+BLOCKS = {
+    (1, 8, 8): [(FWD, BF16, False, (256, 128, 1, 1))],
+    (257, 136, 264): [(FWD, BF16, False, (128, 192, 1, 1)), (DX, BF16, False, (128, 192, 1, 1))],
+    (300, 1096, 520): [(FWD, BF16, True, (128, 192, 1, 6)), (DX, F32, True, (128, 192, 1, 9))],
+    (8200, 520, 776): [(DM, BF16, False, (128, 192, 1, 7))],
+    (2100, 192, 6144): [(FWD, BF16, False, (256, 256, 1, 1)), (FWD, F32, True, (256, 256, 1, 1)), (DM, F32, True, (256, 128, 1, 5))],
+    (2100, 6144, 192): [(DX, BF16, False, (256, 256, 1, 1)), (DX, F32, True, (256, 256, 1, 1)), (FWD, BF16, True, (128, 192, 1, 12))],
+    (5000, 1024, 4096): [(FWD, BF16, False, (256, 192, 1, 1)), (DM, BF16, False, (256, 128, 1, 2))],
+    (509, 1344, 5632): [(DM, BF16, False, (256, 256, 1, 1)), (DM, F32, True, (256, 256, 1, 1))],
+    (516, 1664, 4672): [(DM, F32, True, (256, 192, 1, 1))],
+    (3747, 128, 4608): [(FWD, BF16, False, (128, 192, 3, 1))],
+    (3747, 4608, 128): [(DX, BF16, False, (128, 192, 3, 1))],
+    (1585, 128, 14592): [(FWD, BF16, True, (128, 192, 4, 1))],
+    (1585, 14592, 128): [(DX, BF16, True, (128, 192, 4, 1))],
+    (6958, 128, 3456): [(FWD, BF16, False, (256, 192, 2, 1))],
+    (6958, 3456, 128): [(DX, BF16, False, (256, 192, 2, 1)), (FWD, BF16, True, (256, 128, 1, 6))],
+    (5855, 128, 5760): [(FWD, BF16, False, (256, 192, 3, 1))],
+    (5855, 5760, 128): [(DX, BF16, False, (256, 192, 3, 1))],
+}
+
+
+def check_blocks(roast, shape, d):
+    """The shape still runs on the blocks that it is listed for."""
+    for which, dtype, workspace, blocks in BLOCKS.get(shape[:3], []):
+        assert roast.roast_mm_wide_blocks(d, dtype, shape[0], which, workspace) == blocks, (shape, which, dtype)
 
 
 @pytest.mark.parametrize("shape", SHAPES)
@@ -42,6 +82,7 @@ def test_wide_kernels_match_oracle(roast, shape, pad):
     dY = wl.draw_act(rng, I, O, "bf16")
     h = wl.draw_hash(rng, use_sign=True, align=1)
     d = roast.mm_desc(H, O, Z1, Z2, m, 2, np.float32(0.43), h)
+    check_blocks(roast, shape, d)
     Md = to_dev(M)
     Mb = roast.roast_m_shadow_bf16(Md)
 
@@ -82,6 +123,7 @@ def test_wide_plane_products_match_oracle(roast, shape):
     h = wl.draw_hash(rng, use_sign=True, align=1)
     lam = np.float32(0.43)
     d = roast.mm_desc(H, O, Z1, Z2, m, 2, lam, h)
+    check_blocks(roast, shape, d)
     Md, Xd, dYd = to_dev(M), to_dev(X), to_dev(dY)
     ws = lambda n: torch.full((max(n, 16),), 0xFF, dtype=torch.uint8, device="cuda")  # noqa: E731
     Y, dX, dM = torch.empty((I, O), device="cuda"), torch.empty((I, H), device="cuda"), torch.zeros(m, device="cuda")
@@ -94,6 +136,28 @@ def test_wide_plane_products_match_oracle(roast, shape):
     assert rel_err(to_host_f64(Y), oracle.mm_fwd(Xo, W)) <= F32_TOL
     assert rel_err(to_host_f64(dX), oracle.mm_bwd_dx(dYo, W)) <= F32_TOL
     assert rel_err(to_host_f64(dM), oracle.mm_bwd_dm(h, 2, Z1, Z2, m, float(lam), Xo, dYo)) <= F32_TOL
+
+
+@pytest.mark.parametrize("I", [9001, 8705, 32769])             # 18 parts; 18, the last of one token; 64, seven of them empty
+def test_deterministic_gradient_of_many_parts(roast, I):
+    """The reproducible gradient of M takes up to 64 parts of the tokens, whatever number the wide blocks would take."""
+    H, O, Z1, Z2, m = 136, 264, 96, 96, 20011
+    rng = np.random.default_rng(I)
+    h = wl.draw_hash(rng, use_sign=True, align=1)
+    lam = np.float32(0.43)
+    d = roast.mm_desc(H, O, Z1, Z2, m, 2, lam, h)
+    X, dY = wl.draw_act(rng, I, H, "bf16"), wl.draw_act(rng, I, O, "bf16")
+    Xd, dYd = to_dev(X), to_dev(dY)
+    need = roast.roast_mm_bwd_dM_workspace(d, I, roast.ROAST_REDUCE_DETERMINISTIC)
+    assert need >= 4 * H * O * min(-(-I // 512), 64)
+    got = []
+    for fill in (0xFF, 0x00):
+        dM = torch.zeros(m, device="cuda")
+        roast.roast_mm_bwd_dM(d, Xd, dYd, dM, roast.ROAST_REDUCE_DETERMINISTIC, torch.full((need,), fill, dtype=torch.uint8, device="cuda"))
+        got.append(dM)
+    assert torch.equal(got[0], got[1])
+    ref = oracle.mm_bwd_dm(h, 2, Z1, Z2, m, float(lam), wl.act_as_f64(X), wl.act_as_f64(dY))
+    assert rel_err(to_host_f64(got[0]), ref) <= F32_TOL
 
 
 @pytest.mark.parametrize("shape", [(67, 128, 128), (1027, 768, 1536), (4099, 4096, 4096)])

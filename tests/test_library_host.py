@@ -114,6 +114,26 @@ def test_strip_diagnostic_on_config_shapes_and_bad_arguments():
     assert roast.roast_mm_strip_blocks(bad, 8192, 0) == 0
 
 
+def test_wide_block_diagnostic():
+    """The blocks that the shapes of the GPU tests are listed for; None off the wide blocks and for bad arguments."""
+    import torch
+    from tests import test_gpu_mm_wide as wide
+    h = wl.draw_hash(np.random.default_rng(1), use_sign=True, align=1)
+    for shape in wide.SHAPES:
+        I, H, O, Z1, Z2, m = shape
+        wide.check_blocks(binding, shape, binding.mm_desc(H, O, Z1, Z2, m, 2, np.float32(1.0), h))
+    assert set(wide.BLOCKS) <= {s[:3] for s in wide.SHAPES}
+    d = binding.mm_desc(768, 3072, 64, 64, 47185, 1, np.float32(1.0), h)
+    assert binding.roast_mm_wide_blocks(d, torch.bfloat16, 8192, 0) == (256, 192, 2, 1)
+    assert binding.roast_mm_wide_blocks(d, torch.float32, 8192, 0) is None           # fp32 without a workspace
+    assert binding.roast_mm_wide_blocks(d, torch.bfloat16, 0, 0) is None and binding.roast_mm_wide_blocks(d, torch.bfloat16, 8192, 3) is None
+    d = binding.mm_desc(768, 3072, 64, 16, 47185, 1, np.float32(1.0), h)
+    assert binding.roast_mm_wide_blocks(d, torch.bfloat16, 8192, 1) is None          # tiles that are no multiples of 32
+    assert binding.roast_mm_wide_blocks(d, torch.bfloat16, 8192, 2) is not None      # which the gradient of M does not mind
+    bad = binding.mm_desc(768, 3072, 64, 64, 100, 1, np.float32(1.0), h)             # |M| smaller than a tile
+    assert binding.roast_mm_wide_blocks(bad, torch.bfloat16, 8192, 0) is None
+
+
 @pytest.mark.parametrize("I,H,O", [(16, 4096, 4096), (64, 4096, 4096), (1024, 2048, 2048), (25, 5224, 2608), (126, 5480, 4264), (4096, 2048, 512)])
 def test_parts_of_a_split_suit_the_kernel_without_a_copy_too(I, H, O):
     """bf16 forward with a workspace: calls with and without the copy of M run in the same number of parts.  The
