@@ -156,7 +156,7 @@ __global__ __launch_bounds__(512, 2) void k_roast_mfma_wide(WideArgs p) {
   constexpr bool ROWS = BN % 128 == 0;            // TB: LDS holds [k][BN] rows, else groups of 64 columns, [group][k][64]
   constexpr bool HASHED = MODE != MODE_DM;
   constexpr bool XSIGN = HASHED && !NEG;          // signs by XOR
-  constexpr bool STRIPS = HASHED && !X3 && BN < 256;   // (256 x 256 blocks and fp32 planes have steps enough; a third copy of the step would not fit the registers)
+  constexpr bool STRIPS = HASHED && !X3 && BN == 192;  // (256 x 256 blocks and fp32 planes have steps enough, a third copy of the step would not fit the registers; strips of 128 columns lost to those of 192 on all of 300 000 shapes)
   constexpr int A_BYTES = BM * 128, STAGE = A_BYTES + BN * 128;
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
@@ -941,7 +941,7 @@ struct Block {
 };
 constexpr Block kBlocks[] = {{256, 256, 1.0, 0.33, 5.9, 0.0, 1.11, 8.7, 0.36e6},
                              {256, 192, 0.88, 0.25, 5.2, 4.6, 1.03, 7.7, 0.29e6},    // (48-column rows of a wave: more pieces)
-                             {256, 128, 0.67, 0.18, 4.0, 3.4, 0.78, 4.9, 0.36e6},
+                             {256, 128, 0.67, 0.18, 4.0, 0.0, 0.78, 4.9, 0.36e6},
                              {128, 192, 0.57, 0.14, 4.2, 1.9, 0.635, 4.8, 0.29e6}};
 
 double rounds_of(double wgs) {                     // of 256 workgroups; a last partial round costs less than a full one
@@ -983,7 +983,7 @@ WidePlan plan_hashed(int which, const MMArgs& a, int max_parts, bool x3) {
   for (const Block& b : kBlocks) {
     for (int64_t t = 1; t <= 4; ++t) {
       // a strip: whole blocks of whole tiles, no ragged step, two steps to a block at least
-      if (t > 1 && (x3 || b.bn == 256 || K % BK != 0 || K < 2 * BK || N % (b.bn * t) != 0 || b.bn % zn != 0)) continue;
+      if (t > 1 && (x3 || b.bn != 192 || K % BK != 0 || K < 2 * BK || N % (b.bn * t) != 0 || b.bn % zn != 0)) continue;
       const int64_t tn = t > 1 ? b.bn * t / zn : cdiv(b.bn, zn) + 1;
       const double blocks = (double)cdiv(a.I, b.bm) * (double)cdiv(N, b.bn * t);
       // (a split of what fills the chip anyway only adds work)
