@@ -686,12 +686,20 @@ __global__ __launch_bounds__(kAccThreads) void k_embed_accum(EmbedArgs a, AccPla
   const int sub = threadIdx.x % lpi, which = threadIdx.x / lpi;
   // Several chunks per thread in flight: the list entry and then the dOut chunk it points at are
   // dependent loads, so the entries of the next batch are fetched while this batch's chunks load.
-  // The body is branch-free: a slot past the end of the list becomes chunk 0 with weight 0.
+  // A slot past the end of the list, which only the last batch has, loads chunk 0 of dOut and adds zeros to the bucket's
+  // first slots (not that chunk with weight 0: it may hold an infinity).
   constexpr int U = 8;
+  auto past_the_end = [&](uint2* ent, vfloat4* dv) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (ent[u].y == 0xffffffffu) {
+        ent[u].y = (uint32_t)slot0;
+        dv[u] = vfloat4{0.f, 0.f, 0.f, 0.f};
+      }
+  };
   auto add_chunk = [&](uint2 ent, vfloat4 dv) {
-    const bool ok = ent.y != 0xffffffffu;
-    const float sc = !ok ? 0.f : ((ent.y & 0x80000000u) ? -a.lambda : a.lambda);
-    const int rel = (ok ? (int)((int64_t)(ent.y & 0x7fffffffu) - slot0) : 0) + 4 * sub;
+    const float sc = (ent.y & 0x80000000u) ? -a.lambda : a.lambda;
+    const int rel = (int)((ent.y & 0x7fffffffu) - (uint32_t)slot0) + 4 * sub;
     if constexpr (FIXED) {
       atomicAdd(&img[rel + 0], to_fixed(sc * dv.x, scale));
       atomicAdd(&img[rel + 1], to_fixed(sc * dv.y, scale));
@@ -720,10 +728,10 @@ __global__ __launch_bounds__(kAccThreads) void k_embed_accum(EmbedArgs a, AccPla
         const int src = (u * 8 + (lane >> 3)) << 2;
         e[u].x = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)mine.x);
         e[u].y = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)mine.y);
-        const uint32_t chunk = e[u].y != 0xffffffffu ? e[u].x : 0u;
-        d[u] = __builtin_nontemporal_load(reinterpret_cast<const vfloat4*>(dOut + (int64_t)chunk * a.Z) + sub);
+        d[u] = __builtin_nontemporal_load(reinterpret_cast<const vfloat4*>(dOut + (int64_t)e[u].x * a.Z) + sub);
       }
       nxt = fetch_one(i0 + kAccThreads + threadIdx.x);
+      if (i0 + kAccThreads > end) past_the_end(e, d);
 #pragma unroll
       for (int u = 0; u < U; ++u) add_chunk(e[u], d[u]);
     }
@@ -748,6 +756,7 @@ __global__ __launch_bounds__(kAccThreads) void k_embed_accum(EmbedArgs a, AccPla
       d[u] = __builtin_nontemporal_load(reinterpret_cast<const vfloat4*>(dOut + (int64_t)e[u].x * a.Z) + sub);
     }
     fetch_entries(i0 + U * ipp + which, en);
+    if (ipp * lpi != kAccThreads || i0 + U * ipp > end) past_the_end(e, d);
 #pragma unroll
     for (int u = 0; u < U; ++u) add_chunk(e[u], d[u]);
   }

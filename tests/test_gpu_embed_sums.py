@@ -89,6 +89,20 @@ def test_a_workspace_at_any_multiple_of_four_bytes(roast):
         assert np.array_equal(to_host_f64(dM), ref), at
 
 
+@pytest.mark.parametrize("N,D,Z,m_size", [(65_536, 32, 32, 200_003), (65_536, 64, 32, 50_021), (40_000, 64, 16, 90_001)])
+def test_an_infinity_stays_where_it_belongs(roast, N, D, Z, m_size):
+    """An infinity in the first chunk of dOut reaches the slots that chunk is added to, and no other."""
+    rng = np.random.default_rng(N + Z)
+    h = wl.draw_hash(rng, use_sign=False, align=1)
+    rows, tables = rng.integers(0, 1 << 33, N), np.zeros(N, dtype=np.uint32)
+    dOut = rng.uniform(0.5, 1.5, (N, D)).astype(np.float32)
+    dOut[0, :Z] = np.inf
+    got = gradient(roast, h, D, Z, m_size, rows, tables, dOut)
+    ref = oracle.embed_bwd(h, D, Z, m_size, 1.0, rows, tables, dOut)
+    assert np.isinf(ref).sum() == Z and not np.isnan(ref).any()
+    assert np.array_equal(np.isinf(got), np.isinf(ref)) and not np.isnan(got).any()
+
+
 def test_gradients_of_two_streams_into_one_array(roast):
     """Calls on different streams may add to one dM at the same time: nothing is lost."""
     N, D, Z, m_size = 65_536, 32, 32, 50_021
