@@ -524,9 +524,9 @@ def main():
                 "launch_us": 1e3 * launch_ms[k], "call_us_instrumented": 1e3 * per_call[k]} for k in mm_calls}
         # The dominant kernel = the instantiation with the largest total time per step: the dM
         # product (MODE 2, two launches per step, one per layer; both 38.65 GFLOP).
-        by_kind = {"k_roast_mfma<MODE_DM> (mm_bwd_dM_l1 + mm_bwd_dM_l2)": ["mm_bwd_dM_l1", "mm_bwd_dM_l2"],
-                   "k_roast_mfma<MODE_FWD> (mm_fwd_l1 + mm_fwd_l2)": ["mm_fwd_l1", "mm_fwd_l2"],
-                   "k_roast_mfma<MODE_DX> (mm_bwd_dx_l1 + mm_bwd_dx_l2)": ["mm_bwd_dx_l1", "mm_bwd_dx_l2"]}
+        by_kind = {"k_roast_mfma_wide<MODE_DM> (mm_bwd_dM_l1 + mm_bwd_dM_l2)": ["mm_bwd_dM_l1", "mm_bwd_dM_l2"],
+                   "k_roast_mfma_wide<MODE_FWD> (mm_fwd_l1 + mm_fwd_l2)": ["mm_fwd_l1", "mm_fwd_l2"],
+                   "k_roast_mfma_wide<MODE_DX> (mm_bwd_dx_l1 + mm_bwd_dx_l2)": ["mm_bwd_dx_l1", "mm_bwd_dx_l2"]}
         dom = max(by_kind, key=lambda k: sum(launch_ms[c] for c in by_kind[k]))
         calls = by_kind[dom]
         ach = sum(flop_layer[c[-2:]] for c in calls) / (sum(launch_ms[c] for c in calls) * 1e-3) / 1e12
@@ -552,9 +552,9 @@ def main():
         result["embedding"] = {"value": tot, "unit": "GB/s", "pct_hbm_peak": 100.0 * tot / PEAK_HBM_GBS,
                                "fwd_GBs": gbs_f, "bwd_GBs": gbs_b, "bytes_fwd": bytes_fwd, "bytes_bwd": bytes_bwd,
                                # the gradient is the larger consumer of the two (and of the whole step):
-                               # its kernels together (zero + route + accumulate = one call) are the
+                               # its kernels together (clear + route + accumulate = one call) are the
                                # dominant HBM-bound work
-                               "roofline": {"kernel": "k_embed_zero + k_embed_route + k_embed_accum (embed_bwd)",
+                               "roofline": {"kernel": "k_embed_route_init + k_embed_route + k_embed_accum (embed_bwd)",
                                             "bound": "hbm", "achieved": gbs_b, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                                             "frac": gbs_b / PEAK_HBM_GBS,
                                             "traffic": traffic_of(tr, ["embed_bwd"], "k_embed_accum") if tr else None},

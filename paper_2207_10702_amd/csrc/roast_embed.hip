@@ -56,16 +56,16 @@ __device__ inline int64_t bag_of(const int64_t* __restrict__ bag_off, int64_t B,
 // row of dOut that lookup n takes its gradient from
 __device__ inline int64_t grad_row(const EmbedArgs& a, int64_t n) { return a.bag_off ? bag_of(a.bag_off, a.B, n) : n; }
 
-// Streaming lookup / direct-atomic gradient.  A wave takes 64 lookups: each lane hashes the chunks
-// of one lookup into the wave's LDS key list (offset | sign bit, 32-bit), then the wave walks the
-// 64*C chunks in order, LPI lanes per chunk, VEC floats per lane.
+// Streaming lookup / direct-atomic gradient.  A wave takes rows_wave lookups (64, fewer in a small call): each lane
+// hashes the chunks of one lookup into the wave's LDS key list (offset | sign bit, 32-bit), then the wave walks the
+// rows_wave*C chunks in order, LPI lanes per chunk, VEC floats per lane.
 // VEC = 4 (forward only) requires Z % 4 == 0 and D % Z == 0 (then every chunk is full and out is 16-byte
 // aligned per lane, given a 16-byte aligned base).  Needs |M| < 2^31 and C <= kMaxC.
 constexpr int kMaxC = 16;
 
 // slices > 1 (forward only; 2, 4 or 8): M is larger than one XCD's L2, so the gathered reads would
 // keep missing it.  The workgroups of XCD group s (workgroups go to the 8 XCDs round-robin) then only
-// serve the chunks whose offset lies in the s-th slice of M: every block of 256 lookups is hashed by
+// serve the chunks whose offset lies in the s-th slice of M: every block of 4*rows_wave lookups is hashed by
 // `slices` workgroups on different XCDs (hashing is cheap), each of which gathers from a part of M
 // that stays in its L2 and writes its share of the output chunks.
 template <int VEC, bool BWD>

@@ -930,14 +930,13 @@ bool hashed_ok(const MMArgs& a) {
 }
 
 // ---- which block, how many blocks to a strip, how many parts of the contraction: the smallest
-// modelled time.  The constants (microseconds) are fitted to 13000 timed launches of 160 layer shapes with
-// 16 .. 16384 rows and 256 .. 16384 columns; over those the choice costs 1 % more than the
-// best launch does, on the average.
+// modelled time.  The constants (microseconds) are fitted to timed launches (not kept) of 160 layer shapes with
+// 16 .. 16384 rows and 256 .. 16384 columns.
 struct Block {
   int bm, bn;
   double step, busy;     // forward / dX: a 64-deep step; added to it when all CUs are busy (clocks and memory)
   double fixed, more;    // a workgroup's start and end; a further block of a strip
-  double dm_step, dm_fixed, dm_adds;   // dM: the same; atomic adds per microsecond, whole chip
+  double dm_step, dm_fixed, dm_adds;   // dM: the same; atomic adds per microsecond, whole chip, as if nothing overlapped them (0.36e6: 28 G 64-byte pieces/s, where the chip serves 18.7)
 };
 constexpr Block kBlocks[] = {{256, 256, 1.0, 0.33, 5.9, 0.0, 1.11, 8.7, 0.36e6},
                              {256, 192, 0.88, 0.25, 5.2, 4.6, 1.03, 7.7, 0.29e6},    // (48-column rows of a wave: more pieces)
