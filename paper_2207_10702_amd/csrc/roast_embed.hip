@@ -313,14 +313,6 @@ roast_status launch_embed(const EmbedArgs& a, const int64_t* rows, const uint32_
   const int per_lane = vec4 ? 4 : 1;
   int lpi_log2 = 0;
   while ((1 << lpi_log2) < 64 && (int64_t)(1 << lpi_log2) * per_lane < a.Z) ++lpi_log2;
-  // Lookups per wave: 64 (one per lane) once the call fills the chip with full waves; below that fewer,
-  // so that a small call spreads over up to 8192 waves (32 per CU) instead of walking 64 lookups'
-  // chunks one group after the other in a few waves -- but never fewer than one step of the wave
-  // serves (64 >> lpi_log2 chunks).  2028 lookups of 8 chunks, gradient: 32 -> 14 us.
-  int rows_wave = 64;
-  while (rows_wave > 1 && (a.N + rows_wave / 2 - 1) / (rows_wave / 2) <= 8192 && (rows_wave / 2) * a.C >= (64 >> lpi_log2)) rows_wave /= 2;
-  const int64_t waves = (a.N + rows_wave - 1) / rows_wave;
-  int64_t blocks = (waves + 3) / 4;
   // forward over an M that does not fit one XCD's L2 (4 MiB): four slices (measured on a 5 MiB M:
   // 171 us unsliced, 158 / 144 / 189 us with 2 / 4 / 8 slices -- every slice hashes all lookups),
   // eight once a quarter is too large; not for small calls, nor once even an eighth does not fit
@@ -329,6 +321,16 @@ roast_status launch_embed(const EmbedArgs& a, const int64_t* rows, const uint32_
     const int64_t bytes = a.m_size * 4, fit = 3584 * 1024;
     slices = bytes <= fit ? 1 : bytes <= 4 * fit ? 4 : bytes <= 8 * fit ? 8 : 1;
   }
+  // Lookups per wave: 64 (one per lane) once the call fills the chip with full waves; below that fewer,
+  // so that a small call spreads over up to 8192 waves (32 per CU) instead of walking 64 lookups'
+  // chunks one group after the other in a few waves -- but never fewer than one step of the wave
+  // serves (64 >> lpi_log2 chunks).  2028 lookups of 8 chunks, gradient: 32 -> 14 us.  With slices a wave keeps
+  // 64: it hashes all of its lookups for its slice's share of their chunks, a few of which would be left (in us, 64 and
+  // fewer: 30000 lookups of 4 chunks of 32, four slices 9.1 and 22.9; 66000 of one of 128, eight slices 10.0 and 20.8; 213000 of 4 21.8 and 25.6).
+  int rows_wave = 64;
+  while (slices == 1 && rows_wave > 1 && (a.N + rows_wave / 2 - 1) / (rows_wave / 2) <= 8192 && (rows_wave / 2) * a.C >= (64 >> lpi_log2)) rows_wave /= 2;
+  const int64_t waves = (a.N + rows_wave - 1) / rows_wave;
+  int64_t blocks = (waves + 3) / 4;
   if (slices > 1) blocks = (blocks + 8 / slices - 1) / (8 / slices) * 8;
   if (blocks > 0x7fffffffll) return ROAST_ERR_UNSUPPORTED;
   const dim3 g((unsigned)blocks), b(256);
