@@ -1395,9 +1395,20 @@ roast_status mfma_mm_fwd(const MMArgs& a, const void* X, int64_t ldx, const floa
   return st != ROAST_OK ? st : split_finish(p, grid.z, a.I, a.O, s);
 }
 
+// The wide blocks that a dX call with a copy of M runs on.  Where the hash sign is an XOR of the weight fragments there (no
+// copy of -M), 128 x 192 blocks in one round lose to the kernel below with 256 x 96 blocks, which applies it as it stages the
+// weights, if those make a round too and leave a quarter of the CUs idle (nearer to a full round the two are even; below
+// eight steps the wide blocks start faster).  Over 250 shapes of an M of 6 Mi the wide blocks took 6 % more: 1738 x 384 x 5760 73 us,
+// this 63; 1096 x 3008 x 640 16.6 and 14.1.  Split contractions stay: 2 % the other way.
+static WidePlan dx_plan(const MMArgs& a, int max_parts) {
+  const WidePlan w = wide_dx_plan(a, max_parts, false);
+  if (w.bm != 128 || w.nblk > 1 || w.parts > 1 || shadow_copies(a.m_size) == 4 || a.O % BK != 0 || !mfma_dx_ok(a)) return w;
+  return cdiv(a.I, 128) * cdiv(a.H, 192) <= 256 && cdiv(a.I, kBM) * cdiv(a.H, kBNarrow) <= 192 && a.O >= 8 * BK ? WidePlan{} : w;
+}
+
 roast_status mfma_mm_bwd_dx(const MMArgs& a, const void* dY, int64_t ldy, const float* M, const void* M_bf16,
                             void* dX, int64_t ldx, float* ws, hipStream_t s) {
-  const WidePlan wide = M_bf16 ? wide_dx_plan(a, ws ? kWideParts : 1, false) : WidePlan{};
+  const WidePlan wide = M_bf16 ? dx_plan(a, ws ? kWideParts : 1) : WidePlan{};
   const bool elem = !mfma_dx_ok(a);
   if ((elem && !mfma_elem_ok(a)) || ldy % 8 != 0 || ldx % 8 != 0 || !aligned16(dY) || !aligned16(dX))
     return ROAST_ERR_UNSUPPORTED;
@@ -1628,7 +1639,7 @@ WidePlan mm_wide_plan(const MMArgs& a, bool f32, int which, bool workspace) {
   if (!f32 && !(which == 2 ? a.H >= kBM / 32 && a.O >= kBN / 32 : mfma_elem_ok(a))) return {};
   if (which == 2) return wide_dm_plan(a, 0, f32);
   const int parts = workspace ? kWideParts : 1;
-  return which == 0 ? wide_fwd_plan(a, parts, f32) : wide_dx_plan(a, parts, f32);
+  return which == 0 ? wide_fwd_plan(a, parts, f32) : f32 ? wide_dx_plan(a, parts, true) : dx_plan(a, parts);
 }
 
 }  // namespace roast

@@ -40,6 +40,8 @@ SHAPES = [
     (1585, 14592, 128, 64, 64, 4300001),
     (6958, 3456, 128, 64, 32, 4300001),
     (5855, 128, 5760, 128, 64, 4300001),
+    (1023, 200, 512, 64, 32, 4300001),     # dX on the 256 x 96 blocks; ragged rows and columns
+    (6144, 768, 640, 64, 64, 4300001),     # ... the most of them that it takes
 ]
 
 FWD, DX, DM = 0, 1, 2

@@ -134,6 +134,25 @@ def test_wide_block_diagnostic():
     assert binding.roast_mm_wide_blocks(bad, torch.bfloat16, 8192, 0) is None
 
 
+@pytest.mark.parametrize("I,H,O,m,wide", [
+    (1024, 192, 512, 6 << 20, False),        # eight steps
+    (1024, 192, 448, 6 << 20, True),         # seven
+    (1024, 192, 520, 6 << 20, True),         # a ragged one
+    (1024, 192, 512, 4 << 20, True),         # the shadow has -M
+    (1024, 192, 512, (4 << 20) + 1, False),
+    (6144, 768, 4096, 6 << 20, False),       # 192 blocks of 256 x 96
+    (6145, 768, 4096, 6 << 20, True),        # 200
+])
+def test_dx_of_a_large_m_leaves_small_wide_blocks(I, H, O, m, wide):
+    """dX of an M whose shadow has no negated copies: 256 x 96 blocks where they leave CUs idle, with and without a workspace
+    that would not be used."""
+    import torch
+    d = binding.mm_desc(H, O, 64, 64, m, 0, np.float32(1.0), wl.draw_hash(np.random.default_rng(2)))
+    assert (binding.roast_mm_wide_blocks(d, torch.bfloat16, I, 1) is not None) == wide
+    if binding.roast_mm_bwd_dx_workspace(d, torch.bfloat16, I) > 0:      # a split contraction stays on the wide blocks
+        assert binding.roast_mm_wide_blocks(d, torch.bfloat16, I, 1, True)[3] > 1
+
+
 @pytest.mark.parametrize("I,H,O", [(16, 4096, 4096), (64, 4096, 4096), (1024, 2048, 2048), (25, 5224, 2608), (126, 5480, 4264), (4096, 2048, 512)])
 def test_parts_of_a_split_suit_the_kernel_without_a_copy_too(I, H, O):
     """bf16 forward with a workspace: calls with and without the copy of M run in the same number of parts.  The
