@@ -950,9 +950,9 @@ double rounds_of(double wgs) {                     // of 256 workgroups; a last 
 
 // A call without a copy of M runs on the 256 x 128 kernel, in as many parts (both give the same sums).  Where the number
 // that is best here costs that kernel over a tenth more than its own best, the one with the least
-// time of both together, among those close to the best here: within 7 %, or, if the best is no split at all, 5 % less
-// half a microsecond (a first split is a launch more, which the model sees too small on short calls: 168 x 392 x 552
-// would go from 11.2 to 13.3 us with a copy).  With a copy and without, by the best here and by this rule:
+// time of both together, among those close to the best here: within 7 %, or, if the best is no split at all, 8 % less
+// 1.2 microseconds (a first split is a launch more, which the model sees too small on short calls: with a copy 168 x 392 x 552
+// would go from 11.2 to 13.3 us, 26 x 600 x 4392 from 12.1 to 14.6).  With a copy and without, by the best here and by this rule:
 // 64 x 4096 x 4096 17.9 and 27.4 -> 17.4 and 19.7 us, 126 x 5480 x 4264 22.2 and 43.6 -> 22.4 and 29.3,
 // 1024 x 2048 x 2048 25.1 and 34.9 -> 25.4 and 28.6.
 int parts_for_both(int64_t I, int64_t N, int64_t K, const double* cost_of, int best) {
@@ -964,7 +964,7 @@ int parts_for_both(int64_t I, int64_t N, int64_t K, const double* cost_of, int b
     least = std::min(least, narrow[parts]);
   }
   if (narrow[best] <= 1.1 * least) return best;
-  const double limit = best == 1 ? 1.05 * cost_of[1] - 0.5 : 1.07 * cost_of[best];
+  const double limit = best == 1 ? 1.08 * cost_of[1] - 1.2 : 1.07 * cost_of[best];
   for (int parts = 1; parts <= kWideParts; ++parts)
     if (cost_of[parts] <= limit && cost_of[parts] + narrow[parts] < cost_of[best] + narrow[best]) best = parts;
   return best;

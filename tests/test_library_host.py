@@ -164,6 +164,14 @@ def test_parts_of_a_split_suit_the_kernel_without_a_copy_too(I, H, O):
     assert 128 <= blocks <= 256
 
 
+@pytest.mark.parametrize("I,H,O", [(26, 600, 4392), (168, 392, 552)])
+def test_short_calls_are_not_split_for_the_other_kernel(I, H, O):
+    """Calls that the wide blocks do in about ten microseconds in one launch take no second one, whatever it would save without a copy."""
+    import torch
+    d = binding.mm_desc(H, O, 32, 64, 1 << 19, 0, np.float32(1.0), wl.draw_hash(np.random.default_rng(2)))
+    assert binding.roast_mm_fwd_workspace(d, torch.bfloat16, I) == 0
+
+
 @pytest.mark.parametrize("m", [1, 63, 64, 47185, 4 << 20, (4 << 20) + 1, 64 << 20])
 def test_planes_take_what_they_use(m):
     """Three planes of two bf16 copies each, padded to 64 elements, whatever copies the shadow of an M of that size has."""
