@@ -238,11 +238,17 @@ typedef struct {
 
 /*
  * The same for the wide blocks: what roast_mm_fwd (which = 0) or roast_mm_bwd_dx (1) launch with a copy of M (fp32: with a
- * workspace, unless the call is short enough to multiply in fp32), or roast_mm_bwd_dM (2; ATOMIC, bf16 without a workspace, fp32 with one).  workspace: 1 if a forward / dX
- * call has one, else 0.  1 and *out when they take the shape; 0 and zeros in *out when it runs on other kernels or the
- * descriptor, I, `dt`, `which` or `out` is invalid.
+ * workspace), or roast_mm_bwd_dM (2; ATOMIC, bf16 without a workspace, fp32 with one), on operands whose addresses and leading
+ * dimensions are multiples of 16 bytes.  workspace: 1 if a forward / dX call has one, else 0.  1 and *out when the call runs on them;
+ * 0 and zeros in *out when it runs on other kernels or the descriptor, I, `dt`, `which` or `out` is invalid.
  */
 int roast_mm_wide_blocks(const roast_mm_desc* d, roast_dtype dt, int64_t I, int which, int workspace, roast_mm_blocks* out);
+
+/*
+ * The same for the kernels of small calls, which make the whole product in one launch (strip and parts are 1): roast_mm_fwd or
+ * roast_mm_bwd_dx, fp32 or bf16 (with a copy of M or without one).  Every call is on the wide blocks, on these, or on neither.
+ */
+int roast_mm_direct_blocks(const roast_mm_desc* d, roast_dtype dt, int64_t I, int which, int workspace, roast_mm_blocks* out);
 
 /* Bytes of workspace roast_mm_bwd_dM can use for these sizes and mode (0 = none).
  * DETERMINISTIC: required.  ATOMIC: optional -- with it (bf16 path, contraction split over several

@@ -22,7 +22,7 @@ EXPORTS = ["roast_status_string", "roast_tile_index", "roast_tile_index_device",
            "roast_m_shadow_bytes", "roast_m_shadow_bf16", "roast_m_planes_bytes", "roast_m_planes_bf16",
            "roast_mm_fwd", "roast_mm_bwd_dx",
            "roast_mm_fwd_workspace", "roast_mm_bwd_dx_workspace", "roast_mm_fwd_ws", "roast_mm_bwd_dx_ws",
-           "roast_mm_strip_blocks", "roast_mm_wide_blocks", "roast_mm_bwd_dM_workspace", "roast_mm_bwd_dM_workspace_f32", "roast_mm_bwd_dM",
+           "roast_mm_strip_blocks", "roast_mm_wide_blocks", "roast_mm_direct_blocks", "roast_mm_bwd_dM_workspace", "roast_mm_bwd_dM_workspace_f32", "roast_mm_bwd_dM",
            "roast_embed_fwd", "roast_embed_bwd_workspace", "roast_embed_bwd", "roast_embed_bwd_noalloc",
            "roast_embed_bag_fwd", "roast_embed_bag_bwd_workspace", "roast_embed_bag_bwd", "roast_optim_step"]
 
@@ -97,7 +97,8 @@ def load() -> C.CDLL:
         getattr(lib, name).restype = sz
     lib.roast_mm_fwd_ws.argtypes = [MP, i32, i64, vp, i64, vp, vp, vp, i64, vp, sz, vp]
     lib.roast_mm_strip_blocks.argtypes = [MP, i64, i32]
-    lib.roast_mm_wide_blocks.argtypes = [MP, i32, i64, i32, i32, vp]
+    for name in ("roast_mm_wide_blocks", "roast_mm_direct_blocks"):
+        getattr(lib, name).argtypes = [MP, i32, i64, i32, i32, vp]
     lib.roast_mm_bwd_dx_ws.argtypes = [MP, i32, i64, vp, i64, vp, vp, vp, i64, vp, sz, vp]
     lib.roast_mm_bwd_dM_workspace.argtypes = [MP, i64, i32]
     lib.roast_mm_bwd_dM_workspace.restype = sz
@@ -289,13 +290,22 @@ def roast_mm_strip_blocks(desc: RoastMMDesc, I: int, which: int) -> int:
     return int(load().roast_mm_strip_blocks(C.byref(desc), int(I), int(which)))
 
 
-def roast_mm_wide_blocks(desc: RoastMMDesc, dtype, I: int, which: int, workspace: bool = False):
-    """(rows, columns, blocks per strip, parts of the contraction) of a launch on the wide blocks with a copy of M, which = 0:
-    roast_mm_fwd, 1: roast_mm_bwd_dx, 2: roast_mm_bwd_dM; None where the call runs on other kernels."""
+def _blocks(name: str, desc: RoastMMDesc, dtype, I: int, which: int, workspace: bool):
     torch = _torch()
     code = {torch.float32: ROAST_F32, torch.bfloat16: ROAST_BF16}[dtype]
     out = (C.c_int32 * 4)()
-    return tuple(out) if load().roast_mm_wide_blocks(C.byref(desc), code, int(I), int(which), int(workspace), out) else None
+    return tuple(out) if getattr(load(), name)(C.byref(desc), code, int(I), int(which), int(workspace), out) else None
+
+
+def roast_mm_wide_blocks(desc: RoastMMDesc, dtype, I: int, which: int, workspace: bool = False):
+    """(rows, columns, blocks per strip, parts of the contraction) of a launch on the wide blocks with a copy of M, which = 0:
+    roast_mm_fwd, 1: roast_mm_bwd_dx, 2: roast_mm_bwd_dM; None where the call runs on other kernels."""
+    return _blocks("roast_mm_wide_blocks", desc, dtype, I, which, workspace)
+
+
+def roast_mm_direct_blocks(desc: RoastMMDesc, dtype, I: int, which: int, workspace: bool = False):
+    """The same of a launch on the kernels of small calls, which = 0 or 1."""
+    return _blocks("roast_mm_direct_blocks", desc, dtype, I, which, workspace)
 
 
 def roast_mm_fwd(desc: RoastMMDesc, X, M, Y=None, stream=None, M_bf16=None, ws=None):

@@ -148,6 +148,7 @@ size_t roast_mm_bwd_dx_workspace(const roast_mm_desc* d, roast_dtype dt, int64_t
 int roast_mm_strip_blocks(const roast_mm_desc* d, int64_t I, int which) {
   MMArgs a;
   if (make_mm_args(d, I, &a) != ROAST_OK || I <= 0 || (which != 0 && which != 1)) return 0;
+  if (mm_plan(a, false, which, true, false).route == MMRoute::Direct) return 1;
   return which == 0 ? mfma_fwd_strip(a, true) : mfma_dx_strip(a, true);
 }
 
@@ -156,9 +157,26 @@ int roast_mm_wide_blocks(const roast_mm_desc* d, roast_dtype dt, int64_t I, int 
   *out = roast_mm_blocks{0, 0, 0, 0};
   MMArgs a;
   if (make_mm_args(d, I, &a) != ROAST_OK || I <= 0 || !dtype_ok(dt) || which < 0 || which > 2) return 0;
-  const WidePlan w = mm_wide_plan(a, dt == ROAST_F32, which, workspace != 0);
+  WidePlan w{};
+  if (which == 2) {
+    w = mm_dm_plan(a, dt == ROAST_F32);
+  } else {
+    const MMPlan plan = mm_plan(a, dt == ROAST_F32, which, true, workspace != 0);
+    if (plan.route == MMRoute::Wide) w = plan.wide;
+  }
   if (w.bm == 0) return 0;
   *out = roast_mm_blocks{w.bm, w.bn, w.nblk, w.parts};
+  return 1;
+}
+
+int roast_mm_direct_blocks(const roast_mm_desc* d, roast_dtype dt, int64_t I, int which, int workspace, roast_mm_blocks* out) {
+  if (!out) return 0;
+  *out = roast_mm_blocks{0, 0, 0, 0};
+  MMArgs a;
+  if (make_mm_args(d, I, &a) != ROAST_OK || I <= 0 || !dtype_ok(dt) || (which != 0 && which != 1)) return 0;
+  const MMPlan plan = mm_plan(a, dt == ROAST_F32, which, true, workspace != 0);
+  if (plan.route != MMRoute::Direct) return 0;
+  *out = roast_mm_blocks{16 * plan.direct.mi, 16 * plan.direct.nj, 1, 1};
   return 1;
 }
 
@@ -178,17 +196,14 @@ roast_status roast_mm_fwd_ws(const roast_mm_desc* d, roast_dtype dt, int64_t I, 
     st = mfma_mm_fwd(a, X, ldx, M, M_bf16, Y, ldy, need ? (float*)workspace : nullptr, (hipStream_t)stream);
     if (st != ROAST_ERR_UNSUPPORTED) return st;
   } else {
-    const DirectPlan direct = direct_plan(0, false, a);
-    if (workspace) {
-      const size_t need = roast_mm_fwd_workspace(d, dt, I);
-      if (workspace_bytes < need || ((uintptr_t)workspace & 15) != 0) return ROAST_ERR_WORKSPACE;
-      if (need && !(direct.mi && 1.08 * direct.us < x3_us(0, a))) {
-        st = x3_mm_fwd(a, (const float*)X, ldx, M, M_bf16, (float*)Y, ldy, workspace, (hipStream_t)stream);
-        if (st != ROAST_ERR_UNSUPPORTED) return st;
-      }
+    if (workspace && (workspace_bytes < roast_mm_fwd_workspace(d, dt, I) || ((uintptr_t)workspace & 15) != 0)) return ROAST_ERR_WORKSPACE;
+    const MMPlan plan = mm_plan(a, true, 0, M_bf16 != nullptr, workspace != nullptr);
+    if (plan.route == MMRoute::Wide || plan.route == MMRoute::Columns128) {
+      st = x3_mm_fwd(a, (const float*)X, ldx, M, M_bf16, (float*)Y, ldy, workspace, (hipStream_t)stream);
+      if (st != ROAST_ERR_UNSUPPORTED) return st;
     }
-    if (direct.mi) {
-      st = direct_mm(0, false, direct, a, X, ldx, M, nullptr, Y, ldy, (hipStream_t)stream);
+    if (plan.direct.mi) {
+      st = direct_mm(0, false, plan.direct, a, X, ldx, M, nullptr, Y, ldy, (hipStream_t)stream);
       if (st != ROAST_ERR_UNSUPPORTED) return st;
     }
   }
@@ -216,17 +231,14 @@ roast_status roast_mm_bwd_dx_ws(const roast_mm_desc* d, roast_dtype dt, int64_t 
     st = mfma_mm_bwd_dx(a, dY, ldy, M, M_bf16, dX, ldx, need ? (float*)workspace : nullptr, (hipStream_t)stream);
     if (st != ROAST_ERR_UNSUPPORTED) return st;
   } else {
-    const DirectPlan direct = direct_plan(1, false, a);
-    if (workspace) {
-      const size_t need = roast_mm_bwd_dx_workspace(d, dt, I);
-      if (workspace_bytes < need || ((uintptr_t)workspace & 15) != 0) return ROAST_ERR_WORKSPACE;
-      if (need && !(direct.mi && 1.08 * direct.us < x3_us(1, a))) {
-        st = x3_mm_bwd_dx(a, (const float*)dY, ldy, M, M_bf16, (float*)dX, ldx, workspace, (hipStream_t)stream);
-        if (st != ROAST_ERR_UNSUPPORTED) return st;
-      }
+    if (workspace && (workspace_bytes < roast_mm_bwd_dx_workspace(d, dt, I) || ((uintptr_t)workspace & 15) != 0)) return ROAST_ERR_WORKSPACE;
+    const MMPlan plan = mm_plan(a, true, 1, M_bf16 != nullptr, workspace != nullptr);
+    if (plan.route == MMRoute::Wide || plan.route == MMRoute::Columns128) {
+      st = x3_mm_bwd_dx(a, (const float*)dY, ldy, M, M_bf16, (float*)dX, ldx, workspace, (hipStream_t)stream);
+      if (st != ROAST_ERR_UNSUPPORTED) return st;
     }
-    if (direct.mi) {
-      st = direct_mm(1, false, direct, a, dY, ldy, M, nullptr, dX, ldx, (hipStream_t)stream);
+    if (plan.direct.mi) {
+      st = direct_mm(1, false, plan.direct, a, dY, ldy, M, nullptr, dX, ldx, (hipStream_t)stream);
       if (st != ROAST_ERR_UNSUPPORTED) return st;
     }
   }

@@ -155,21 +155,31 @@ constexpr int kWideParts = 16;
 WidePlan wide_fwd_plan(const MMArgs& a, int max_parts, bool x3);   // max_parts: 1 where no workspace is given, else kWideParts
 WidePlan wide_dx_plan(const MMArgs& a, int max_parts, bool x3);
 WidePlan wide_dm_plan(const MMArgs& a, int parts, bool x3);        // parts == 0: atomic adds, any number of parts
-// what a call with a copy of M runs on (which: 0 forward, 1 dX, 2 dM with atomic adds), for the diagnostic
-WidePlan mm_wide_plan(const MMArgs& a, bool f32, int which, bool workspace);
 roast_status wide_mm(int which, const MMArgs& a, const WidePlan& plan, const uint16_t* A, int64_t lda, int64_t a_plane,
                      const uint16_t* Mb, bool x3, uint16_t* C, float* C32, int64_t ldc, float* ws, hipStream_t s);
 roast_status wide_mm_dM(const MMArgs& a, const WidePlan& plan, const uint16_t* X, int64_t ldx, int64_t a_plane, const uint16_t* dY,
                         int64_t ldy, int64_t b_plane, bool x3, float* dM, float* G, const int* split_begin, hipStream_t s);
 
-// ---- fp32 forward (which = 0) and dX (1) from fp32 operands in one launch (roast_mm_direct.hip)
+// ---- forward (which = 0) and dX (1) of small calls in one launch (roast_mm_direct.hip): fp32 from fp32 operands; bf16 with weights
+// from the copy of M, or from fp32 M and rounded in registers.  bf16: A and C 16-byte aligned, leading dimensions multiples of 8.
 struct DirectPlan {
   int mi, nj;            // 16 mi x 16 nj output block (0: not the shape for these kernels)
   double us;             // modelled time
 };
 DirectPlan direct_plan(int which, bool bf16, const MMArgs& a);
 roast_status direct_mm(int which, bool bf16, const DirectPlan& d, const MMArgs& a, const void* A, int64_t lda, const float* M, const void* M_bf16, void* C, int64_t ldc, hipStream_t s);
-double x3_us(int which, const MMArgs& a);   // modelled time of the three-plane kernels (roast_mm_mfma.hip)
+
+// ---- which kernels a forward (which = 0) or dX (1) call takes where its operands are aligned for them: asked by the calls and by
+// the diagnostics alike (roast_mm_mfma.hip)
+enum class MMRoute { Generic, Direct, Wide, Columns128 };   // (Columns128: the 128-column kernels of that file, with their 96-column and element-wise variants)
+struct MMPlan {
+  MMRoute route;
+  DirectPlan direct;     // (direct.mi: they take the shape, whatever the route)
+  WidePlan wide;         // (wide.bm: likewise, with a copy of M)
+};
+// copy: a copy of M is given (fp32: planes are made where none is).  workspace: likewise, of the bytes that the query names
+MMPlan mm_plan(const MMArgs& a, bool f32, int which, bool copy, bool workspace);
+WidePlan mm_dm_plan(const MMArgs& a, bool f32);   // the same of the gradient of M with atomic adds
 
 // ---- lookup kernels (roast_embed.hip)
 roast_status embed_fwd_launch(const EmbedArgs& a, const int64_t* rows, const uint32_t* tables, const float* M,

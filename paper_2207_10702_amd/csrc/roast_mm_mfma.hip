@@ -1366,15 +1366,15 @@ static double bf16_us(int which, const MMArgs& a, bool ws) {
 
 roast_status mfma_mm_fwd(const MMArgs& a, const void* X, int64_t ldx, const float* M, const void* M_bf16, void* Y,
                          int64_t ldy, float* ws, hipStream_t s) {
-  const WidePlan wide = M_bf16 ? wide_fwd_plan(a, ws ? kWideParts : 1, false) : WidePlan{};
   const bool elem = !mfma_fwd_ok(a);
   if ((elem && !mfma_elem_ok(a)) || ldx % 8 != 0 || ldy % 8 != 0 || !aligned16(X) || !aligned16(Y))
     return ROAST_ERR_UNSUPPORTED;
-  const DirectPlan direct = direct_plan(0, true, a);
-  if (direct.mi && 1.08 * direct.us < bf16_us(0, a, ws != nullptr)) {
-    const roast_status st = direct_mm(0, true, direct, a, X, ldx, M, M_bf16, Y, ldy, s);
+  const MMPlan plan = mm_plan(a, false, 0, M_bf16 != nullptr, ws != nullptr);
+  if (plan.route == MMRoute::Direct) {
+    const roast_status st = direct_mm(0, true, plan.direct, a, X, ldx, M, M_bf16, Y, ldy, s);
     if (st != ROAST_ERR_UNSUPPORTED) return st;
   }
+  const WidePlan& wide = plan.wide;
   constexpr int BM = kBM, BN = kBN;
   KernArgs p{};
   p.a = a; p.A = (const uint16_t*)X; p.lda = ldx; p.M = M; p.Mb = (const uint16_t*)M_bf16;
@@ -1424,15 +1424,15 @@ static WidePlan dx_plan(const MMArgs& a, int max_parts) {
 
 roast_status mfma_mm_bwd_dx(const MMArgs& a, const void* dY, int64_t ldy, const float* M, const void* M_bf16,
                             void* dX, int64_t ldx, float* ws, hipStream_t s) {
-  const WidePlan wide = M_bf16 ? dx_plan(a, ws ? kWideParts : 1) : WidePlan{};
   const bool elem = !mfma_dx_ok(a);
   if ((elem && !mfma_elem_ok(a)) || ldy % 8 != 0 || ldx % 8 != 0 || !aligned16(dY) || !aligned16(dX))
     return ROAST_ERR_UNSUPPORTED;
-  const DirectPlan direct = direct_plan(1, true, a);
-  if (direct.mi && 1.08 * direct.us < bf16_us(1, a, ws != nullptr)) {
-    const roast_status st = direct_mm(1, true, direct, a, dY, ldy, M, M_bf16, dX, ldx, s);
+  const MMPlan plan = mm_plan(a, false, 1, M_bf16 != nullptr, ws != nullptr);
+  if (plan.route == MMRoute::Direct) {
+    const roast_status st = direct_mm(1, true, plan.direct, a, dY, ldy, M, M_bf16, dX, ldx, s);
     if (st != ROAST_ERR_UNSUPPORTED) return st;
   }
+  const WidePlan& wide = plan.wide;
   constexpr int BM = kBM, BN = kBN;
   KernArgs p{};
   p.a = a; p.A = (const uint16_t*)dY; p.lda = ldy; p.M = M; p.Mb = (const uint16_t*)M_bf16;
@@ -1554,7 +1554,7 @@ size_t x3_dm_workspace(const MMArgs& a) {
 
 // The products, and before them the launch that splits the activations (10 bytes of traffic an element).  Shapes that the wide blocks do
 // not take: 256 x 128 blocks of 1.2 us a step.
-double x3_us(int which, const MMArgs& a) {
+static double x3_us(int which, const MMArgs& a) {
   const int64_t K = which ? a.O : a.H, N = which ? a.H : a.O;
   const WidePlan w = which ? wide_dx_plan(a, kWideParts, true) : wide_fwd_plan(a, kWideParts, true);
   const int parts = which ? x3_dx_splits(a) : x3_fwd_splits(a);
@@ -1665,12 +1665,26 @@ roast_status x3_mm_bwd_dM(const MMArgs& a, const float* X, int64_t ldx, const fl
   return launch<MODE_DM, kBM, kBN, 4, 2, false, true>(p, grid, s);
 }
 
-WidePlan mm_wide_plan(const MMArgs& a, bool f32, int which, bool workspace) {
-  if (f32 && !(which == 2 ? x3_dm_ok(a) : workspace && (which == 0 ? x3_fwd_ok(a) : x3_dx_ok(a)))) return {};
-  if (!f32 && !(which == 2 ? a.H >= kBM / 32 && a.O >= kBN / 32 : mfma_elem_ok(a))) return {};
-  if (which == 2) return wide_dm_plan(a, 0, f32);
-  const int parts = workspace ? kWideParts : 1;
-  return which == 0 ? wide_fwd_plan(a, parts, f32) : f32 ? wide_dx_plan(a, parts, true) : dx_plan(a, parts);
+MMPlan mm_plan(const MMArgs& a, bool f32, int which, bool copy, bool workspace) {
+  MMPlan p{};
+  p.direct = direct_plan(which, !f32, a);
+  bool blocks;                           // the larger kernels take the shape
+  if (f32) {
+    blocks = workspace && (which == 0 ? x3_fwd_ok(a) : x3_dx_ok(a));
+    if (blocks) p.wide = which == 0 ? wide_fwd_plan(a, kWideParts, true) : wide_dx_plan(a, kWideParts, true);
+  } else {
+    blocks = mfma_elem_ok(a);
+    if (blocks && copy) p.wide = which == 0 ? wide_fwd_plan(a, workspace ? kWideParts : 1, false) : dx_plan(a, workspace ? kWideParts : 1);
+  }
+  // (8 %: what the models are good for)
+  const bool direct = p.direct.mi && (!blocks ? f32 : 1.08 * p.direct.us < (f32 ? x3_us(which, a) : bf16_us(which, a, workspace)));
+  p.route = direct ? MMRoute::Direct : !blocks ? MMRoute::Generic : p.wide.bm ? MMRoute::Wide : MMRoute::Columns128;
+  return p;
+}
+
+WidePlan mm_dm_plan(const MMArgs& a, bool f32) {
+  if (f32 ? !x3_dm_ok(a) : a.H < kBM / 32 || a.O < kBN / 32) return {};
+  return wide_dm_plan(a, 0, f32);
 }
 
 }  // namespace roast

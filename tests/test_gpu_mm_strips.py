@@ -46,8 +46,9 @@ def test_strip_launches_match_oracle(roast, shape, pad):
     lam = np.float32(0.37)
     d = roast.mm_desc(H, O, Z1, Z2, m, 5, lam, h)
     assert roast.roast_mm_strip_blocks(d, I, 0) == tf and roast.roast_mm_strip_blocks(d, I, 1) == tx
-    for which in (0, 1):                                    # where the call with the shadow runs
-        assert (roast.roast_mm_wide_blocks(d, torch.bfloat16, I, which) is None) == (Z1 % 32 != 0 or Z2 % 32 != 0)
+    which = 0 if tf > 1 else 1                              # where the call with the shadow runs that has strips without it
+    assert (roast.roast_mm_wide_blocks(d, torch.bfloat16, I, which) is None) == (Z1 % 32 != 0 or Z2 % 32 != 0)
+    assert roast.roast_mm_direct_blocks(d, torch.bfloat16, I, which) is None
     Md = to_dev(M)
     Mb = roast.roast_m_shadow_bf16(Md)
     Xd = torch.zeros((I, H + pad), dtype=torch.bfloat16, device="cuda")[:, :H]

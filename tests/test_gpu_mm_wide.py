@@ -17,9 +17,12 @@ SHAPES = [
     (1, 8, 8, 32, 32, 1025),               # one row, one 16-byte piece
     (127, 64, 192, 32, 64, 5001),          # one step; a row and a column block just missed / just full
     (129, 72, 200, 64, 32, 9000),          # ragged step, one row and one column piece too many
-    (257, 136, 264, 96, 96, 20011),        # tiles that are no power of two
+    (257, 136, 264, 96, 96, 20011),
+    (2057, 1096, 1160, 96, 96, 20011),     # tiles that are no power of two
     (255, 128, 128, 128, 128, 16384),      # |M| == one tile: every tile at base 0
-    (300, 1096, 520, 32, 96, 30000),       # contraction split (with a workspace), ragged last part
+    (300, 1096, 520, 32, 96, 30000),
+    (300, 6152, 2056, 32, 96, 30000),      # contraction split (with a workspace), ragged last part
+    (301, 2056, 6152, 96, 32, 30000),
     (8200, 520, 776, 64, 64, 47185),       # many rows: uneven dM parts
     (2100, 192, 6144, 64, 64, 33333),      # 256 x 256 blocks, ragged rows
     (2100, 6144, 192, 64, 64, 33333),
@@ -33,24 +36,28 @@ SHAPES = [
     (5855, 5760, 128, 64, 128, 100003),
     # |M| beyond 4 Mi: the shadow has no negated copies
     (129, 72, 200, 64, 32, 5000001),
-    (300, 1096, 520, 32, 96, 4300000),
+    (300, 6152, 2056, 32, 96, 4300000),
     (2100, 192, 6144, 64, 64, 4300001),
     (5000, 1024, 4096, 128, 64, 4300001),
     (3747, 128, 4608, 128, 64, 4300001),
     (1585, 14592, 128, 64, 64, 4300001),
     (6958, 3456, 128, 64, 32, 4300001),
     (5855, 128, 5760, 128, 64, 4300001),
-    (1023, 200, 512, 64, 32, 4300001),     # dX on the 256 x 96 blocks; ragged rows and columns
+    (2047, 1000, 1024, 64, 32, 4300001),   # dX on the 256 x 96 blocks; ragged rows and columns
     (6144, 768, 640, 64, 64, 4300001),     # ... the most of them that it takes
 ]
 
 FWD, DX, DM = 0, 1, 2
 BF16, F32 = torch.bfloat16, torch.float32
-# What some of them are there for: (I, H, O) -> (which product, type, workspace given, (rows, columns, strip, parts))
+# What some of them are there for: (I, H, O) -> (which product, type, workspace given, (rows, columns, strip, parts); None: the 128-column kernels and their
+# narrower blocks).  The smallest shapes run on the kernels of small calls in the products that are not listed.
 BLOCKS = {
     (1, 8, 8): [(FWD, BF16, False, (256, 128, 1, 1))],
-    (257, 136, 264): [(FWD, BF16, False, (128, 192, 1, 1)), (DX, BF16, False, (128, 192, 1, 1))],
-    (300, 1096, 520): [(FWD, BF16, True, (128, 192, 1, 6)), (DX, F32, True, (128, 192, 1, 9))],
+    (127, 64, 192): [(FWD, BF16, False, (256, 128, 1, 1))],
+    (129, 72, 200): [(FWD, BF16, False, (256, 128, 1, 1))],
+    (2057, 1096, 1160): [(FWD, BF16, False, (128, 192, 1, 1)), (DX, BF16, False, (128, 192, 1, 1)), (FWD, F32, True, (128, 192, 1, 2)), (DX, F32, True, (256, 128, 1, 3))],
+    (300, 6152, 2056): [(FWD, BF16, True, (128, 192, 1, 7)), (FWD, F32, True, (128, 192, 1, 7)), (DX, F32, True, (256, 256, 1, 5))],
+    (301, 2056, 6152): [(DX, BF16, True, (128, 192, 1, 7)), (DX, F32, True, (128, 192, 1, 7))],
     (8200, 520, 776): [(DM, BF16, False, (128, 192, 1, 7))],
     (2100, 192, 6144): [(FWD, BF16, False, (256, 256, 1, 1)), (FWD, F32, True, (256, 256, 1, 1)), (DM, F32, True, (256, 128, 1, 5))],
     (2100, 6144, 192): [(DX, BF16, False, (256, 256, 1, 1)), (DX, F32, True, (256, 256, 1, 1)), (FWD, BF16, True, (128, 192, 1, 12))],
@@ -65,6 +72,8 @@ BLOCKS = {
     (6958, 3456, 128): [(DX, BF16, False, (256, 192, 2, 1)), (FWD, BF16, True, (256, 128, 1, 6))],
     (5855, 128, 5760): [(FWD, BF16, False, (256, 192, 3, 1))],
     (5855, 5760, 128): [(DX, BF16, False, (256, 192, 3, 1))],
+    (2047, 1000, 1024): [(DX, BF16, False, None)],
+    (6144, 768, 640): [(DX, BF16, False, None)],
 }
 
 
@@ -72,6 +81,7 @@ def check_blocks(roast, shape, d):
     """The shape still runs on the blocks that it is listed for."""
     for which, dtype, workspace, blocks in BLOCKS.get(shape[:3], []):
         assert roast.roast_mm_wide_blocks(d, dtype, shape[0], which, workspace) == blocks, (shape, which, dtype)
+        assert roast.roast_mm_direct_blocks(d, dtype, shape[0], which, workspace) is None if which != DM else True
 
 
 @pytest.mark.parametrize("shape", SHAPES)
@@ -180,25 +190,31 @@ def test_infinity_in_the_last_token_stays_an_infinity(roast, shape):
     assert torch.all(torch.isfinite(dM[torch.arange(128) != 5]))
 
 
-@pytest.mark.parametrize("H,O,Z1,Z2", [(72, 200, 32, 32), (200, 72, 128, 32),       # 32: wide blocks with a copy of M
-                                       (1096, 520, 64, 64), (520, 1096, 64, 64),    # (a contraction of several parts, with a workspace)
-                                       (72, 200, 8, 8),                             # blocks of 128 columns, with and without a copy
-                                       (72, 200, 5, 3)])                            # element by element
-def test_infinity_in_a_row_stays_an_infinity(roast, H, O, Z1, Z2):
+@pytest.mark.parametrize("I,H,O,Z1,Z2,wide", [
+    (300, 72, 200, 32, 32, [(FWD, False, True)]), (300, 200, 72, 128, 32, [(DX, False, True)]),              # wide blocks with a copy of M
+    (300, 6152, 2056, 64, 64, [(FWD, True, True)]), (300, 2056, 6152, 64, 64, [(DX, True, True)]),           # (a contraction of several parts, with a workspace)
+    (3000, 1096, 1544, 8, 8, [(FWD, False, False), (DX, False, False)]),                                     # blocks of 128 columns, with and without a copy
+    (300, 72, 200, 5, 3, [(FWD, False, False), (DX, False, False)])])                                        # element by element
+def test_infinity_in_a_row_stays_an_infinity(roast, I, H, O, Z1, Z2, wide):
     """A ragged contraction: what fills the last step of forward / dX meets no infinity of the row.  No signs and
-    M > 0: the row of that infinity is +inf, the others are finite."""
-    I, m = 300, Z1 * Z2 + 1
+    M > 0: the row of that infinity is +inf, the others are finite.  wide: (product, workspace given, on wide blocks) of
+    what a case is there for."""
+    m = Z1 * Z2 + 1
     h = wl.draw_hash(np.random.default_rng(H), use_sign=False, align=1)
     d = roast.mm_desc(H, O, Z1, Z2, m, 0, 1.0, h)
+    for which, workspace, on in wide:
+        blocks = roast.roast_mm_wide_blocks(d, BF16, I, which, workspace)
+        assert (blocks is not None) == on and (not workspace or blocks[3] > 1)
+        assert roast.roast_mm_direct_blocks(d, BF16, I, which, workspace) is None
     g = torch.Generator(device="cuda").manual_seed(H)
     M = torch.rand(m, generator=g, device="cuda") + 0.5
     Mb = roast.roast_m_shadow_bf16(M)
     for n, call, want in ((H, roast.roast_mm_fwd, roast.roast_mm_fwd_workspace), (O, roast.roast_mm_bwd_dx, roast.roast_mm_bwd_dx_workspace)):
         A = torch.randn((I, n), generator=g, device="cuda").bfloat16()
         A[3, 5] = float("inf")                                                      # in the row's first piece
-        A[299, n - 1] = float("inf")                                                # in its last
+        A[I - 1, n - 1] = float("inf")                                              # in its last
         for copy in (None, Mb):
             for ws in (None, torch.empty(max(want(d, torch.bfloat16, I), 16), dtype=torch.uint8, device="cuda")):
                 R = call(d, A, M, M_bf16=copy, ws=ws).cpu()
-                assert torch.all(R[[3, 299]] == float("inf"))
-                assert torch.all(torch.isfinite(R[[r for r in range(I) if r not in (3, 299)]]))
+                assert torch.all(R[[3, I - 1]] == float("inf"))
+                assert torch.all(torch.isfinite(R[[r for r in range(I) if r not in (3, I - 1)]]))

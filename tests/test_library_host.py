@@ -134,12 +134,36 @@ def test_wide_block_diagnostic():
     assert binding.roast_mm_wide_blocks(bad, torch.bfloat16, 8192, 0) is None
 
 
+@pytest.mark.parametrize("I,H,O,Z,m,dtype,which,workspace,direct", [
+    (512, 2048, 2048, 64, 1 << 20, "bfloat16", 0, True, (64, 64, 1, 1)),
+    (300, 1096, 520, 32, 30000, "bfloat16", 0, True, (16, 32, 1, 1)),
+    (300, 1096, 520, 32, 30000, "float32", 1, True, (32, 32, 1, 1)),
+    (257, 136, 264, 96, 20011, "bfloat16", 1, False, (16, 32, 1, 1)),
+    (64, 256, 256, 32, 4096, "float32", 0, True, (16, 16, 1, 1)),
+    (4096, 4096, 4096, 64, 1 << 20, "float32", 0, False, (32, 64, 1, 1)),    # without a workspace there are no planes
+    (4096, 4096, 4096, 64, 1 << 20, "float32", 0, True, None),
+    (8192, 768, 3072, 64, 47185, "bfloat16", 0, False, None),
+])
+def test_the_diagnostics_name_the_kernels_of_a_call(I, H, O, Z, m, dtype, which, workspace, direct):
+    """A call is on the kernels of small calls, on wide blocks or on neither, and both diagnostics say so."""
+    import torch
+    dtype = getattr(torch, dtype)
+    d = binding.mm_desc(H, O, Z, Z, m, 0, np.float32(1.0), wl.draw_hash(np.random.default_rng(2)))
+    assert binding.roast_mm_direct_blocks(d, dtype, I, which, workspace) == direct
+    assert (binding.roast_mm_wide_blocks(d, dtype, I, which, workspace) is None) == (direct is not None)
+    if direct:
+        assert dtype == torch.float32 or workspace or binding.roast_mm_strip_blocks(d, I, which) == 1
+    assert binding.roast_mm_direct_blocks(d, dtype, 0, which, workspace) is None and binding.roast_mm_direct_blocks(d, dtype, I, 2, workspace) is None
+    bad = binding.mm_desc(H, O, Z, Z, 100, 0, np.float32(1.0), wl.draw_hash(np.random.default_rng(2)))      # |M| smaller than a tile
+    assert binding.roast_mm_direct_blocks(bad, dtype, I, which, workspace) is None
+
+
 @pytest.mark.parametrize("I,H,O,m,wide", [
-    (1024, 192, 512, 6 << 20, False),        # eight steps
-    (1024, 192, 448, 6 << 20, True),         # seven
-    (1024, 192, 520, 6 << 20, True),         # a ragged one
-    (1024, 192, 512, 4 << 20, True),         # the shadow has -M
-    (1024, 192, 512, (4 << 20) + 1, False),
+    (4096, 960, 512, 6 << 20, False),        # eight steps
+    (4096, 960, 448, 6 << 20, True),         # seven
+    (4096, 960, 520, 6 << 20, True),         # a ragged one
+    (4096, 960, 512, 4 << 20, True),         # the shadow has -M
+    (4096, 960, 512, (4 << 20) + 1, False),
     (6144, 768, 4096, 6 << 20, False),       # 192 blocks of 256 x 96
     (6145, 768, 4096, 6 << 20, True),        # 200
 ])
@@ -149,6 +173,7 @@ def test_dx_of_a_large_m_leaves_small_wide_blocks(I, H, O, m, wide):
     import torch
     d = binding.mm_desc(H, O, 64, 64, m, 0, np.float32(1.0), wl.draw_hash(np.random.default_rng(2)))
     assert (binding.roast_mm_wide_blocks(d, torch.bfloat16, I, 1) is not None) == wide
+    assert binding.roast_mm_direct_blocks(d, torch.bfloat16, I, 1) is None
     if binding.roast_mm_bwd_dx_workspace(d, torch.bfloat16, I) > 0:      # a split contraction stays on the wide blocks
         assert binding.roast_mm_wide_blocks(d, torch.bfloat16, I, 1, True)[3] > 1
 
