@@ -32,6 +32,7 @@ struct __attribute__((packed, aligned(4))) Floats {
 
 constexpr int kWaves = 8;
 constexpr int kTable = 2048;             // tile-table entries (8 bytes each) in LDS
+constexpr int64_t kMaxBlocks = 0xffffffffll / (64 * kWaves);   // of a launch, whose threads are counted in 32 bits
 
 struct DirectArgs {
   MMArgs a;
@@ -276,8 +277,7 @@ constexpr Variant kVariants[] = {{false, 1, 1, {3.8, 3.5}, {2.7, 3.3}},
 
 template <typename T, bool SH, bool DX, int MI, int NJ>
 roast_status launch_one(const DirectArgs& p, hipStream_t s) {
-  const int64_t blocks = cdiv(p.a.I, 16 * MI) * p.nbx;
-  if (blocks > 0x7fffffffll) return ROAST_ERR_UNSUPPORTED;
+  const int64_t blocks = cdiv(p.a.I, 16 * MI) * p.nbx;   // (direct_plan: at most kMaxBlocks)
   constexpr size_t lds = std::max<size_t>((size_t)kTable * 8, (size_t)kWaves * std::min(16 * MI * 16 * NJ, 2048) * 4);
   static_assert(lds <= 64 * 1024, "LDS without an attribute");
   hipLaunchKernelGGL((k_mm_direct<T, SH, DX, MI, NJ>), dim3((unsigned)blocks), dim3(64 * kWaves), lds, s, p);
@@ -324,7 +324,9 @@ DirectPlan direct_plan(int which, bool bf16, const MMArgs& a) {
   const int64_t K = which ? a.O : a.H, N = which ? a.H : a.O;
   for (const Variant& v : kVariants) {
     if (v.bf16 != bf16 || v.alone[which] == 0.0 || !direct_ok(a, bf16, which == 1, 16 * v.nj)) continue;
-    const double blocks = (double)cdiv(a.I, 16 * v.mi) * (double)cdiv(N, 16 * v.nj), r = blocks / 256.0;
+    const int64_t blocks = cdiv(a.I, 16 * v.mi) * cdiv(N, 16 * v.nj);
+    if (blocks > kMaxBlocks) continue;
+    const double r = (double)blocks / 256.0;
     const double us = 5.0 + 1e-3 * (double)K * (r <= 1.0 ? v.alone[which] : v.busy[which] * 0.5 * (r + std::ceil(r)));
     if (us < best.us) best = {v.mi, v.nj, us};
   }

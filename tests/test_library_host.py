@@ -158,6 +158,20 @@ def test_the_diagnostics_name_the_kernels_of_a_call(I, H, O, Z, m, dtype, which,
     assert binding.roast_mm_direct_blocks(bad, dtype, I, which, workspace) is None
 
 
+@pytest.mark.parametrize("I,H,O,which,direct", [
+    (524_256, 16384, 256, 1, (32, 32, 1, 1)),      # 8 388 096 blocks of 512 threads
+    (524_257, 16384, 256, 1, (16, 64, 1, 1)),      # 8 388 608 would be 2^32 threads: 8 388 352 of another block
+    (524_288, 16384, 256, 1, None),                # 2^32 with that too
+    (524_288, 256, 32704, 0, (32, 64, 1, 1)),      # forward
+    (524_288, 256, 32768, 0, None),
+])
+def test_a_launch_of_small_blocks_has_fewer_than_2_to_the_32_threads(I, H, O, which, direct):
+    """fp32 without a workspace: the kernels of small calls take any size that one launch can hold, the generic kernels the rest."""
+    import torch
+    d = binding.mm_desc(H, O, 64, 64, 65536, 0, np.float32(1.0), wl.draw_hash(np.random.default_rng(2)))
+    assert binding.roast_mm_direct_blocks(d, torch.float32, I, which) == direct
+
+
 @pytest.mark.parametrize("I,H,O,m,wide", [
     (4096, 960, 512, 6 << 20, False),        # eight steps
     (4096, 960, 448, 6 << 20, True),         # seven
