@@ -377,9 +377,11 @@ struct BucketPlan {
   int R() const { return (int)(g << s_log2); }
 };
 
-// Buckets of 4096 slots, and no more than 256 of them: a route workgroup waits for one reservation in each bucket, and
-// a list's workgroups can share out its slots (AccPlan).  6.8 M chunks with 1024 buckets of a 4 Mi-slot M 412 us, with 250 of
-// 16384 slots 248; 313 of 4096 and 250 of 5120 slots of 1.28 M 239 and 237.  (At most 10 parts of 4096 slots.)
+// Buckets of 4096 slots, and no more than 256 of them, or 512 of a larger M.  Few: a route workgroup waits for one reservation in
+// each bucket, and the list of a bucket with popular rows has room for less (of 6.8 M chunks over 3 Mi slots, 512 lists spill 84 000 that
+// every workgroup then looks through: 516 us, with 256 303).  But a list's workgroups that share out the slots (AccPlan) read all of
+// it, more of them the longer a bucket is, which counts more the shorter a chunk is: from 2 Mi slots on with chunks of 16 (13.6 M
+// chunks over 6 Mi: 256 buckets 576 us, 512 487), from 4 Mi on with 32 (6.8 M over 6 Mi 327 and 294, but 6.2 M over 4 Mi with a fixed order 393 and 461).
 inline BucketPlan bucket_plan(const EmbedArgs& a) {
   BucketPlan p{};
   p.n_items = a.N * a.C;
@@ -391,7 +393,8 @@ inline BucketPlan bucket_plan(const EmbedArgs& a) {
          a.hash.use_sign != 2 &&                     // list entries carry one sign per chunk
          room_buckets <= kMaxBuckets;
   if (!p.ok) return p;
-  const int64_t want = std::min<int64_t>(std::max<int64_t>(4096, (a.m_size + 255) / 256), 10 * 4096);
+  const int64_t most = a.m_size > std::min(a.Z, 32) * (128ll << 10) ? 512 : 256;
+  const int64_t want = std::min<int64_t>(std::max<int64_t>(4096, (a.m_size + most - 1) / most), 10 * 4096);
   while (((want - 1) >> p.s_log2) + 1 > 8) ++p.s_log2;
   p.g = (uint32_t)(((want - 1) >> p.s_log2) + 1);
   p.nb = (int)((a.m_size + p.R() - 1) / p.R());
@@ -419,29 +422,40 @@ struct AccPlan {
   int q_log2;            // a workgroup owns R >> q_log2 slots
   uint32_t cap;          // of a list
   uint32_t spill_cap;    // of what lies behind the lists: the entries that found theirs full, where every workgroup looks for its own
-  uint32_t seg_len, most;   // a list of more than seg_len entries is read by several workgroups to a part, at most `most`
+  // A list is read by several workgroups to a part, at most `most`: one for each seg_len entries, of which those up to the mean
+  // load count `share` each (the nearest number, or the next above: `up` is half of seg_len, or all but one)
+  uint32_t seg_len, up, mean, most;
+  float share;
   bool owned;            // (fixed point) every slot has one workgroup that sees all of its chunks and writes dM
   __host__ __device__ int R() const { return (int)(g << s_log2); }
+  __host__ __device__ uint32_t segments(uint32_t count) const {
+    const uint32_t usual = count < mean ? count : mean, n = ((uint32_t)((float)usual * share) + (count - usual) + up) / seg_len;
+    return n < 1u ? 1u : n > most ? most : n;
+  }
   __device__ uint32_t bucket(uint32_t off) const { return __umulhi(off >> s_log2, mu); }   // exact: off < 2^31, g <= 8
 };
 
-// Every fp32 add to dM rounds, so there is one per slot and kSeg chunks of a bucket, or one in all where lists are
-// shorter on average.  (Segments of 16384 take 257 us on 6.8 M chunks over 250 buckets, of 8192 238: a CU holds two workgroups.)
+// Every fp32 add to dM rounds, so there is one per slot and kSeg chunks of the 4096 slots around it, or one in all where those get
+// fewer on average.  In a bucket of more slots the mean load is spread evenly over them, what a list has beyond it starts at a
+// few popular rows and may be all in one place.  With a workgroup for every kSeg entries of a list instead, 6.2 M chunks over 4 Mi
+// slots took 250 us and were 4.6e-8 off the exact gradient; this takes 258 and is 2.9e-8 off; 6.8 M over 1.28 M 236 and 4.8e-8, 239 to 246 and
+// 4.3e-8.  From 4 Mi slots on popular rows are split too where lists are short: one workgroup to a list takes 306 us instead of 258 (2.6e-8).
 inline AccPlan acc_plan(const EmbedArgs& a, const BucketPlan& p, bool fixed) {
   AccPlan k{};
   k.s_log2 = p.s_log2; k.g = p.g; k.nb = p.nb;
   k.mu = (uint32_t)(((1ull << 32) + p.g - 1) / p.g);
   const int64_t room = (int64_t)((p.total - p.list_off) / 8), mean = p.n_items / p.nb;
+  k.share = fixed ? 1.f : 4096.f / (float)k.R();
   // (fixed point: one workgroup while that costs less than an accumulator of all of M to clear and to add up)
-  const bool many = mean > (fixed ? kSeg / 2 * 3 : kSeg);
+  const bool many = fixed ? mean > kSeg / 2 * 3 : mean * 4096 > (int64_t)kSeg * k.R() || a.m_size >= (4ll << 20);
   k.owned = fixed && !many;
   // Skew: lists have room for twice their mean load and half of what there is beyond that, the rest is spill.  Owned slots:
   // lists have room for the mean load and all there is beyond twice that, any number of entries can be spilled.
   k.cap = (uint32_t)((k.owned ? room - p.n_items : p.n_items + room / 2) / p.nb);
   k.spill_cap = (uint32_t)std::min<int64_t>(room - (int64_t)p.nb * k.cap, 0x7fffffff);
-  k.seg_len = many ? (uint32_t)kSeg : k.cap;
-  k.most = (k.cap + k.seg_len - 1) / k.seg_len;
-  const int64_t wgs = p.nb * std::max<int64_t>(1, mean / k.seg_len);
+  k.seg_len = (uint32_t)kSeg; k.up = (uint32_t)(fixed || k.R() == 4096 ? kSeg - 1 : kSeg / 2); k.mean = (uint32_t)mean; k.most = many ? ~0u : 1u;
+  k.most = k.segments(k.cap);
+  const int64_t wgs = p.nb * (many ? std::max<int64_t>(1, (int64_t)((float)mean * k.share) / kSeg) : 1);
   // parts: so that a CU holds two workgroups, and a workgroup for most of the places (512: two to a CU)
   while (acc_lds(k.R() >> k.q_log2, a.Z) > 80 * 1024 || (k.q_log2 < 3 && wgs << k.q_log2 < 400 && k.q_log2 < k.s_log2 && (int64_t)a.Z << (k.q_log2 + 1) <= k.R())) ++k.q_log2;
   return k;
@@ -747,7 +761,7 @@ __global__ __launch_bounds__(kAccThreads, 4) void k_embed_accum(EmbedArgs a, Acc
   const int64_t slot0 = (int64_t)b * k.R() + part * S;
   if (slot0 >= a.m_size) return;
   const uint32_t count = min(cursor[b], k.cap), spilled = min(cursor[k.nb], k.spill_cap);
-  const uint32_t nseg = max(1u, min(k.most, (count + k.seg_len - 1) / k.seg_len));
+  const uint32_t nseg = k.segments(count);
   if (seg >= nseg) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // image: Z slots of the part before, this part's, Z slots of the next

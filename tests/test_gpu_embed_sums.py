@@ -44,14 +44,15 @@ def test_a_popular_row_keeps_its_digits(roast, N, D, Z):
 
 @pytest.mark.parametrize("N,D,Z,m_size", [
     (65_536, 32, 32, 200_003),      # 1337 chunks to a bucket: one segment
-    (65_536, 32, 32, 50_021),       # 5041: several, their sums meet in fp64
+    (65_536, 32, 32, 50_021),       # 5041
     (60_001, 64, 16, 190_000),
     (20_000, 512, 128, 300_000),
-    (40_000, 512, 256, 600_000),    # one or two segments
+    (40_000, 512, 256, 600_000),
     (66_000, 1024, 1024, 500_000),  # chunks as long as a quarter of a bucket
+    (2_200_000, 16, 16, 2_000_000), # buckets of 8192 slots, 8980 chunks to each
 ])
 def test_a_slot_is_rounded_once(roast, N, D, Z, m_size):
-    """No bucket has more than 8192 chunks, and dM is zero before: the gradient of a slot is the fp64 sum, rounded to
+    """No 4096 slots have more than 8192 chunks, and dM is zero before: the gradient of a slot is the fp64 sum, rounded to
     fp32 once (twice, and added, where the chunks of two buckets meet: a bucket's first Z slots)."""
     rng = np.random.default_rng(N + Z)
     h = wl.draw_hash(rng, use_sign=True, align=1)
@@ -72,8 +73,7 @@ def test_a_slot_is_rounded_once(roast, N, D, Z, m_size):
 
 
 def test_a_workspace_at_any_multiple_of_four_bytes(roast):
-    """Sums of a bucket are added to in 64-bit atomics, which only take addresses that are multiples of 8: a workspace
-    that is not has none.  Whole numbers: exact either way."""
+    """The lists' 8-byte entries lie behind the cursors wherever the workspace starts.  Whole numbers: exact."""
     N, D, Z, m_size = 65_536, 32, 32, 50_021
     rng = np.random.default_rng(6)
     h = wl.draw_hash(rng, use_sign=True, align=1)
