@@ -440,6 +440,8 @@ struct AccPlan {
 // few popular rows and may be all in one place.  With a workgroup for every kSeg entries of a list instead, 6.2 M chunks over 4 Mi
 // slots took 250 us and were 4.6e-8 off the exact gradient; this takes 258 and is 2.9e-8 off; 6.8 M over 1.28 M 236 and 4.8e-8, 239 to 246 and
 // 4.3e-8.  From 4 Mi slots on popular rows are split too where lists are short: one workgroup to a list takes 306 us instead of 258 (2.6e-8).
+// Fixed point is exact however it is cut: one pass of the sort, where chunks are long enough and a part is a whole bucket
+// (6.8 M chunks of 32 over 0.1 Mi slots 362 -> 354 us, 3.4 M 218 -> 204, of 64 363 -> 337; 6.8 M of 32 over 0.6 Mi 349 -> 356, of 16 535 -> 548).
 inline AccPlan acc_plan(const EmbedArgs& a, const BucketPlan& p, bool fixed) {
   AccPlan k{};
   k.s_log2 = p.s_log2; k.g = p.g; k.nb = p.nb;
@@ -453,7 +455,8 @@ inline AccPlan acc_plan(const EmbedArgs& a, const BucketPlan& p, bool fixed) {
   // lists have room for the mean load and all there is beyond twice that, any number of entries can be spilled.
   k.cap = (uint32_t)((k.owned ? room - p.n_items : p.n_items + room / 2) / p.nb);
   k.spill_cap = (uint32_t)std::min<int64_t>(room - (int64_t)p.nb * k.cap, 0x7fffffff);
-  k.seg_len = (uint32_t)kSeg; k.up = (uint32_t)(fixed || k.R() == 4096 ? kSeg - 1 : kSeg / 2); k.mean = (uint32_t)mean; k.most = many ? ~0u : 1u;
+  k.seg_len = (uint32_t)(fixed && k.R() == 4096 && a.Z >= 32 ? kPass : kSeg); k.up = fixed || k.R() == 4096 ? k.seg_len - 1 : k.seg_len / 2;
+  k.mean = (uint32_t)mean; k.most = many ? ~0u : 1u;
   k.most = k.segments(k.cap);
   const int64_t wgs = p.nb * (many ? std::max<int64_t>(1, (int64_t)((float)mean * k.share) / kSeg) : 1);
   // parts: so that a CU holds two workgroups, and a workgroup for most of the places (512: two to a CU)
