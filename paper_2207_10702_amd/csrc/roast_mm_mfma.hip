@@ -1353,12 +1353,26 @@ int mfma_dx_splits(const MMArgs& a) {
   return (mfma_dx_ok(a) || mfma_elem_ok(a)) ? mm_pick_splits(cdiv(a.H, kBN) * cdiv(a.I, kBM), a.O) : 1;
 }
 
+// The wide blocks that a dX call with a copy of M runs on.  Where the hash sign is an XOR of the weight fragments there (no
+// copy of -M), 128 x 192 blocks in one round lose to the kernel below with 256 x 96 blocks, which applies it as it stages the
+// weights, if those make a round too and leave a quarter of the CUs idle (nearer to a full round the two are even; below
+// eight steps the wide blocks start faster).  Over 250 shapes of an M of 6 Mi the wide blocks took 6 % more: 1738 x 384 x 5760 73 us,
+// this 63; 1096 x 3008 x 640 16.6 and 14.1.  Split contractions stay: 2 % the other way.
+static WidePlan dx_plan(const MMArgs& a, int max_parts) {
+  const WidePlan w = wide_dx_plan(a, max_parts, false);
+  if (w.bm != 128 || w.nblk > 1 || w.parts > 1 || shadow_copies(a.m_size) == 4 || a.O % BK != 0 || !mfma_dx_ok(a)) return w;
+  return cdiv(a.I, 128) * cdiv(a.H, 192) <= 256 && cdiv(a.I, kBM) * cdiv(a.H, kBNarrow) <= 192 && a.O >= 8 * BK ? WidePlan{} : w;
+}
+
 // Modelled time of the kernels below with a copy of M (what a call without one costs more does not count, for the same sums).  Shapes that the
-// wide blocks do not take: 256 x 128 blocks of 0.95 us a step.
+// wide blocks do not take: 256 x 128 blocks of 0.95 us a step, or where dx_plan leaves it to 256 x 96 blocks, those: 0.61 a step and 6.9 (dX over an M of
+// more than 4 Mi slots, 320 x 1888 x 576 11.9 -> 7.7 us here, 231 x 4656 x 1024 stays, 16.9 and 21.7).
 static double bf16_us(int which, const MMArgs& a, bool ws) {
   const int64_t K = which ? a.O : a.H, N = which ? a.H : a.O;
-  const WidePlan w = which ? wide_dx_plan(a, ws ? kWideParts : 1, false) : wide_fwd_plan(a, ws ? kWideParts : 1, false);
+  const int max_parts = ws ? kWideParts : 1;
+  const WidePlan w = which ? dx_plan(a, max_parts) : wide_fwd_plan(a, max_parts, false);
   if (w.bm) return w.us;
+  if (which && wide_dx_plan(a, max_parts, false).bm) return 0.61 * (double)(K / BK) + 6.9;
   const int parts = !ws ? 1 : which ? mfma_dx_splits(a) : mfma_fwd_splits(a);
   return (double)cdiv(cdiv(N, kBN) * cdiv(a.I, kBM) * parts, 256) * (0.95 * (double)cdiv(cdiv(K, parts), BK) + 4.0) +
          (parts > 1 ? 4.0 + (double)parts * (double)a.I * (double)N * 4.0 / 3.0e6 : 0.0);
@@ -1409,17 +1423,6 @@ roast_status mfma_mm_fwd(const MMArgs& a, const void* X, int64_t ldx, const floa
     st = shadow ? launch<MODE_FWD, BM, BN, 4, 2, true>(p, grid, s) : launch<MODE_FWD, BM, BN, 4, 2, false>(p, grid, s);
   }
   return st != ROAST_OK ? st : split_finish(p, grid.z, a.I, a.O, s);
-}
-
-// The wide blocks that a dX call with a copy of M runs on.  Where the hash sign is an XOR of the weight fragments there (no
-// copy of -M), 128 x 192 blocks in one round lose to the kernel below with 256 x 96 blocks, which applies it as it stages the
-// weights, if those make a round too and leave a quarter of the CUs idle (nearer to a full round the two are even; below
-// eight steps the wide blocks start faster).  Over 250 shapes of an M of 6 Mi the wide blocks took 6 % more: 1738 x 384 x 5760 73 us,
-// this 63; 1096 x 3008 x 640 16.6 and 14.1.  Split contractions stay: 2 % the other way.
-static WidePlan dx_plan(const MMArgs& a, int max_parts) {
-  const WidePlan w = wide_dx_plan(a, max_parts, false);
-  if (w.bm != 128 || w.nblk > 1 || w.parts > 1 || shadow_copies(a.m_size) == 4 || a.O % BK != 0 || !mfma_dx_ok(a)) return w;
-  return cdiv(a.I, 128) * cdiv(a.H, 192) <= 256 && cdiv(a.I, kBM) * cdiv(a.H, kBNarrow) <= 192 && a.O >= 8 * BK ? WidePlan{} : w;
 }
 
 roast_status mfma_mm_bwd_dx(const MMArgs& a, const void* dY, int64_t ldy, const float* M, const void* M_bf16,

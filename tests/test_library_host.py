@@ -143,6 +143,8 @@ def test_wide_block_diagnostic():
     (4096, 4096, 4096, 64, 1 << 20, "float32", 0, False, (32, 64, 1, 1)),    # without a workspace there are no planes
     (4096, 4096, 4096, 64, 1 << 20, "float32", 0, True, None),
     (8192, 768, 3072, 64, 47185, "bfloat16", 0, False, None),
+    # dX over an M whose copy has no -M: compared with the 256 x 96 blocks that it would run on
+    (320, 1888, 576, 32, 15273911, "bfloat16", 1, True, (64, 64, 1, 1)),
 ])
 def test_the_diagnostics_name_the_kernels_of_a_call(I, H, O, Z, m, dtype, which, workspace, direct):
     """A call is on the kernels of small calls, on wide blocks or on neither, and both diagnostics say so."""
