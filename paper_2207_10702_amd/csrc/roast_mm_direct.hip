@@ -263,17 +263,18 @@ bool direct_ok(const MMArgs& a, bool bf16, bool dx, int bn) {
 struct Variant {
   bool bf16;
   int mi, nj;
+  double fixed;                          // microseconds: a launch, a workgroup's start and end
   double alone[2], busy[2];              // nanoseconds a contraction index (forward, dX; 0: not built): where every CU has one workgroup, where more
 };
-constexpr Variant kVariants[] = {{false, 1, 1, {3.8, 3.5}, {2.7, 3.3}},
-                                 {false, 1, 2, {5.2, 5.3}, {4.3, 5.1}},
-                                 {false, 1, 4, {6.6, 8.6}, {6.7, 8.7}},
-                                 {false, 2, 2, {6.4, 6.5}, {6.4, 7.2}},
-                                 {false, 2, 4, {10.4, 0.0}, {10.7, 0.0}},   // (dX: its registers leave a CU one workgroup)
-                                 {true, 1, 2, {2.34, 2.28}, {1.7, 2.45}},
-                                 {true, 1, 4, {3.05, 4.2}, {2.65, 4.1}},
-                                 {true, 2, 4, {3.55, 4.85}, {3.5, 4.85}},
-                                 {true, 4, 4, {5.5, 6.8}, {5.55, 7.05}}};
+constexpr Variant kVariants[] = {{false, 1, 1, 2.8, {3.15, 3.45}, {2.7, 3.1}},
+                                 {false, 1, 2, 3.4, {4.1, 4.95}, {4.3, 5.0}},
+                                 {false, 1, 4, 3.8, {6.6, 8.6}, {6.7, 8.7}},
+                                 {false, 2, 2, 4.0, {6.15, 6.6}, {6.4, 6.7}},
+                                 {false, 2, 4, 4.4, {10.7, 0.0}, {10.2, 0.0}},   // (dX: its registers leave a CU one workgroup)
+                                 {true, 1, 2, 5.0, {2.34, 2.28}, {1.7, 2.45}},
+                                 {true, 1, 4, 5.0, {3.05, 4.2}, {2.65, 4.1}},
+                                 {true, 2, 4, 5.0, {3.55, 4.85}, {3.5, 4.85}},
+                                 {true, 4, 4, 5.0, {5.5, 6.8}, {5.55, 7.05}}};
 
 template <typename T, bool SH, bool DX, int MI, int NJ>
 roast_status launch_one(const DirectArgs& p, hipStream_t s) {
@@ -312,22 +313,31 @@ roast_status launch_variant(bool bf16, int mi, int nj, const DirectArgs& p, hipS
 
 }  // namespace
 
-// The block with the smallest modelled time, a launch and 5 us of start and end included.  (An fp32 call with a workspace comes here where
-// that is 8 % less than what the three-plane kernels are modelled to take: up to 1 GFLOP mostly, 4 at the few rows or columns that leave those idle.
-// 64 x 256 x 256 17.9 -> 11.0 us of which the GPU is busy half, 885 x 576 x 384 26.5 -> 11.4, 512 x 1024 x 1024 32 -> 17, 46 x 3136 x 1728 31.6 -> 20.9; 80 x 7040 x 1152
-// 45.7 -> 44.8; 2048 x 1024 x 1024 stays, 46.9 against 46.9.  Without one, against the generic kernel: 300 x 1096 x 520 162 -> 12.9.  bf16, by the same
-// margin on what the wide blocks are modelled to take: 512 x 2048 x 2048 23.8 -> 17.2 (two launches), 206 x 1664 x 1152 17.0 -> 10.5; 1024 x 2048 x 2048 stays, 27 and 29;
-// without a workspace 35 x 4352 x 5504 43.7 -> 19.6.  A 64 x 64 block of bf16 takes 167 ns a unit of 32, 20 bytes a clock and CU: neither more units in flight nor
-// fewer address instructions, whole lines of A or other channels of the L2 change that.)
+// The block with the smallest modelled time.  The fp32 constants are fitted to 300 timed launches (most within 8 %) of 16 .. 1024 rows: up to two
+// workgroups to a CU both run to the end; beyond that a CU takes the next as one ends.  Where M is larger than an XCD's L2 (4 MiB: 1 Mi slots) its
+// share beyond that comes from the memory-side cache, in pieces of a tile's row: 6.5 TB/s, 3.5 where those are 64 or 128 bytes.
+// An fp32 call with a workspace comes here where that is 8 % less than what the three-plane kernels are modelled to take: up to 1 GFLOP mostly, 4 at the few rows
+// or columns that leave those idle.  Of 300 calls of 16 .. 2048 rows the worst loses 3 % by it.  64 x 256 x 256 17.9 -> 11.0 us of which the GPU is busy half,
+// 885 x 576 x 384 26.5 -> 11.4, 512 x 1024 x 1024 32 -> 17, 46 x 3136 x 1728 31.6 -> 20.9, 39 x 7648 x 2496 over 1 Mi slots 48 -> 34, but over 4 Mi it stays (49, here 52 to 60), as
+// does 2048 x 1024 x 1024.  Without one, against the generic kernel: 300 x 1096 x 520 162 -> 12.9.
+// bf16, by the same margin on what the wide blocks are modelled to take: 512 x 2048 x 2048 23.8 -> 17.2 (two launches), 206 x 1664 x 1152 17.0 -> 10.5;
+// 1024 x 2048 x 2048 stays, 27 and 29; without a workspace 35 x 4352 x 5504 43.7 -> 19.6.  A 64 x 64 block of bf16 takes 167 ns a unit of 32, 20 bytes a clock and CU:
+// neither more units in flight nor fewer address instructions, whole lines of A or other channels of the L2 change that.
 DirectPlan direct_plan(int which, bool bf16, const MMArgs& a) {
   DirectPlan best{0, 0, 1e300};
-  const int64_t K = which ? a.O : a.H, N = which ? a.H : a.O;
+  const int64_t K = which ? a.O : a.H, N = which ? a.H : a.O, l2 = 1 << 20;
   for (const Variant& v : kVariants) {
     if (v.bf16 != bf16 || v.alone[which] == 0.0 || !direct_ok(a, bf16, which == 1, 16 * v.nj)) continue;
     const int64_t blocks = cdiv(a.I, 16 * v.mi) * cdiv(N, 16 * v.nj);
     if (blocks > kMaxBlocks) continue;
     const double r = (double)blocks / 256.0;
-    const double us = 5.0 + 1e-3 * (double)K * (r <= 1.0 ? v.alone[which] : v.busy[which] * 0.5 * (r + std::ceil(r)));
+    double rounds = 0.5 * (r + std::ceil(r)), us;
+    if (!bf16 && r <= 2.0) rounds = 2.0;            // (some CUs have two workgroups from the start)
+    us = v.fixed + 1e-3 * (double)K * (r <= 1.0 ? v.alone[which] : v.busy[which] * rounds) + (bf16 ? 0.0 : 0.6 * std::max(0.0, std::ceil(r) - 2.0));
+    if (!bf16 && a.m_size > l2) {                   // weights from beyond the L2, once for each row of blocks
+      const double bytes = (double)cdiv(a.I, 16 * v.mi) * (double)K * (double)N * 4.0 * (1.0 - (double)l2 / (double)a.m_size);
+      us = std::max(us, v.fixed + bytes / (which || v.nj == 4 || a.Z2 <= 16 * v.nj ? 6.5e6 : 3.5e6));
+    }
     if (us < best.us) best = {v.mi, v.nj, us};
   }
   return best;

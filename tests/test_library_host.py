@@ -143,6 +143,10 @@ def test_wide_block_diagnostic():
     (4096, 4096, 4096, 64, 1 << 20, "float32", 0, False, (32, 64, 1, 1)),    # without a workspace there are no planes
     (4096, 4096, 4096, 64, 1 << 20, "float32", 0, True, None),
     (8192, 768, 3072, 64, 47185, "bfloat16", 0, False, None),
+    # few rows and a long contraction: M in the L2 or beyond it, one workgroup on some CUs and two on others
+    (39, 7648, 2496, 64, 1 << 20, "float32", 0, True, (16, 32, 1, 1)),
+    (39, 7648, 2496, 64, 4 << 20, "float32", 0, True, None),
+    (34, 14656, 1472, 64, 2179514, "float32", 0, True, (16, 32, 1, 1)),
     # dX over an M whose copy has no -M: compared with the 256 x 96 blocks that it would run on
     (320, 1888, 576, 32, 15273911, "bfloat16", 1, True, (64, 64, 1, 1)),
 ])
