@@ -427,6 +427,7 @@ struct AccPlan {
   uint32_t seg_len, up, mean, most;
   float share;
   bool owned;            // (fixed point) every slot has one workgroup that sees all of its chunks and writes dM
+  bool take_max;         // ... and the route kernel takes the largest |dOut|
   __host__ __device__ int R() const { return (int)(g << s_log2); }
   __host__ __device__ uint32_t segments(uint32_t count) const {
     const uint32_t usual = count < mean ? count : mean, n = ((uint32_t)((float)usual * share) + (count - usual) + up) / seg_len;
@@ -451,6 +452,7 @@ inline AccPlan acc_plan(const EmbedArgs& a, const BucketPlan& p, bool fixed) {
   // (fixed point: one workgroup while that costs less than an accumulator of all of M to clear and to add up)
   const bool many = fixed ? mean > kSeg / 2 * 3 : mean * 4096 > (int64_t)kSeg * k.R() || a.m_size >= (4ll << 20);
   k.owned = fixed && !many;
+  k.take_max = k.owned && a.B <= 4 * a.N;   // (beyond that few workgroups would read a large dOut: 70 000 chunks of 32, 2 M bags 197 us, 95 with a launch for it; 0.4 M 70 and 68, 0.14 M 42 and 46)
   // Skew: lists have room for twice their mean load and half of what there is beyond that, the rest is spill.  Owned slots:
   // lists have room for the mean load and all there is beyond twice that, any number of entries can be spilled.
   k.cap = (uint32_t)((k.owned ? room - p.n_items : p.n_items + room / 2) / p.nb);
@@ -667,7 +669,7 @@ __global__ __launch_bounds__(kRouteThreads) void k_embed_route(EmbedArgs a, AccP
     got[j] = cnt[j] ? atomicAdd(&cursor[i], cnt[j]) : 0u;
     sum += cnt[j];
   }
-  if (twice) take_max();
+  if (FIXED && k.take_max) take_max();
   uint32_t run = sum;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
@@ -1002,7 +1004,7 @@ roast_status bucket_run(const EmbedArgs& a, const BucketPlan& p, const int64_t* 
         return ROAST_ERR_HIP;
       configured.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL(k_embed_route_init, dim3((unsigned)(p.nb + 256) / 256), dim3(256), 0, s, p.nb, cursor, k.owned ? (uint32_t*)fs : nullptr);
+    hipLaunchKernelGGL(k_embed_route_init, dim3((unsigned)(p.nb + 256) / 256), dim3(256), 0, s, p.nb, cursor, k.take_max ? (uint32_t*)fs : nullptr);
     hipLaunchKernelGGL(k_embed_route<FIXED>, dim3((unsigned)((a.N + rows_wg - 1) / rows_wg)), dim3(kRouteThreads), lds_route, s, a,
                        k, walk_ok(a), items, rows, tables, cursor, list, dOut, dM, pbits, fs, acc);
     hipLaunchKernelGGL(accum, grid, dim3(kAccThreads), acc_lds(S, a.Z), s, a, k, cursor, list, dOut, dM, pbits, fs, acc);
@@ -1067,13 +1069,14 @@ roast_status embed_bwd_det_run(const EmbedArgs& a, const int64_t* rows, const ui
   const int pbits = fixed_pbits(a.N * a.C);
   const BucketPlan p = bucket_plan(a);
   const bool routed = bucket_worthwhile(p, dOut);
-  // where every slot has one owner, the accumulator is not used, and the route kernel takes the maximum
-  const bool owned = routed && acc_plan(a, p, true).owned;
+  // where every slot has one owner, the accumulator is not used, and mostly the route kernel takes the maximum
+  const AccPlan k = routed ? acc_plan(a, p, true) : AccPlan{};
+  const bool owned = k.owned;
   const int64_t n_el = a.N * a.D;                               // contributions
   const int64_t n_grad = (a.bag_off ? a.B : a.N) * a.D;          // elements of dOut
-  if (!owned) {
+  if (!k.take_max) {
     // zero the scale record and the accumulator (contiguous: fs_off == 0, acc follows)
-    const int64_t zero_words = (int64_t)((l.acc_off + (size_t)a.m_size * 8) / 4);
+    const int64_t zero_words = (int64_t)((owned ? sizeof(FixedScale) : l.acc_off + (size_t)a.m_size * 8) / 4);
     const int64_t zb = (zero_words + 255) / 256;
     if (zb > 0x7fffffffll) return ROAST_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(k_embed_zero, dim3((unsigned)zb), dim3(256), 0, s, (uint32_t*)base, zero_words);

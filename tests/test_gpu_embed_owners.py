@@ -64,3 +64,21 @@ def test_lane_layouts_and_parts(roast, m_size, N, D, Z):
     h = wl.draw_hash(rng, use_sign=True, align=1)
     rows = np.where(rng.random(N) < 0.3, rng.integers(0, 50, N), rng.integers(0, 1 << 33, N)).astype(np.int64)
     check(roast, h, D, Z, m_size, rows, rng)
+
+
+@pytest.mark.parametrize("B", [70_000, 280_000, 280_001])
+def test_more_bags_than_lookups(roast, B):
+    """The largest magnitude of dOut, that of an empty bag here, is found by a launch of its own where most bags are empty."""
+    N, Z, m_size = 70_000, 32, 300_007
+    rng = np.random.default_rng(B)
+    h = wl.draw_hash(rng, use_sign=True, align=1)
+    rows, tables = rng.integers(0, 1 << 33, N), np.zeros(N, dtype=np.uint32)
+    offsets = np.concatenate([[0, 0], np.sort(rng.integers(0, N + 1, B - 2)), [N]]).astype(np.int64)
+    dOut = rng.integers(-3, 4, (B, Z)).astype(np.float32)
+    dOut[0] = 1000.0
+    d = roast.embed_desc(Z, Z, m_size, 1.0, h)
+    ref = oracle.embed_bag_bwd(h, Z, Z, m_size, 1.0, rows, tables, offsets, dOut)
+    ws = torch.empty(roast.roast_embed_bag_bwd_workspace(d, N, B, roast.ROAST_REDUCE_DETERMINISTIC), dtype=torch.uint8, device="cuda").fill_(0xa5)
+    dM = torch.ones(m_size, device="cuda")
+    roast.roast_embed_bag_bwd(d, to_dev(rows), to_dev(tables), to_dev(offsets), to_dev(dOut), dM, roast.ROAST_REDUCE_DETERMINISTIC, ws)
+    assert np.array_equal(to_host_f64(dM), ref + 1.0)
