@@ -188,8 +188,10 @@ roast_status roast_mm_bwd_dx(const roast_mm_desc* d, roast_dtype dt, int64_t I, 
  *    the fp32 bar of the conventions above.  Short calls, and calls without a
  *    workspace, multiply in fp32 from M itself (Z1, Z2, H and O multiples of 4, H and O below 65536; other shapes without
  *    a workspace run on the vector ALUs).
- * The *_workspace queries return the bytes that help for these sizes (0: nothing to gain, or a
- * shape the matrix-core kernels do not cover; the plain call is used).
+ * The *_workspace queries return the bytes that these kernels take for these sizes (0: nothing to gain, or a
+ * shape the matrix-core kernels do not cover; the plain call is used).  Which kernels a call runs on also depends on
+ * what only the call knows (leading dimensions, addresses, a copy of M): a short call is given the bytes and
+ * leaves them alone, but they are checked all the same.
  * workspace: NULL (same as the plain call), or a DEVICE buffer, 16-byte aligned, of at least the
  * queried size (else ROAST_ERR_WORKSPACE); its contents are scratch, owned by the caller, and may be
  * reused by the next call on the same stream.  Results are deterministic for a fixed shape.
@@ -280,7 +282,8 @@ roast_status roast_embed_fwd(const roast_embed_desc* d, int64_t N, const int64_t
 /* Bytes of workspace roast_embed_bwd can use for these sizes and mode (0 = none).
  * ATOMIC: optional -- with it, large batches are first routed by destination (per-bucket lists in
  * the workspace) and summed in on-chip memory before they touch dM; without it every element is an
- * fp32 atomic add into dM.  DETERMINISTIC: required. */
+ * fp32 atomic add into dM.  DETERMINISTIC: required; 8 |M| bytes of it are an accumulator, which a call leaves alone
+ * whose lists are short on average and whose dOut is 16-byte aligned. */
 size_t roast_embed_bwd_workspace(const roast_embed_desc* d, int64_t N, roast_reduce_mode mode);
 
 /*

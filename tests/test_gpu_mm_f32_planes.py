@@ -1,7 +1,8 @@
-"""GPU parity of the fp32 products run on the bf16 matrix cores (three bfloat16 planes per operand,
-six plane products): same oracle and the same fp32 bar (1e-5 max relative error per tensor) as the
-vector-ALU fp32 kernels, on shapes that span several workgroup tiles with ragged edges, small and
-large batches (split contraction), strided rows, and values across many binades."""
+"""GPU parity of the fp32 products with a workspace: on the bf16 matrix cores (three bfloat16 planes per operand,
+six plane products) or, forward and dX of small calls, in fp32 from the operands as they lie: same oracle and the same
+fp32 bar (1e-5 max relative error per tensor) as the vector-ALU fp32 kernels, on shapes that span several workgroup
+tiles with ragged edges, small and large batches (split contraction), strided rows, and values across many binades.
+What is about planes in forward and dX asserts that the call is on them (ON_PLANES)."""
 import numpy as np
 import pytest
 
@@ -12,6 +13,42 @@ from tests.util import F32_TOL, rel_err, to_dev, to_host_f64
 pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
+
+FWD, DX = 0, 1
+# (which product, I, H, O, Z1, Z2, blocks: those of tiles that are multiples of 32, or None: 256 x 128 and 256 x 96), contraction in parts or not
+ON_PLANES = [
+    (FWD, 515, 3072, 512, 24, 24, None, True),
+    (FWD, 515, 2056, 1000, 16, 16, None, True),          # ragged contraction, rows and columns; ten parts
+    (FWD, 6000, 64, 1000, 24, 24, None, False),
+    (FWD, 6000, 520, 1000, 16, 16, None, False),         # ragged, not split
+    (FWD, 4000, 64, 1536, 8, 8, None, False),            # 256 x 96
+    (FWD, 2100, 192, 6144, 64, 64, (256, 256), False),
+    (DX, 130, 2048, 1536, 8, 24, None, True),
+    (DX, 515, 512, 2056, 16, 16, None, True),            # ragged; fifteen parts
+    (DX, 6000, 1000, 64, 8, 24, None, False),
+    (DX, 8000, 520, 200, 64, 8, None, False),            # ragged, not split
+    (DX, 2050, 1536, 64, 24, 24, None, False),           # 256 x 96
+    (DX, 2100, 6144, 192, 64, 64, (256, 256), False),
+]
+
+
+def on_planes(roast, h, case, m, lam):
+    """The descriptor of a call that runs on planes, and its workspace."""
+    which, I, H, O, Z1, Z2, blocks, parts = case
+    d = roast.mm_desc(H, O, Z1, Z2, m, 2, lam, h)
+    assert roast.roast_mm_direct_blocks(d, torch.float32, I, which, True) is None
+    wide = roast.roast_mm_wide_blocks(d, torch.float32, I, which, True)
+    assert (wide and wide[:2]) == blocks
+    K, N = (O, H) if which else (H, O)
+    need = (roast.roast_mm_bwd_dx_workspace if which else roast.roast_mm_fwd_workspace)(d, torch.float32, I)
+    planes = -(-(3 * 2 * I * (-(-K // 8) * 8)) // 256) * 256 + roast.roast_m_planes_bytes(m)
+    assert (need >= planes + 2 * 4 * I * N) == parts and need >= planes - 256
+    return d, ws_tensor(need)
+
+
+def product(roast, which, d, A, M, out, ws, planes=None):
+    return (roast.roast_mm_bwd_dx if which else roast.roast_mm_fwd)(d, A, M, out, ws=ws, M_bf16=planes)
+
 
 # (I, H, O, Z1, Z2, |M|)
 SHAPES = [
@@ -107,6 +144,82 @@ def test_f32_plane_products_worst_case_mantissas(roast, same_sign):
     assert rel_err(to_host_f64(Y), oracle.mm_fwd(Xo, W)) <= F32_TOL
     assert rel_err(to_host_f64(dX), oracle.mm_bwd_dx(dYo, W)) <= F32_TOL
     assert rel_err(to_host_f64(dM), oracle.mm_bwd_dm(h, 1, Z1, Z2, m, 1.0, Xo, dYo)) <= F32_TOL
+
+
+@pytest.mark.parametrize("case", ON_PLANES)
+@pytest.mark.parametrize("pad", [0, 4])
+def test_forward_and_dx_on_planes_match_oracle(roast, case, pad):
+    which, I, H, O, Z1, Z2 = case[:6]
+    K, N, m = *((O, H) if which else (H, O)), 9001
+    rng = np.random.default_rng(I + H + O + pad)
+    h, lam = wl.draw_hash(rng, use_sign=True, align=1), np.float32(0.37)
+    d, ws = on_planes(roast, h, case, m, lam)
+    M = wl.draw_m(rng, m, ("normal", 0.05))
+    A = (rng.standard_normal((I, K)) * np.exp2(rng.integers(-6, 6, size=(I, K)))).astype(np.float32)
+    Md = to_dev(M)
+    Ad = torch.full((I, K + pad), 9.0, device="cuda")[:, :K]
+    Ad.copy_(to_dev(A))
+    outs = []
+    for planes in (roast.roast_m_planes_bf16(Md), None):          # made once, or in the workspace: same bits
+        ws.fill_(0xFF)
+        out = torch.full((I, N + pad), 7.0, device="cuda")
+        product(roast, which, d, Ad, Md, out[:, :N], ws, planes)
+        assert torch.all(out[:, N:] == 7.0)
+        outs.append(out[:, :N])
+    assert torch.equal(*outs)
+    W = oracle.materialize_w(h, 2, H, O, Z1, Z2, float(lam), M)
+    assert rel_err(to_host_f64(outs[0]), (oracle.mm_bwd_dx if which else oracle.mm_fwd)(A.astype(np.float64), W)) <= F32_TOL
+
+
+@pytest.mark.parametrize("case", [ON_PLANES[i] for i in (0, 5, 6, 11)])
+@pytest.mark.parametrize("same_sign", [True, False])
+def test_worst_case_mantissas_on_planes(roast, case, same_sign):
+    """As above, where forward and dX are on planes."""
+    which, I, H, O, Z1, Z2 = case[:6]
+    K, m = O if which else H, 9001
+    rng = np.random.default_rng(98)
+    worst = np.float32(1.0 + 2.0 ** -7 - 2.0 ** -23)
+
+    def draw(shape, spread):
+        v = worst * np.exp2(rng.integers(-spread, spread + 1, size=shape)).astype(np.float32)
+        return v if same_sign else v * rng.choice(np.float32([-1.0, 1.0]), size=shape)
+
+    h = wl.draw_hash(rng, use_sign=not same_sign, align=1)
+    d, ws = on_planes(roast, h, case, m, 1.0)
+    M, A = draw(m, 2) * np.float32(0.05), draw((I, K), 3)
+    got = product(roast, which, d, to_dev(A), to_dev(M), None, ws)
+    W = oracle.materialize_w(h, 2, H, O, Z1, Z2, 1.0, M)
+    assert rel_err(to_host_f64(got), (oracle.mm_bwd_dx if which else oracle.mm_fwd)(A.astype(np.float64), W)) <= F32_TOL
+
+
+def awkward_column(rng, I):
+    """Values of one column of X, and which of them are finite."""
+    exact = np.array([3.4028235e38, -3.4028235e38, 3.3895314e38, 0.99999994, 1.9999999, 16777215.0, 1.0000001,
+                      65504.0, 1e-30, -7.7e-31, 0.0], dtype=np.float32)
+    tiny = np.array([1.1754944e-38, 1e-40, -1e-45, 3e-36], dtype=np.float32)
+    nonfinite = np.array([np.inf, -np.inf, np.nan], dtype=np.float32)
+    col = np.concatenate([exact, tiny, nonfinite, rng.standard_normal(I - 18).astype(np.float32)])
+    return col, np.isfinite(col)
+
+
+@pytest.mark.parametrize("case", [ON_PLANES[i] for i in (0, 4, 5)])
+def test_forward_planes_are_exact_on_awkward_values(roast, case):
+    """As below, on planes: every tile is the one with the 1.0, so that one column of X appears in a column of each."""
+    which, I, H, O, Z1, Z2 = case[:6]
+    rng = np.random.default_rng(9)
+    d, ws = on_planes(roast, wl.draw_hash(rng, use_sign=False, align=1), case, Z1 * Z2, 1.0)
+    M = np.zeros(Z1 * Z2, dtype=np.float32)
+    M[5 * Z2 + 3] = 1.0
+    X = np.zeros((I, H), dtype=np.float32)
+    X[:, 5], fin = awkward_column(rng, I)
+    Y = product(roast, which, d, to_dev(X), to_dev(M), None, ws).cpu().numpy()
+    got, col = Y[:, 3::Z2], X[:, 5:6]
+    big = fin & ((np.abs(col[:, 0]) >= 2.0 ** -100) | (col[:, 0] == 0))
+    np.testing.assert_array_equal(got[big], np.broadcast_to(col, got.shape)[big])
+    assert np.all(np.abs(got[fin].astype(np.float64) - col[fin].astype(np.float64)) <= 2.0 ** -126)
+    assert not np.isfinite(got[~fin]).any()
+    Y[:, 3::Z2] = 0
+    assert not Y[fin].any()
 
 
 def test_plane_split_is_exact_on_awkward_values(roast):

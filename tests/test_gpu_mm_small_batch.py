@@ -78,6 +78,30 @@ def test_split_contraction_matches_oracle(roast, shape, pad):
     assert rel_err(to_host_f64(outs[0][1]), to_host_f64(dXp)) <= 2.0 ** -7
 
 
+@pytest.mark.parametrize("which,I,H,O,Z1,Z2,parts", [
+    (0, 300, 2056, 1088, 8, 8, 7),        # ragged contraction, rows and columns
+    (0, 64, 3072, 64, 8, 24, 12),
+    (1, 130, 1088, 2056, 24, 24, 7),
+    (1, 64, 64, 3072, 16, 16, 12),
+])
+def test_split_contraction_on_128_columns(roast, which, I, H, O, Z1, Z2, parts):
+    """Tiles that the wide blocks do not take, calls that are too long for one launch of small blocks."""
+    m = 9001
+    M, X, dY, h, lam = case(I + H, I, H, O, Z1, Z2, m, 0.41)
+    d = roast.mm_desc(H, O, Z1, Z2, m, 3, lam, h)
+    call, want, A = ((roast.roast_mm_fwd, roast.roast_mm_fwd_workspace, X), (roast.roast_mm_bwd_dx, roast.roast_mm_bwd_dx_workspace, dY))[which]
+    assert roast.roast_mm_direct_blocks(d, torch.bfloat16, I, which, True) is None
+    assert roast.roast_mm_wide_blocks(d, torch.bfloat16, I, which, True) is None
+    need = want(d, torch.bfloat16, I)
+    assert need == parts * 4 * I * (H if which else O)
+    Md, Ad = to_dev(M), to_dev(A)
+    outs = [call(d, Ad, Md, M_bf16=Mb, ws=ws_tensor(need).fill_(0xFF)) for Mb in (roast.roast_m_shadow_bf16(Md), None)]
+    assert torch.equal(*outs)
+    W = oracle.materialize_w(h, 3, H, O, Z1, Z2, float(lam), M)
+    ref = (oracle.mm_bwd_dx if which else oracle.mm_fwd)(wl.act_as_f64(A), W)
+    assert rel_err(to_host_f64(outs[0]), ref) <= BF16_TOL
+
+
 def test_workspace_contract(roast):
     I, H, O, Z1, Z2, m = 512, 2048, 512, 64, 64, 50000
     M, X, dY, h, lam = case(5, I, H, O, Z1, Z2, m, 1.0)

@@ -102,7 +102,7 @@ def test_cfg1_single_layer_fp32_complete(roast):
     ref_dM = oracle.mm_bwd_dm(inp.hash, l.layer_id, cfg.Z1, cfg.Z2, cfg.m_size, cfg.lam, X, dY)
     assert rel_err(to_host_f64(dM), ref_dM) <= F32_TOL
     # the configuration bench.py --workload cfg1_single_f32 times: the same calls with their workspaces
-    # (fp32 on the matrix cores; the 32x32 hash tiles are half the kernel's contraction step)
+    # (forward and dX in one launch each, from the operands as they lie; dM on planes, whose step is two 32x32 hash tiles)
     sizes = (roast.roast_mm_fwd_workspace(d, torch.float32, cfg.I), roast.roast_mm_bwd_dx_workspace(d, torch.float32, cfg.I),
              roast.roast_mm_bwd_dM_workspace_f32(d, cfg.I))
     assert min(sizes) > 0
