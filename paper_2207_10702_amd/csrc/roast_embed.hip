@@ -426,12 +426,19 @@ struct AccPlan {
   // load count `share` each (the nearest number, or the next above: `up` is half of seg_len, or all but one)
   uint32_t seg_len, up, mean, most;
   float share;
+  uint32_t less;         // the last of three and more is that many tenths of the others' length shorter
   bool owned;            // (fixed point) every slot has one workgroup that sees all of its chunks and writes dM
   bool take_max;         // ... and the route kernel takes the largest |dOut|
   __host__ __device__ int R() const { return (int)(g << s_log2); }
   __host__ __device__ uint32_t segments(uint32_t count) const {
+    if (most == 1u) return 1u;
     const uint32_t usual = count < mean ? count : mean, n = ((uint32_t)((float)usual * share) + (count - usual) + up) / seg_len;
     return n < 1u ? 1u : n > most ? most : n;
+  }
+  __host__ __device__ uint32_t length(uint32_t entries, uint32_t nseg) const {
+    if (nseg == 1u) return entries;
+    const uint32_t tenths = 10u * nseg - (nseg < 3u ? 0u : less), whole = entries / tenths;
+    return 10u * whole + (10u * (entries - whole * tenths) + tenths - 1u) / tenths;
   }
   __device__ uint32_t bucket(uint32_t off) const { return __umulhi(off >> s_log2, mu); }   // exact: off < 2^31, g <= 8
 };
@@ -439,7 +446,7 @@ struct AccPlan {
 // Every fp32 add to dM rounds, so there is one per slot and kSeg chunks of the 4096 slots around it, or one in all where those get
 // fewer on average.  In a bucket of more slots the mean load is spread evenly over them, what a list has beyond it starts at a
 // few popular rows and may be all in one place.  With a workgroup for every kSeg entries of a list instead, 6.2 M chunks over 4 Mi
-// slots took 250 us and were 4.6e-8 off the exact gradient; this takes 258 and is 2.9e-8 off; 6.8 M over 1.28 M 236 and 4.8e-8, 239 to 246 and
+// slots took 250 us and were 4.6e-8 off the exact gradient; this takes 258 and is 2.9e-8 off; 6.8 M over 1.28 M 238 and 4.8e-8, 238 and
 // 4.3e-8.  From 4 Mi slots on popular rows are split too where lists are short: one workgroup to a list takes 306 us instead of 258 (2.6e-8).
 // Fixed point is exact however it is cut: one pass of the sort, where chunks are long enough and a part is a whole bucket
 // (6.8 M chunks of 32 over 0.1 Mi slots 362 -> 354 us, 3.4 M 218 -> 204, of 64 363 -> 337; 6.8 M of 32 over 0.6 Mi 349 -> 356, of 16 535 -> 548).
@@ -449,6 +456,7 @@ inline AccPlan acc_plan(const EmbedArgs& a, const BucketPlan& p, bool fixed) {
   k.mu = (uint32_t)(((1ull << 32) + p.g - 1) / p.g);
   const int64_t room = (int64_t)((p.total - p.list_off) / 8), mean = p.n_items / p.nb;
   k.share = fixed ? 1.f : 4096.f / (float)k.R();
+  k.less = !fixed && k.R() > 4096 && a.Z >= 32 ? 3u : 0u;   // (the last third of 750 workgroups in 512 places runs alone: 1.28 M slots 246 -> 238 us, 2 Mi 249 -> 244)
   // (fixed point: one workgroup while that costs less than an accumulator of all of M to clear and to add up)
   const bool many = fixed ? mean > kSeg / 2 * 3 : mean * 4096 > (int64_t)kSeg * k.R() || a.m_size >= (4ll << 20);
   k.owned = fixed && !many;
@@ -783,11 +791,11 @@ __global__ __launch_bounds__(kAccThreads, 4) void k_embed_accum(EmbedArgs a, Acc
 #pragma unroll 1
   for (int r = 0; r < 2; ++r) {
     const uint2* lst = list + (size_t)b * k.cap;
-    uint32_t entries = count, len = (entries + nseg - 1) / nseg, first = seg * len;
+    uint32_t entries = count, len = k.length(entries, nseg), first = seg * len;
     if (r == 1) {
       lst = list + (size_t)k.nb * k.cap;
       entries = spilled;
-      len = (entries + nseg - 1) / nseg;
+      len = k.length(entries, nseg);
       first = seg * len;
     }
     const uint32_t end = min(entries, first + len);
