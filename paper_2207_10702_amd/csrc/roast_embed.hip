@@ -394,7 +394,7 @@ inline BucketPlan bucket_plan(const EmbedArgs& a) {
          room_buckets <= kMaxBuckets;
   if (!p.ok) return p;
   const int64_t most = a.m_size > std::min(a.Z, 32) * (128ll << 10) ? 512 : 256;
-  const int64_t want = std::min<int64_t>(std::max<int64_t>(4096, (a.m_size + most - 1) / most), 10 * 4096);
+  const int64_t want = std::max<int64_t>(4096, (a.m_size + most - 1) / most);   // (at most 32768)
   while (((want - 1) >> p.s_log2) + 1 > 8) ++p.s_log2;
   p.g = (uint32_t)(((want - 1) >> p.s_log2) + 1);
   p.nb = (int)((a.m_size + p.R() - 1) / p.R());
