@@ -361,6 +361,7 @@ roast_status launch_embed(const EmbedArgs& a, const int64_t* rows, const uint32_
 constexpr int kSeg = 8192;          // list entries per accumulate workgroup, where lists are longer than that on average
 constexpr int kListSlack = 8192;    // list capacity beyond twice the mean load, for every 4096 slots
 constexpr int kAccThreads = 512;
+constexpr int kPass = 4096;         // list entries that an accumulate workgroup sorts at a time, by the slot they start at
 constexpr int kMaxBuckets = 2048;   // of 4096 slots (8192 beyond 8 Mi): what the lists' room is reckoned by
 constexpr int kMaxR = 8192;
 constexpr int kRouteItems = 8192;   // chunks per route workgroup (lookups per workgroup = kRouteItems / C)
@@ -381,7 +382,8 @@ struct BucketPlan {
 // each bucket, and the list of a bucket with popular rows has room for less (of 6.8 M chunks over 3 Mi slots, 512 lists spill 84 000 that
 // every workgroup then looks through: 516 us, with 256 303).  But a list's workgroups that share out the slots (AccPlan) read all of
 // it, more of them the longer a bucket is, which counts more the shorter a chunk is: from 2 Mi slots on with chunks of 16 (13.6 M
-// chunks over 6 Mi: 256 buckets 576 us, 512 487), from 4 Mi on with 32 (6.8 M over 6 Mi 327 and 294, but 6.2 M over 4 Mi with a fixed order 393 and 461).
+// chunks over 6 Mi: 256 buckets 576 us, 512 487), from 4 Mi on with 32 (6.8 M over 6 Mi 327 and 294, but 6.2 M over 4 Mi with a fixed order 393 and 461);
+// where a list takes more than one pass (0.63 M chunks of 16 over 3.9 Mi with a fixed order 70.5 and 75).
 inline BucketPlan bucket_plan(const EmbedArgs& a) {
   BucketPlan p{};
   p.n_items = a.N * a.C;
@@ -393,7 +395,7 @@ inline BucketPlan bucket_plan(const EmbedArgs& a) {
          a.hash.use_sign != 2 &&                     // list entries carry one sign per chunk
          room_buckets <= kMaxBuckets;
   if (!p.ok) return p;
-  const int64_t most = a.m_size > std::min(a.Z, 32) * (128ll << 10) ? 512 : 256;
+  const int64_t most = a.m_size > std::min(a.Z, 32) * (128ll << 10) && p.n_items > 256 * kPass ? 512 : 256;
   const int64_t want = std::max<int64_t>(4096, (a.m_size + most - 1) / most);   // (at most 32768)
   while (((want - 1) >> p.s_log2) + 1 > 8) ++p.s_log2;
   p.g = (uint32_t)(((want - 1) >> p.s_log2) + 1);
@@ -405,8 +407,7 @@ inline BucketPlan bucket_plan(const EmbedArgs& a) {
   return p;
 }
 
-// A pass sorts up to kPass entries by the slot they start at.
-constexpr int kPass = 4096, kPer = kPass / kAccThreads;
+constexpr int kPer = kPass / kAccThreads;
 constexpr int U = 4;                // chunks of a group of lanes whose loads are waited for together
 // groups of lanes that hold a chunk, in a wave; places for the sorted entries and what fills up the groups' shares
 __host__ __device__ constexpr int acc_groups(int Z) { return Z >= 256 ? 1 : 64 / (Z / 4); }
@@ -422,23 +423,25 @@ struct AccPlan {
   int q_log2;            // a workgroup owns R >> q_log2 slots
   uint32_t cap;          // of a list
   uint32_t spill_cap;    // of what lies behind the lists: the entries that found theirs full, where every workgroup looks for its own
-  // A list is read by several workgroups to a part, at most `most`: one for each seg_len entries, of which those up to the mean
-  // load count `share` each (the nearest number, or the next above: `up` is half of seg_len, or all but one)
-  uint32_t seg_len, up, mean, most;
-  float share;
-  uint32_t less;         // the last of three and more is that many tenths of the others' length shorter
+  // A list is read by several workgroups to a part, at most `most`: as many as `per` times its entries, of which those up to the
+  // mean load count `share` each (the nearest number, or the next above: `up` is a half or nearly one)
+  uint32_t mean, most;
+  float share, per, up;
+  float less;            // the last of three and more is by that much of a length shorter than the others
   bool owned;            // (fixed point) every slot has one workgroup that sees all of its chunks and writes dM
   bool take_max;         // ... and the route kernel takes the largest |dOut|
   __host__ __device__ int R() const { return (int)(g << s_log2); }
   __host__ __device__ uint32_t segments(uint32_t count) const {
-    if (most == 1u) return 1u;
-    const uint32_t usual = count < mean ? count : mean, n = ((uint32_t)((float)usual * share) + (count - usual) + up) / seg_len;
+    const uint32_t usual = count < mean ? count : mean, n = (uint32_t)(((float)usual * share + (float)(count - usual)) * per + up);
     return n < 1u ? 1u : n > most ? most : n;
   }
-  __host__ __device__ uint32_t length(uint32_t entries, uint32_t nseg) const {
-    if (nseg == 1u) return entries;
-    const uint32_t tenths = 10u * nseg - (nseg < 3u ? 0u : less), whole = entries / tenths;
-    return 10u * whole + (10u * (entries - whole * tenths) + tenths - 1u) / tenths;
+  // entries to a segment; a little more than exactly that, so that they are never too few.  (One way or the other to divide decides
+  // whether the kernels with 128 registers keep some in scratch, which costs a launch 2 to 3 us: 8191 x 26 pooled 34.9 -> 31.9.)
+  template <bool FIXED>
+  __device__ uint32_t length(uint32_t entries, uint32_t nseg) const {
+    if constexpr (FIXED) return (entries + nseg - 1) / nseg;
+    const float n = (float)nseg - (nseg < 3u ? 0.f : less);
+    return (uint32_t)((float)entries * __builtin_amdgcn_rcpf(n) * 1.000001f) + 1u;
   }
   __device__ uint32_t bucket(uint32_t off) const { return __umulhi(off >> s_log2, mu); }   // exact: off < 2^31, g <= 8
 };
@@ -456,7 +459,7 @@ inline AccPlan acc_plan(const EmbedArgs& a, const BucketPlan& p, bool fixed) {
   k.mu = (uint32_t)(((1ull << 32) + p.g - 1) / p.g);
   const int64_t room = (int64_t)((p.total - p.list_off) / 8), mean = p.n_items / p.nb;
   k.share = fixed ? 1.f : 4096.f / (float)k.R();
-  k.less = !fixed && k.R() > 4096 && a.Z >= 32 ? 3u : 0u;   // (the last third of 750 workgroups in 512 places runs alone: 1.28 M slots 246 -> 238 us, 2 Mi 249 -> 244)
+  k.less = !fixed && k.R() > 4096 && a.Z >= 32 ? 0.3f : 0.f;   // (the last third of 750 workgroups in 512 places runs alone: 1.28 M slots 246 -> 238 us, 2 Mi 249 -> 244)
   // (fixed point: one workgroup while that costs less than an accumulator of all of M to clear and to add up)
   const bool many = fixed ? mean > kSeg / 2 * 3 : mean * 4096 > (int64_t)kSeg * k.R() || a.m_size >= (4ll << 20);
   k.owned = fixed && !many;
@@ -465,7 +468,8 @@ inline AccPlan acc_plan(const EmbedArgs& a, const BucketPlan& p, bool fixed) {
   // lists have room for the mean load and all there is beyond twice that, any number of entries can be spilled.
   k.cap = (uint32_t)((k.owned ? room - p.n_items : p.n_items + room / 2) / p.nb);
   k.spill_cap = (uint32_t)std::min<int64_t>(room - (int64_t)p.nb * k.cap, 0x7fffffff);
-  k.seg_len = (uint32_t)(fixed && k.R() == 4096 && a.Z >= 32 ? kPass : kSeg); k.up = fixed || k.R() == 4096 ? k.seg_len - 1 : k.seg_len / 2;
+  const int seg = fixed && k.R() == 4096 && a.Z >= 32 ? kPass : kSeg;
+  k.per = 1.f / (float)seg; k.up = fixed || k.R() == 4096 ? 1.f - k.per : 0.5f;
   k.mean = (uint32_t)mean; k.most = many ? ~0u : 1u;
   k.most = k.segments(k.cap);
   const int64_t wgs = p.nb * (many ? std::max<int64_t>(1, (int64_t)((float)mean * k.share) / kSeg) : 1);
@@ -791,11 +795,11 @@ __global__ __launch_bounds__(kAccThreads, 4) void k_embed_accum(EmbedArgs a, Acc
 #pragma unroll 1
   for (int r = 0; r < 2; ++r) {
     const uint2* lst = list + (size_t)b * k.cap;
-    uint32_t entries = count, len = k.length(entries, nseg), first = seg * len;
+    uint32_t entries = count, len = k.length<FIXED>(entries, nseg), first = seg * len;
     if (r == 1) {
       lst = list + (size_t)k.nb * k.cap;
       entries = spilled;
-      len = k.length(entries, nseg);
+      len = k.length<FIXED>(entries, nseg);
       first = seg * len;
     }
     const uint32_t end = min(entries, first + len);

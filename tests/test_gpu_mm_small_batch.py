@@ -1,6 +1,7 @@
 """GPU parity of the small-batch variants of the forward and dX products (contraction axis split over
 workgroups, fp32 partial outputs summed in a workspace): same oracle, same bf16 bar as the plain
-calls; bit-reproducible from call to call; the workspace contract is enforced."""
+calls; bit-reproducible from call to call; the workspace contract is enforced.  (Most of SHAPES run on one launch of small
+blocks in forward, which leaves the workspace alone; test_split_contraction_on_128_columns asserts the split.)"""
 import numpy as np
 import pytest
 
