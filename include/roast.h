@@ -247,8 +247,8 @@ typedef struct {
 int roast_mm_wide_blocks(const roast_mm_desc* d, roast_dtype dt, int64_t I, int which, int workspace, roast_mm_blocks* out);
 
 /*
- * The same for the kernels of small calls, which make the whole product in one launch (strip and parts are 1): roast_mm_fwd or
- * roast_mm_bwd_dx, fp32 or bf16 (with a copy of M or without one).  Every call is on the wide blocks, on these, or on neither.
+ * The same for the kernels of small calls, which make the whole product in one launch (strip and parts are 1; bf16 with a workspace also in
+ * parts, which a second launch adds up): roast_mm_fwd or roast_mm_bwd_dx, fp32 or bf16 (with a copy of M or without one).  Every call is on the wide blocks, on these, or on neither.
  */
 int roast_mm_direct_blocks(const roast_mm_desc* d, roast_dtype dt, int64_t I, int which, int workspace, roast_mm_blocks* out);
 

@@ -133,7 +133,7 @@ size_t roast_mm_fwd_workspace(const roast_mm_desc* d, roast_dtype dt, int64_t I)
   MMArgs a;
   if (make_mm_args(d, I, &a) != ROAST_OK || !dtype_ok(dt) || I == 0) return 0;
   if (dt == ROAST_F32) return x3_fwd_workspace(a);
-  const int s = mfma_fwd_splits(a);
+  const int s = mm_bf16_parts(0, a);
   return s > 1 ? (size_t)s * (size_t)I * (size_t)a.O * sizeof(float) : 0;
 }
 
@@ -141,7 +141,7 @@ size_t roast_mm_bwd_dx_workspace(const roast_mm_desc* d, roast_dtype dt, int64_t
   MMArgs a;
   if (make_mm_args(d, I, &a) != ROAST_OK || !dtype_ok(dt) || I == 0) return 0;
   if (dt == ROAST_F32) return x3_dx_workspace(a);
-  const int s = mfma_dx_splits(a);
+  const int s = mm_bf16_parts(1, a);
   return s > 1 ? (size_t)s * (size_t)I * (size_t)a.H * sizeof(float) : 0;
 }
 
@@ -176,7 +176,7 @@ int roast_mm_direct_blocks(const roast_mm_desc* d, roast_dtype dt, int64_t I, in
   if (make_mm_args(d, I, &a) != ROAST_OK || I <= 0 || !dtype_ok(dt) || (which != 0 && which != 1)) return 0;
   const MMPlan plan = mm_plan(a, dt == ROAST_F32, which, true, workspace != 0);
   if (plan.route != MMRoute::Direct) return 0;
-  *out = roast_mm_blocks{16 * plan.direct.mi, 16 * plan.direct.nj, 1, 1};
+  *out = roast_mm_blocks{16 * plan.direct.mi, 16 * plan.direct.nj, 1, plan.direct.parts};
   return 1;
 }
 
@@ -203,7 +203,7 @@ roast_status roast_mm_fwd_ws(const roast_mm_desc* d, roast_dtype dt, int64_t I, 
       if (st != ROAST_ERR_UNSUPPORTED) return st;
     }
     if (plan.direct.mi) {
-      st = direct_mm(0, false, plan.direct, a, X, ldx, M, nullptr, Y, ldy, (hipStream_t)stream);
+      st = direct_mm(0, false, plan.direct, a, X, ldx, M, nullptr, Y, ldy, nullptr, (hipStream_t)stream);
       if (st != ROAST_ERR_UNSUPPORTED) return st;
     }
   }
@@ -238,7 +238,7 @@ roast_status roast_mm_bwd_dx_ws(const roast_mm_desc* d, roast_dtype dt, int64_t 
       if (st != ROAST_ERR_UNSUPPORTED) return st;
     }
     if (plan.direct.mi) {
-      st = direct_mm(1, false, plan.direct, a, dY, ldy, M, nullptr, dX, ldx, (hipStream_t)stream);
+      st = direct_mm(1, false, plan.direct, a, dY, ldy, M, nullptr, dX, ldx, nullptr, (hipStream_t)stream);
       if (st != ROAST_ERR_UNSUPPORTED) return st;
     }
   }

@@ -164,10 +164,16 @@ roast_status wide_mm_dM(const MMArgs& a, const WidePlan& plan, const uint16_t* X
 // from the copy of M, or from fp32 M and rounded in registers.  bf16: A and C 16-byte aligned, leading dimensions multiples of 8.
 struct DirectPlan {
   int mi, nj;            // 16 mi x 16 nj output block (0: not the shape for these kernels)
+  int parts;             // of the contraction (more than one: bf16, 64 x 64 blocks, with a workspace)
   double us;             // modelled time
 };
 DirectPlan direct_plan(int which, bool bf16, const MMArgs& a);
-roast_status direct_mm(int which, bool bf16, const DirectPlan& d, const MMArgs& a, const void* A, int64_t lda, const float* M, const void* M_bf16, void* C, int64_t ldc, hipStream_t s);
+DirectPlan ring_plan(int which, const MMArgs& a, int max_parts, double copy_us, double nocopy_us);   // max_parts: 1 where no workspace is given
+roast_status direct_mm(int which, bool bf16, const DirectPlan& d, const MMArgs& a, const void* A, int64_t lda, const float* M, const void* M_bf16, void* C, int64_t ldc, float* G, hipStream_t s);
+
+// ---- the 64 x 64 blocks of those for calls with a copy of M (roast_mm_ring.hip): the same sums, operands through LDS.  A and C as above.
+bool ring_ok(int which, const MMArgs& a);
+roast_status ring_mm(int which, int parts, const MMArgs& a, const void* A, int64_t lda, const void* M_bf16, void* C, int64_t ldc, float* G, hipStream_t s);
 
 // ---- which kernels a forward (which = 0) or dX (1) call takes where its operands are aligned for them: asked by the calls and by
 // the diagnostics alike (roast_mm_mfma.hip)
@@ -179,6 +185,7 @@ struct MMPlan {
 };
 // copy: a copy of M is given (fp32: planes are made where none is).  workspace: likewise, of the bytes that the query names
 MMPlan mm_plan(const MMArgs& a, bool f32, int which, bool copy, bool workspace);
+int mm_bf16_parts(int which, const MMArgs& a);   // fp32 partial outputs that a bf16 call's workspace has room for (1: none)
 WidePlan mm_dm_plan(const MMArgs& a, bool f32);   // the same of the gradient of M with atomic adds
 
 // ---- lookup kernels (roast_embed.hip)

@@ -45,7 +45,9 @@ struct DirectArgs {
   void* C;
   int64_t ldc;
   uint32_t mu1, mu2;                     // 2^32 / Z1, 2^32 / Z2, rounded up
-  int nbx;                               // column blocks
+  int nbx, nby;                          // column, row blocks
+  int parts;                             // of the contraction (bf16), whose partial outputs go to G, [part][rows][columns]
+  float* G;
 };
 
 template <typename V, typename T>
@@ -74,12 +76,15 @@ __global__ __launch_bounds__(64 * kWaves, MI * NJ > 8 ? 2 : 4) void k_mm_direct(
   const int K = DX ? (int)a.O : (int)a.H, N = DX ? (int)a.H : (int)a.O, I = (int)a.I;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, g = lane >> 4;
-  const int bx = (int)blockIdx.x % p.nbx, by = (int)blockIdx.x / p.nbx;
+  const int plane = (int)(blockIdx.x / (unsigned)p.nbx), bx = (int)blockIdx.x - plane * p.nbx;
+  const int bz = p.parts > 1 ? plane / p.nby : 0, by = plane - bz * p.nby;
   const int m0 = by * BM, n0 = bx * BN;
-  const int units = (K + KU - 1) / KU;
+  // (parts: of a contraction whose length is a multiple of 64, in whole pairs of bf16 units)
+  const int u0 = p.parts > 1 ? 2 * (K / 64 * bz / p.parts) : 0;
+  const int units = p.parts > 1 ? 2 * (K / 64 * (bz + 1) / p.parts) - u0 : (K + KU - 1) / KU;
   // a wave's share of them is contiguous: rows of A whose length is a power of two lie in the same few channels of the L2, and
   // waves that read next to one another would all ask those
-  const int first = units * wave / kWaves, end = units * (wave + 1) / kWaves;
+  const int first = u0 + units * wave / kWaves, end = u0 + units * (wave + 1) / kWaves;
   // Addresses are a uniform base and a 32-bit offset in bytes: with 64-bit ones per lane the address arithmetic took
   // longer than the products.  Rows and columns beyond the problem repeat the last ones, they are not stored.
   const T* a_base = A + (int64_t)m0 * p.lda;
@@ -89,6 +94,7 @@ __global__ __launch_bounds__(64 * kWaves, MI * NJ > 8 ? 2 : 4) void k_mm_direct(
   // table: row = tile along the contraction, column = tile along the block's columns
   const int zk = DX ? a.Z2 : a.Z1, zn = DX ? a.Z1 : a.Z2;
   const uint32_t muk = DX ? p.mu2 : p.mu1, mun = DX ? p.mu1 : p.mu2;
+  const int t0 = quot(u0 * KU, muk);     // first tile along the contraction
   const int c0 = quot(n0, mun), TN = quot(min(n0 + BN, N) - 1, mun) - c0 + 1;
   constexpr int NC = DX ? NJ : 1;        // columns (FWD: groups of NJ) a lane looks up
   int tc[NC];                            // its table column,
@@ -116,7 +122,7 @@ __global__ __launch_bounds__(64 * kWaves, MI * NJ > 8 ? 2 : 4) void k_mm_direct(
     const int k = min(KU * kk + KL * g, K - KL), t = quot(k, muk), kin = k - t * zk;
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-      const int64_t e = s_tab[t * TN + tc[j]];
+      const int64_t e = s_tab[(t - t0) * TN + tc[j]];
       u.flip[j] = (uint32_t)(e >> 32) & 0x80000000u;
       using W = typename std::conditional<SH, uint16_t, float>::type;
       const W* base;
@@ -138,9 +144,9 @@ __global__ __launch_bounds__(64 * kWaves, MI * NJ > 8 ? 2 : 4) void k_mm_direct(
   };
   Unit nxt;
   if (first < end) load_x(nxt, first);
-  const int rows_k = quot(K - 1, muk) + 1;
+  const int rows_k = quot(min((u0 + units) * KU, K) - 1, muk) + 1 - t0;
   for (int e = tid; e < rows_k * TN; e += 64 * kWaves) {
-    const int ek = e / TN, en = c0 + e - ek * TN;
+    const int row = e / TN, ek = t0 + row, en = c0 + e - row * TN;
     bool neg;
     const int64_t off = tile_place(a.hash, p.th, a.layer, (uint32_t)(DX ? en : ek), (uint32_t)(DX ? ek : en), &neg);
     // (an odd offset is read from the second copy, where it is dword-aligned: everything added to it is even)
@@ -232,6 +238,14 @@ __global__ __launch_bounds__(64 * kWaves, MI * NJ > 8 ? 2 : 4) void k_mm_direct(
       for (int w = 1; w < kWaves; ++w)
 #pragma unroll
         for (int v = 0; v < V / 4; ++v) sum[v] += *reinterpret_cast<const floatx4*>(s_part + w * (16 * RI * BN) + row * BN + c + 4 * v);
+      if constexpr (BF && MI * NJ == 16) {
+        if (p.parts > 1) {
+          float* part_to = p.G + ((int64_t)bz * I + out_row) * N + n0 + c;
+#pragma unroll
+          for (int v = 0; v < 2; ++v) *reinterpret_cast<floatx4*>(part_to + 4 * v) = a.lambda * sum[v];
+          continue;
+        }
+      }
       T* to = static_cast<T*>(p.C) + (int64_t)out_row * p.ldc + n0 + c;
       if constexpr (BF) {
         uint4v out;
@@ -278,7 +292,7 @@ constexpr Variant kVariants[] = {{false, 1, 1, 2.8, {3.15, 3.45}, {2.7, 3.1}},
 
 template <typename T, bool SH, bool DX, int MI, int NJ>
 roast_status launch_one(const DirectArgs& p, hipStream_t s) {
-  const int64_t blocks = cdiv(p.a.I, 16 * MI) * p.nbx;   // (direct_plan: at most kMaxBlocks)
+  const int64_t blocks = (int64_t)p.nby * p.nbx * p.parts;   // (direct_plan: at most kMaxBlocks)
   constexpr size_t lds = std::max<size_t>((size_t)kTable * 8, (size_t)kWaves * std::min(16 * MI * 16 * NJ, 2048) * 4);
   static_assert(lds <= 64 * 1024, "LDS without an attribute");
   hipLaunchKernelGGL((k_mm_direct<T, SH, DX, MI, NJ>), dim3((unsigned)blocks), dim3(64 * kWaves), lds, s, p);
@@ -320,11 +334,11 @@ roast_status launch_variant(bool bf16, int mi, int nj, const DirectArgs& p, hipS
 // or columns that leave those idle.  Of 300 calls of 16 .. 2048 rows the worst loses 3 % by it.  64 x 256 x 256 17.9 -> 11.0 us of which the GPU is busy half,
 // 885 x 576 x 384 26.5 -> 11.4, 512 x 1024 x 1024 32 -> 17, 46 x 3136 x 1728 31.6 -> 20.9, 39 x 7648 x 2496 over 1 Mi slots 48 -> 34, but over 4 Mi it stays (49, here 52 to 60), as
 // does 2048 x 1024 x 1024.  Without one, against the generic kernel: 300 x 1096 x 520 162 -> 12.9.
-// bf16, by the same margin on what the wide blocks are modelled to take: 512 x 2048 x 2048 23.8 -> 17.2 (two launches), 206 x 1664 x 1152 17.0 -> 10.5;
-// 1024 x 2048 x 2048 stays, 27 and 29; without a workspace 35 x 4352 x 5504 43.7 -> 19.6.  A 64 x 64 block of bf16 takes 167 ns a unit of 32, 20 bytes a clock and CU:
+// bf16, by the same margin on what the wide blocks are modelled to take: 206 x 1664 x 1152 17.0 -> 10.5, 512 x 2048 x 2048 without a copy of M 23.8 -> 17.2 (two
+// launches; with one see roast_mm_ring.hip); without a workspace 35 x 4352 x 5504 43.7 -> 19.6.  A 64 x 64 block of bf16 takes 167 ns a unit of 32, 20 bytes a clock and CU:
 // neither more units in flight nor fewer address instructions, whole lines of A or other channels of the L2 change that.
 DirectPlan direct_plan(int which, bool bf16, const MMArgs& a) {
-  DirectPlan best{0, 0, 1e300};
+  DirectPlan best{0, 0, 1, 1e300};
   const int64_t K = which ? a.O : a.H, N = which ? a.H : a.O, l2 = 1 << 20;
   for (const Variant& v : kVariants) {
     if (v.bf16 != bf16 || v.alone[which] == 0.0 || !direct_ok(a, bf16, which == 1, 16 * v.nj)) continue;
@@ -338,21 +352,51 @@ DirectPlan direct_plan(int which, bool bf16, const MMArgs& a) {
       const double bytes = (double)cdiv(a.I, 16 * v.mi) * (double)K * (double)N * 4.0 * (1.0 - (double)l2 / (double)a.m_size);
       us = std::max(us, v.fixed + bytes / (which || v.nj == 4 || a.Z2 <= 16 * v.nj ? 6.5e6 : 3.5e6));
     }
-    if (us < best.us) best = {v.mi, v.nj, us};
+    if (us < best.us) best = {v.mi, v.nj, 1, us};
+  }
+  return best;
+}
+
+// bf16 64 x 64 blocks in `parts` of the contraction, in microseconds: with a copy of M (roast_mm_ring.hip), a launch; a round of up to 256
+// workgroups, whose start and end take 4 and a contraction index 2 ns, 3 where every CU has one, a quarter of the 2 more where a tile is wider than
+// the block (its rows are pieces of 128 bytes at any multiple of four: two lines each); weights of an M beyond an XCD's L2, at 6.5 TB/s; the launch that
+// adds up the parts.  Fitted to 1100 launches of 16 to 2048 rows, most within 12 %.  Without a copy (the kernel above) an index takes 5.2 ns, in dX 9.7.
+static double ring_us(int which, int parts, const MMArgs& a, bool copy) {
+  const double K = (double)(which ? a.O : a.H), N = (double)(which ? a.H : a.O), part = K / parts;
+  const int64_t wgs = cdiv(a.I, 64) * ((which ? a.H : a.O) / 64) * parts, rest = wgs % 256;
+  const double finish = parts == 1 ? 0.0 : 2.5 + 0.12 * parts + (double)parts * (double)a.I * N * 4.0 / 1.95e6;
+  if (!copy) return 5.0 + (double)cdiv(wgs, 256) * part * (which ? 9.7e-3 : 5.2e-3) + finish;
+  const double index = 2.0e-3 * (a.Z2 >= 128 ? 1.25 : 1.0);
+  double us = 1.3 + (double)(wgs / 256) * (4.05 + part * (index + 1.0e-3));
+  if (rest) us += 4.05 + part * (index + 1.0e-3 * (double)rest / 256.0);
+  if (a.m_size > (1 << 20)) us = std::max(us, 5.35 + 2.0 * K * N / 6.5e6);
+  return us + finish;
+}
+
+// The best number of parts of those blocks for a call that takes copy_us, or nocopy_us without a copy of M, on other kernels: where a call with a copy is 8 % faster
+// for it and one without, which has to give the same sums, no more than 10 % slower.  (mi == 0: none.)
+DirectPlan ring_plan(int which, const MMArgs& a, int max_parts, double copy_us, double nocopy_us) {
+  DirectPlan best{0, 0, 1, copy_us / 1.08};
+  if (a.I > 2048 || !ring_ok(which, a) || !direct_ok(a, true, which == 1, 64)) return best;
+  const int64_t K = which ? a.O : a.H, blocks = cdiv(a.I, 64) * ((which ? a.H : a.O) / 64);
+  for (int parts = 1; parts <= max_parts && (parts == 1 || (K >= 128 * parts && blocks * parts <= 512)); ++parts) {
+    const double us = ring_us(which, parts, a, true);
+    if (us < best.us && ring_us(which, parts, a, false) <= 1.1 * nocopy_us) best = {4, 4, parts, us};
   }
   return best;
 }
 
 // which: 0 forward, 1 dX.  bf16: A and C 16-byte aligned, leading dimensions multiples of 8
 roast_status direct_mm(int which, bool bf16, const DirectPlan& d, const MMArgs& a, const void* A, int64_t lda, const float* M, const void* M_bf16, void* C, int64_t ldc,
-                       hipStream_t s) {
+                       float* G, hipStream_t s) {
   if (lda >= (1ll << 23)) return ROAST_ERR_UNSUPPORTED;       // (32-bit byte offsets of 64 rows)
+  if (bf16 && M_bf16 && d.mi == 4 && d.nj == 4 && ring_ok(which, a)) return ring_mm(which, d.parts, a, A, lda, M_bf16, C, ldc, G, s);
   DirectArgs p{};
   p.a = a; p.th = make_tile_hash(a.hash, a.layer, a.nTx, a.nTy);
   p.A = A; p.lda = lda; p.M = M; p.Mb = (const uint16_t*)M_bf16; p.mb_stride = shadow_stride(a.m_size); p.C = C; p.ldc = ldc;
   auto mu = [](int64_t z) { return (uint32_t)(((1ull << 32) + (uint64_t)z - 1) / (uint64_t)z); };
   p.mu1 = mu(a.Z1); p.mu2 = mu(a.Z2);
-  p.nbx = (int)cdiv(which ? a.H : a.O, 16 * d.nj);
+  p.nbx = (int)cdiv(which ? a.H : a.O, 16 * d.nj); p.nby = (int)cdiv(a.I, 16 * d.mi); p.parts = d.parts; p.G = G;
   return which ? launch_variant<true>(bf16, d.mi, d.nj, p, s) : launch_variant<false>(bf16, d.mi, d.nj, p, s);
 }
 

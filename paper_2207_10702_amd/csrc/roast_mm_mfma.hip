@@ -1272,15 +1272,18 @@ void split_setup(KernArgs* p, dim3* grid, int64_t K, int splits, float* ws) {
   grid->z = (unsigned)cdiv(K, p->rows_per_split);
 }
 
+roast_status split_finish(const float* G, int parts, int64_t rows, int64_t cols, uint16_t* C, int64_t ldc, hipStream_t s) {
+  const int64_t blocks = cdiv(rows * (cols / 8), 256);
+  if (blocks > 0x7fffffffll) return ROAST_ERR_UNSUPPORTED;
+  hipLaunchKernelGGL(k_split_finish, dim3((unsigned)blocks), dim3(256), 0, s, G, parts, rows, cols, C, ldc);
+  return hip_status(hipGetLastError());
+}
 roast_status split_finish(const KernArgs& p, unsigned parts, int64_t rows, int64_t cols, hipStream_t s) {
   if (p.G == nullptr) return ROAST_OK;
-  const int64_t blocks = cdiv(rows * (cols / (p.C32 ? 4 : 8)), 256);
+  if (!p.C32) return split_finish(p.G, (int)parts, rows, cols, p.C, p.ldc, s);
+  const int64_t blocks = cdiv(rows * (cols / 4), 256);
   if (blocks > 0x7fffffffll) return ROAST_ERR_UNSUPPORTED;
-  if (p.C32)
-    hipLaunchKernelGGL(k_split_finish_f32, dim3((unsigned)blocks), dim3(256), 0, s, p.G, (int)parts, rows, cols, p.C32,
-                       p.ldc);
-  else
-    hipLaunchKernelGGL(k_split_finish, dim3((unsigned)blocks), dim3(256), 0, s, p.G, (int)parts, rows, cols, p.C, p.ldc);
+  hipLaunchKernelGGL(k_split_finish_f32, dim3((unsigned)blocks), dim3(256), 0, s, p.G, (int)parts, rows, cols, p.C32, p.ldc);
   return hip_status(hipGetLastError());
 }
 
@@ -1367,15 +1370,20 @@ static WidePlan dx_plan(const MMArgs& a, int max_parts) {
 // Modelled time of the kernels below with a copy of M (what a call without one costs more does not count, for the same sums).  Shapes that the
 // wide blocks do not take: 256 x 128 blocks of 0.95 us a step, or where dx_plan leaves it to 256 x 96 blocks, those: 0.61 a step and 6.9 (dX over an M of
 // more than 4 Mi slots, 320 x 1888 x 576 11.9 -> 7.7 us here, 231 x 4656 x 1024 stays, 16.9 and 21.7).
-static double bf16_us(int which, const MMArgs& a, bool ws) {
+static double columns128_us(int which, const MMArgs& a, bool ws) {
   const int64_t K = which ? a.O : a.H, N = which ? a.H : a.O;
+  const int parts = !ws ? 1 : which ? mfma_dx_splits(a) : mfma_fwd_splits(a);
+  return (double)cdiv(cdiv(N, kBN) * cdiv(a.I, kBM) * parts, 256) * (0.95 * (double)cdiv(cdiv(K, parts), BK) + 4.0) +
+         (parts > 1 ? 4.0 + (double)parts * (double)a.I * (double)N * 4.0 / 3.0e6 : 0.0);
+}
+
+static double bf16_us(int which, const MMArgs& a, bool ws) {
+  const int64_t K = which ? a.O : a.H;
   const int max_parts = ws ? kWideParts : 1;
   const WidePlan w = which ? dx_plan(a, max_parts) : wide_fwd_plan(a, max_parts, false);
   if (w.bm) return w.us;
   if (which && wide_dx_plan(a, max_parts, false).bm) return 0.61 * (double)(K / BK) + 6.9;
-  const int parts = !ws ? 1 : which ? mfma_dx_splits(a) : mfma_fwd_splits(a);
-  return (double)cdiv(cdiv(N, kBN) * cdiv(a.I, kBM) * parts, 256) * (0.95 * (double)cdiv(cdiv(K, parts), BK) + 4.0) +
-         (parts > 1 ? 4.0 + (double)parts * (double)a.I * (double)N * 4.0 / 3.0e6 : 0.0);
+  return columns128_us(which, a, ws);
 }
 
 roast_status mfma_mm_fwd(const MMArgs& a, const void* X, int64_t ldx, const float* M, const void* M_bf16, void* Y,
@@ -1385,8 +1393,8 @@ roast_status mfma_mm_fwd(const MMArgs& a, const void* X, int64_t ldx, const floa
     return ROAST_ERR_UNSUPPORTED;
   const MMPlan plan = mm_plan(a, false, 0, M_bf16 != nullptr, ws != nullptr);
   if (plan.route == MMRoute::Direct) {
-    const roast_status st = direct_mm(0, true, plan.direct, a, X, ldx, M, M_bf16, Y, ldy, s);
-    if (st != ROAST_ERR_UNSUPPORTED) return st;
+    const roast_status st = direct_mm(0, true, plan.direct, a, X, ldx, M, M_bf16, Y, ldy, ws, s);
+    if (st != ROAST_ERR_UNSUPPORTED) return st != ROAST_OK || plan.direct.parts == 1 ? st : split_finish(ws, plan.direct.parts, a.I, a.O, (uint16_t*)Y, ldy, s);
   }
   const WidePlan& wide = plan.wide;
   constexpr int BM = kBM, BN = kBN;
@@ -1432,8 +1440,8 @@ roast_status mfma_mm_bwd_dx(const MMArgs& a, const void* dY, int64_t ldy, const 
     return ROAST_ERR_UNSUPPORTED;
   const MMPlan plan = mm_plan(a, false, 1, M_bf16 != nullptr, ws != nullptr);
   if (plan.route == MMRoute::Direct) {
-    const roast_status st = direct_mm(1, true, plan.direct, a, dY, ldy, M, M_bf16, dX, ldx, s);
-    if (st != ROAST_ERR_UNSUPPORTED) return st;
+    const roast_status st = direct_mm(1, true, plan.direct, a, dY, ldy, M, M_bf16, dX, ldx, ws, s);
+    if (st != ROAST_ERR_UNSUPPORTED) return st != ROAST_OK || plan.direct.parts == 1 ? st : split_finish(ws, plan.direct.parts, a.I, a.H, (uint16_t*)dX, ldx, s);
   }
   const WidePlan& wide = plan.wide;
   constexpr int BM = kBM, BN = kBN;
@@ -1680,9 +1688,22 @@ MMPlan mm_plan(const MMArgs& a, bool f32, int which, bool copy, bool workspace) 
     if (blocks && copy) p.wide = which == 0 ? wide_fwd_plan(a, workspace ? kWideParts : 1, false) : dx_plan(a, workspace ? kWideParts : 1);
   }
   // (8 %: what the models are good for)
-  const bool direct = p.direct.mi && (!blocks ? f32 : 1.08 * p.direct.us < (f32 ? x3_us(which, a) : bf16_us(which, a, workspace)));
+  const double larger = !blocks ? 0.0 : f32 ? x3_us(which, a) : bf16_us(which, a, workspace);
+  bool direct = p.direct.mi && (!blocks ? f32 : 1.08 * p.direct.us < larger);
+  if (!f32 && blocks) {
+    const DirectPlan ring = ring_plan(which, a, workspace ? kWideParts : 1, direct ? p.direct.us : larger, direct ? p.direct.us : columns128_us(which, a, workspace));
+    if (ring.mi) {
+      p.direct = ring;
+      direct = true;
+    }
+  }
   p.route = direct ? MMRoute::Direct : !blocks ? MMRoute::Generic : p.wide.bm ? MMRoute::Wide : MMRoute::Columns128;
   return p;
+}
+
+int mm_bf16_parts(int which, const MMArgs& a) {
+  const MMPlan p = mm_plan(a, false, which, true, true);
+  return std::max(which ? mfma_dx_splits(a) : mfma_fwd_splits(a), p.route == MMRoute::Direct ? p.direct.parts : 1);
 }
 
 WidePlan mm_dm_plan(const MMArgs& a, bool f32) {
