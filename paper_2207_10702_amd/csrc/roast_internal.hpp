@@ -175,6 +175,14 @@ roast_status direct_mm(int which, bool bf16, const DirectPlan& d, const MMArgs& 
 bool ring_ok(int which, const MMArgs& a);
 roast_status ring_mm(int which, int parts, const MMArgs& a, const void* A, int64_t lda, const void* M_bf16, void* C, int64_t ldc, float* G, hipStream_t s);
 
+// ---- gradient of M of few bf16 tokens, by windows of slots (roast_mm_window.hip); atomic mode.  X, dY 16-byte aligned, leading dimensions multiples of 8.
+struct WindowPlan {
+  int window;            // slots of a window (0: not the shape for this kernel)
+  int shares;            // workgroups to a window
+};
+WindowPlan window_plan(const MMArgs& a, double wide_us);   // wide_us: modelled time of the blocks that the call takes else
+roast_status window_dM(const MMArgs& a, const WindowPlan& w, const void* X, int64_t ldx, const void* dY, int64_t ldy, float* dM, hipStream_t s);
+
 // ---- which kernels a forward (which = 0) or dX (1) call takes where its operands are aligned for them: asked by the calls and by
 // the diagnostics alike (roast_mm_mfma.hip)
 enum class MMRoute { Generic, Direct, Wide, Columns128 };   // (Columns128: the 128-column kernels of that file, with their 96-column and element-wise variants)

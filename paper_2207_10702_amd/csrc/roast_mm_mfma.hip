@@ -1505,6 +1505,13 @@ roast_status mfma_mm_bwd_dM(const MMArgs& a, const void* X, int64_t ldx, const v
     return ROAST_ERR_UNSUPPORTED;
   if (Gws != nullptr && (splits < 1 || splits > 65535)) return ROAST_ERR_UNSUPPORTED;
   const WidePlan wide = wide_dm_plan(a, Gws ? splits : 0, false);
+  if (Gws == nullptr && wide.bm) {
+    const WindowPlan window = window_plan(a, wide.us);
+    if (window.window) {
+      const roast_status st = window_dM(a, window, X, ldx, dY, ldy, dM, s);
+      if (st != ROAST_ERR_UNSUPPORTED) return st;
+    }
+  }
   if (wide.bm) {
     int begin[kWideParts + 1] = {};
     if (Gws == nullptr) uneven_parts(a.I, wide.parts, begin);
@@ -1708,7 +1715,8 @@ int mm_bf16_parts(int which, const MMArgs& a) {
 
 WidePlan mm_dm_plan(const MMArgs& a, bool f32) {
   if (f32 ? !x3_dm_ok(a) : a.H < kBM / 32 || a.O < kBN / 32) return {};
-  return wide_dm_plan(a, 0, f32);
+  const WidePlan wide = wide_dm_plan(a, 0, f32);
+  return !f32 && wide.bm && window_plan(a, wide.us).window ? WidePlan{} : wide;
 }
 
 }  // namespace roast
