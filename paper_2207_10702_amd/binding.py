@@ -1,7 +1,8 @@
 """Python names for the C-ABI of libroast_hip.so (see include/roast.h).
 
 Argument marshalling only: every function checks dtypes / contiguity, passes raw device pointers
-and the current HIP stream to the library, and raises RoastError on a non-zero status.  There is no
+and the current HIP stream to the library, and raises RoastError on a non-zero status.  The calls that launch kernels
+do so in csrc/roast_call.cpp where their arguments are plain tensors.  There is no
 fallback: if the library has not been built, loading fails.
 """
 import ctypes as C
@@ -13,6 +14,7 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libroast_hip.so")
+CALL_PATH = os.path.join(_HERE, "_roast_call.so")
 
 ROAST_F32, ROAST_BF16 = 0, 1
 ROAST_OK, ROAST_ERR_ARG, ROAST_ERR_SHAPE, ROAST_ERR_RANGE, ROAST_ERR_WORKSPACE, ROAST_ERR_HIP, ROAST_ERR_UNSUPPORTED = range(7)
@@ -58,11 +60,33 @@ class RoastOptimDesc(C.Structure):
 ROAST_OPT_SGD, ROAST_OPT_ADAGRAD, ROAST_OPT_ADAM = 0, 1, 2
 
 _lib = None
+_call = None              # the module of csrc/roast_call.cpp, once the library is loaded
+
+
+def _connect(lib):
+    """The compiled form of the calls below, on the library that has been loaded; None without one (torch is not there)."""
+    try:
+        import torch
+    except ImportError:
+        return None
+    if not hasattr(torch._C, "_cuda_getCurrentRawStream"):
+        return None
+    import importlib.util
+    if not os.path.exists(CALL_PATH):
+        from . import build as _build
+        _build._compile_call()
+    spec = importlib.util.spec_from_file_location("_roast_call", CALL_PATH)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    names = ("roast_mm_fwd_ws", "roast_mm_bwd_dx_ws", "roast_mm_bwd_dM", "roast_embed_fwd", "roast_embed_bwd", "roast_embed_bag_fwd",
+             "roast_embed_bag_bwd", "roast_optim_step", "roast_m_shadow_bytes", "roast_m_planes_bytes", "roast_m_shadow_bf16", "roast_m_planes_bf16")
+    module.connect(torch._C, *(C.cast(getattr(lib, n), C.c_void_p).value for n in names))
+    return module
 
 
 def load() -> C.CDLL:
     """Load the in-tree library (building it first only if it has never been built)."""
-    global _lib
+    global _lib, _call
     if _lib is not None:
         return _lib
     path = os.environ.get("ROAST_HIP_LIB", LIB_PATH)     # override: point at another build of the same library
@@ -121,6 +145,7 @@ def load() -> C.CDLL:
                         "roast_embed_bwd_workspace", "roast_mm_fwd_workspace", "roast_mm_bwd_dx_workspace",
                         "roast_embed_bag_bwd_workspace", "roast_mm_bwd_dM_workspace_f32", "roast_m_planes_bytes"):
             f.restype = i32
+    _call = _connect(lib)
     _lib = lib
     return lib
 
@@ -223,6 +248,11 @@ def roast_m_shadow_bytes(m_size: int) -> int:
 def roast_m_shadow_bf16(M, shadow=None, stream=None):
     """bf16 shadow of M for the bf16 ROAST-MM kernels (make it once per update of M); a bfloat16
     tensor of roast_m_shadow_bytes(|M|) / 2 elements whose layout is private to the library."""
+    if shadow is not None:
+        st = _fast("m_shadow_bf16", stream, M, shadow)
+        if st is not None:
+            _check(st, "roast_m_shadow_bf16")
+            return shadow
     torch = _torch()
     n = roast_m_shadow_bytes(M.numel()) // 2
     if shadow is None:
@@ -241,6 +271,11 @@ def roast_m_planes_bytes(m_size: int) -> int:
 def roast_m_planes_bf16(M, planes=None, stream=None):
     """Three bfloat16 planes of M for fp32 roast_mm_fwd / roast_mm_bwd_dx calls with a workspace
     (pass as M_bf16; make once per update of M)."""
+    if planes is not None:
+        st = _fast("m_planes_bf16", stream, M, planes)
+        if st is not None:
+            _check(st, "roast_m_planes_bf16")
+            return planes
     torch = _torch()
     n = roast_m_planes_bytes(M.numel()) // 2
     if planes is None:
@@ -266,6 +301,16 @@ def _shadow_ptr(M, M_bf16, f32: bool = False) -> int:
         raise ValueError("M_bf16 must be the tensor made by roast_m_shadow_bf16 (bf16 calls) or "
                          "roast_m_planes_bf16 (fp32 calls) for this M")
     return _vec(M_bf16, torch.bfloat16, "M_bf16")
+
+
+def _fast(name: str, stream, *args):
+    """The status of a call in its compiled form, which makes the same checks; None where it did nothing, because a check failed or for an
+    argument that is no plain tensor: the Python form then does it, or says what is wrong.  (Explicit streams take that too.)"""
+    if stream is not None:
+        return None
+    if _lib is None:
+        load()
+    return getattr(_call, name)(*args) if _call is not None else None
 
 
 def _ws(ws):
@@ -311,6 +356,11 @@ def roast_mm_direct_blocks(desc: RoastMMDesc, dtype, I: int, which: int, workspa
 def roast_mm_fwd(desc: RoastMMDesc, X, M, Y=None, stream=None, M_bf16=None, ws=None):
     """`ws` (optional): uint8 device tensor of at least roast_mm_fwd_workspace(...) bytes; the call then
     goes through roast_mm_fwd_ws."""
+    if Y is not None:
+        st = _fast("mm_fwd", stream, desc, X, M, Y, M_bf16, ws)
+        if st is not None:
+            _check(st, "roast_mm_fwd" if ws is None else "roast_mm_fwd_ws")
+            return Y
     torch = _torch()
     I = X.shape[0]
     if X.shape[1] != desc.H:
@@ -332,6 +382,11 @@ def roast_mm_fwd(desc: RoastMMDesc, X, M, Y=None, stream=None, M_bf16=None, ws=N
 
 
 def roast_mm_bwd_dx(desc: RoastMMDesc, dY, M, dX=None, stream=None, M_bf16=None, ws=None):
+    if dX is not None:
+        st = _fast("mm_bwd_dx", stream, desc, dY, M, dX, M_bf16, ws)
+        if st is not None:
+            _check(st, "roast_mm_bwd_dx" if ws is None else "roast_mm_bwd_dx_ws")
+            return dX
     torch = _torch()
     I = dY.shape[0]
     if dY.shape[1] != desc.O:
@@ -364,6 +419,10 @@ def roast_mm_bwd_dM_workspace_f32(desc: RoastMMDesc, I: int) -> int:
 def roast_mm_bwd_dM(desc: RoastMMDesc, X, dY, dM, mode: int = ROAST_REDUCE_ATOMIC, ws=None, stream=None):
     """dM += gradient of this layer.  `ws` is a uint8 device tensor of at least
     roast_mm_bwd_dM_workspace(...) bytes (only the deterministic mode needs one)."""
+    st = _fast("mm_bwd_dM", stream, desc, X, dY, dM, mode, ws)
+    if st is not None:
+        _check(st, "roast_mm_bwd_dM")
+        return dM
     torch = _torch()
     I = X.shape[0]
     if X.shape[1] != desc.H or tuple(dY.shape) != (I, desc.O) or X.dtype != dY.dtype:
@@ -380,6 +439,11 @@ def roast_mm_bwd_dM(desc: RoastMMDesc, X, dY, dM, mode: int = ROAST_REDUCE_ATOMI
 
 
 def roast_embed_fwd(desc: RoastEmbedDesc, rows, table_ids, M, out=None, stream=None):
+    if out is not None:
+        st = _fast("embed_fwd", stream, desc, rows, table_ids, M, out)
+        if st is not None:
+            _check(st, "roast_embed_fwd")
+            return out
     torch = _torch()
     N = rows.numel()
     if out is None:
@@ -398,6 +462,10 @@ def roast_embed_bwd_workspace(desc: RoastEmbedDesc, N: int, mode: int = ROAST_RE
 
 def roast_embed_bwd(desc: RoastEmbedDesc, rows, table_ids, dOut, dM, mode: int = ROAST_REDUCE_ATOMIC, ws=None,
                     stream=None):
+    st = _fast("embed_bwd", stream, desc, rows, table_ids, dOut, dM, mode, ws)
+    if st is not None:
+        _check(st, "roast_embed_bwd")
+        return dM
     torch = _torch()
     N = rows.numel()
     if tuple(dOut.shape) != (N, desc.D) or dM.numel() != desc.m_size:
@@ -426,6 +494,11 @@ def roast_embed_bwd_noalloc(desc: RoastEmbedDesc, rows, table_ids, dOut, dM, mod
 
 def roast_embed_bag_fwd(desc: RoastEmbedDesc, rows, table_ids, bag_offsets, M, out=None, stream=None):
     """Pooled lookup: out[b] = sum of the rows of the lookups [bag_offsets[b], bag_offsets[b+1])."""
+    if out is not None:
+        st = _fast("embed_bag_fwd", stream, desc, rows, table_ids, bag_offsets, M, out)
+        if st is not None:
+            _check(st, "roast_embed_bag_fwd")
+            return out
     torch = _torch()
     N, B = rows.numel(), bag_offsets.numel() - 1
     if B < 0:
@@ -447,6 +520,10 @@ def roast_embed_bag_bwd_workspace(desc: RoastEmbedDesc, N: int, B: int, mode: in
 
 def roast_embed_bag_bwd(desc: RoastEmbedDesc, rows, table_ids, bag_offsets, dOut, dM, mode: int = ROAST_REDUCE_ATOMIC,
                         ws=None, stream=None):
+    st = _fast("embed_bag_bwd", stream, desc, rows, table_ids, bag_offsets, dOut, dM, mode, ws)
+    if st is not None:
+        _check(st, "roast_embed_bag_bwd")
+        return dM
     torch = _torch()
     N, B = rows.numel(), bag_offsets.numel() - 1
     if B < 0 or tuple(dOut.shape) != (B, desc.D) or dM.numel() != desc.m_size:
@@ -467,6 +544,10 @@ def optim_desc(kind: int, lr: float, weight_decay: float = 0.0, beta1: float = 0
 
 def roast_optim_step(desc: RoastOptimDesc, M, dM, state1=None, state2=None, M_bf16=None, stream=None):
     """One optimizer step on M (in place); clears dM when desc.zero_grad; refreshes M_bf16 when given."""
+    st = _fast("optim_step", stream, desc, M, dM, state1, state2, M_bf16)
+    if st is not None:
+        _check(st, "roast_optim_step")
+        return M
     torch = _torch()
     n = M.numel()
     if dM.numel() != n:

@@ -129,20 +129,23 @@ roast_status roast_m_shadow_bf16(const float* M, int64_t m_size, void* shadow, v
   return shadow_bf16_launch(M, m_size, shadow, (hipStream_t)stream);
 }
 
+// bytes of workspace of a forward (which = 0) or dX (1) call
+static size_t product_workspace(int which, roast_dtype dt, const MMArgs& a) {
+  if (dt == ROAST_F32) return which ? x3_dx_workspace(a) : x3_fwd_workspace(a);
+  const int s = mm_bf16_parts(which, a);
+  return s > 1 ? (size_t)s * (size_t)a.I * (size_t)(which ? a.H : a.O) * sizeof(float) : 0;
+}
+
 size_t roast_mm_fwd_workspace(const roast_mm_desc* d, roast_dtype dt, int64_t I) {
   MMArgs a;
   if (make_mm_args(d, I, &a) != ROAST_OK || !dtype_ok(dt) || I == 0) return 0;
-  if (dt == ROAST_F32) return x3_fwd_workspace(a);
-  const int s = mm_bf16_parts(0, a);
-  return s > 1 ? (size_t)s * (size_t)I * (size_t)a.O * sizeof(float) : 0;
+  return product_workspace(0, dt, a);
 }
 
 size_t roast_mm_bwd_dx_workspace(const roast_mm_desc* d, roast_dtype dt, int64_t I) {
   MMArgs a;
   if (make_mm_args(d, I, &a) != ROAST_OK || !dtype_ok(dt) || I == 0) return 0;
-  if (dt == ROAST_F32) return x3_dx_workspace(a);
-  const int s = mm_bf16_parts(1, a);
-  return s > 1 ? (size_t)s * (size_t)I * (size_t)a.H * sizeof(float) : 0;
+  return product_workspace(1, dt, a);
 }
 
 int roast_mm_strip_blocks(const roast_mm_desc* d, int64_t I, int which) {
@@ -191,12 +194,12 @@ roast_status roast_mm_fwd_ws(const roast_mm_desc* d, roast_dtype dt, int64_t I, 
   if (I == 0) return ROAST_OK;
   if (!X || !M || !Y || ldx < a.H || ldy < a.O) return ROAST_ERR_ARG;
   if (dt == ROAST_BF16) {
-    const size_t need = roast_mm_fwd_workspace(d, dt, I);
+    const size_t need = workspace ? product_workspace(0, dt, a) : 0;
     if (workspace && (workspace_bytes < need || ((uintptr_t)workspace & 15) != 0)) return ROAST_ERR_WORKSPACE;
     st = mfma_mm_fwd(a, X, ldx, M, M_bf16, Y, ldy, need ? (float*)workspace : nullptr, (hipStream_t)stream);
     if (st != ROAST_ERR_UNSUPPORTED) return st;
   } else {
-    if (workspace && (workspace_bytes < roast_mm_fwd_workspace(d, dt, I) || ((uintptr_t)workspace & 15) != 0)) return ROAST_ERR_WORKSPACE;
+    if (workspace && (workspace_bytes < product_workspace(0, dt, a) || ((uintptr_t)workspace & 15) != 0)) return ROAST_ERR_WORKSPACE;
     const MMPlan plan = mm_plan(a, true, 0, M_bf16 != nullptr, workspace != nullptr);
     if (plan.route == MMRoute::Wide || plan.route == MMRoute::Columns128) {
       st = x3_mm_fwd(a, (const float*)X, ldx, M, M_bf16, (float*)Y, ldy, workspace, (hipStream_t)stream);
@@ -226,12 +229,12 @@ roast_status roast_mm_bwd_dx_ws(const roast_mm_desc* d, roast_dtype dt, int64_t 
   if (I == 0) return ROAST_OK;
   if (!dY || !M || !dX || ldx < a.H || ldy < a.O) return ROAST_ERR_ARG;
   if (dt == ROAST_BF16) {
-    const size_t need = roast_mm_bwd_dx_workspace(d, dt, I);
+    const size_t need = workspace ? product_workspace(1, dt, a) : 0;
     if (workspace && (workspace_bytes < need || ((uintptr_t)workspace & 15) != 0)) return ROAST_ERR_WORKSPACE;
     st = mfma_mm_bwd_dx(a, dY, ldy, M, M_bf16, dX, ldx, need ? (float*)workspace : nullptr, (hipStream_t)stream);
     if (st != ROAST_ERR_UNSUPPORTED) return st;
   } else {
-    if (workspace && (workspace_bytes < roast_mm_bwd_dx_workspace(d, dt, I) || ((uintptr_t)workspace & 15) != 0)) return ROAST_ERR_WORKSPACE;
+    if (workspace && (workspace_bytes < product_workspace(1, dt, a) || ((uintptr_t)workspace & 15) != 0)) return ROAST_ERR_WORKSPACE;
     const MMPlan plan = mm_plan(a, true, 1, M_bf16 != nullptr, workspace != nullptr);
     if (plan.route == MMRoute::Wide || plan.route == MMRoute::Columns128) {
       st = x3_mm_bwd_dx(a, (const float*)dY, ldy, M, M_bf16, (float*)dX, ldx, workspace, (hipStream_t)stream);

@@ -1683,7 +1683,7 @@ roast_status x3_mm_bwd_dM(const MMArgs& a, const float* X, int64_t ldx, const fl
   return launch<MODE_DM, kBM, kBN, 4, 2, false, true>(p, grid, s);
 }
 
-MMPlan mm_plan(const MMArgs& a, bool f32, int which, bool copy, bool workspace) {
+static MMPlan find_mm_plan(const MMArgs& a, bool f32, int which, bool copy, bool workspace) {
   MMPlan p{};
   p.direct = direct_plan(which, !f32, a);
   bool blocks;                           // the larger kernels take the shape
@@ -1706,6 +1706,10 @@ MMPlan mm_plan(const MMArgs& a, bool f32, int which, bool copy, bool workspace) 
   }
   p.route = direct ? MMRoute::Direct : !blocks ? MMRoute::Generic : p.wide.bm ? MMRoute::Wide : MMRoute::Columns128;
   return p;
+}
+
+MMPlan mm_plan(const MMArgs& a, bool f32, int which, bool copy, bool workspace) {
+  return remembered<MMPlan>(a, which + 2 * copy + 4 * workspace, f32, [&] { return find_mm_plan(a, f32, which, copy, workspace); });
 }
 
 int mm_bf16_parts(int which, const MMArgs& a) {

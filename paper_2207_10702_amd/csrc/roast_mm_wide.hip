@@ -1063,38 +1063,16 @@ WidePlan plan_dm(const MMArgs& a, int parts, bool x3) {
   return best;
 }
 
-// A plan takes a microsecond or two to find, as long as a third of a small call's host time: each thread keeps
-// the plans of the last few shapes it has launched.
-template <typename F>
-WidePlan remembered(const MMArgs& a, int kind, int parts, bool x3, F&& find) {
-  struct Key {
-    int64_t I, H, O, Z1, Z2, m;
-    int sign2, kind, parts, x3;
-    bool operator==(const Key& o) const {
-      return I == o.I && H == o.H && O == o.O && Z1 == o.Z1 && Z2 == o.Z2 && m == o.m && sign2 == o.sign2 && kind == o.kind &&
-             parts == o.parts && x3 == o.x3;
-    }
-  };
-  struct Slot { Key key; WidePlan plan; };
-  constexpr int kSlots = 64;
-  static thread_local Slot slots[kSlots] = {};
-  const Key k = {a.I, a.H, a.O, a.Z1, a.Z2, a.m_size, a.hash.use_sign == 2, kind + 1, parts, x3};
-  const uint64_t h = ((((uint64_t)a.I * 31 + (uint64_t)a.H) * 31 + (uint64_t)a.O) * 31 + (uint64_t)(4 * parts + kind)) * 0x9e3779b97f4a7c15ull;
-  Slot& s = slots[h >> 58];
-  if (!(s.key == k)) s = {k, find()};
-  return s.plan;
-}
-
 }  // namespace
 
 WidePlan wide_fwd_plan(const MMArgs& a, int max_parts, bool x3) {
-  return remembered(a, MODE_FWD, max_parts, x3, [&] { return plan_hashed(MODE_FWD, a, max_parts, x3); });
+  return remembered<WidePlan>(a, 4 * max_parts + MODE_FWD, x3, [&] { return plan_hashed(MODE_FWD, a, max_parts, x3); });
 }
 WidePlan wide_dx_plan(const MMArgs& a, int max_parts, bool x3) {
-  return remembered(a, MODE_DX, max_parts, x3, [&] { return plan_hashed(MODE_DX, a, max_parts, x3); });
+  return remembered<WidePlan>(a, 4 * max_parts + MODE_DX, x3, [&] { return plan_hashed(MODE_DX, a, max_parts, x3); });
 }
 WidePlan wide_dm_plan(const MMArgs& a, int parts, bool x3) {
-  return remembered(a, MODE_DM, parts, x3, [&] { return plan_dm(a, parts, x3); });
+  return remembered<WidePlan>(a, 4 * parts + MODE_DM, x3, [&] { return plan_dm(a, parts, x3); });
 }
 
 // plan.parts > 1: ws holds the partial outputs
