@@ -206,7 +206,7 @@ roast_status roast_mm_fwd_ws(const roast_mm_desc* d, roast_dtype dt, int64_t I, 
       if (st != ROAST_ERR_UNSUPPORTED) return st;
     }
     if (plan.direct.mi) {
-      st = direct_mm(0, false, plan.direct, a, X, ldx, M, nullptr, Y, ldy, nullptr, (hipStream_t)stream);
+      st = direct_f32(0, plan.direct, a, (const float*)X, ldx, M, (float*)Y, ldy, workspace, (hipStream_t)stream);
       if (st != ROAST_ERR_UNSUPPORTED) return st;
     }
   }
@@ -241,7 +241,7 @@ roast_status roast_mm_bwd_dx_ws(const roast_mm_desc* d, roast_dtype dt, int64_t 
       if (st != ROAST_ERR_UNSUPPORTED) return st;
     }
     if (plan.direct.mi) {
-      st = direct_mm(1, false, plan.direct, a, dY, ldy, M, nullptr, dX, ldx, nullptr, (hipStream_t)stream);
+      st = direct_f32(1, plan.direct, a, (const float*)dY, ldy, M, (float*)dX, ldx, workspace, (hipStream_t)stream);
       if (st != ROAST_ERR_UNSUPPORTED) return st;
     }
   }

@@ -185,12 +185,14 @@ roast_status wide_mm_dM(const MMArgs& a, const WidePlan& plan, const uint16_t* X
 // from the copy of M, or from fp32 M and rounded in registers.  bf16: A and C 16-byte aligned, leading dimensions multiples of 8.
 struct DirectPlan {
   int mi, nj;            // 16 mi x 16 nj output block (0: not the shape for these kernels)
-  int parts;             // of the contraction (more than one: bf16, 64 x 64 blocks, with a workspace)
+  int parts;             // of the contraction (more than one: with a workspace; bf16: 64 x 64 blocks)
   double us;             // modelled time
 };
-DirectPlan direct_plan(int which, bool bf16, const MMArgs& a);
+DirectPlan direct_plan(int which, bool bf16, const MMArgs& a, size_t room);   // room (fp32): bytes of workspace for partial outputs
 DirectPlan ring_plan(int which, const MMArgs& a, int max_parts, double copy_us, double nocopy_us);   // max_parts: 1 where no workspace is given
 roast_status direct_mm(int which, bool bf16, const DirectPlan& d, const MMArgs& a, const void* A, int64_t lda, const float* M, const void* M_bf16, void* C, int64_t ldc, float* G, hipStream_t s);
+
+roast_status direct_f32(int which, const DirectPlan& d, const MMArgs& a, const float* A, int64_t lda, const float* M, float* C, int64_t ldc, void* ws, hipStream_t s);   // its fp32 calls, parts added up
 
 // ---- the 64 x 64 blocks of those for calls with a copy of M (roast_mm_ring.hip): the same sums, operands through LDS.  A and C as above.
 bool ring_ok(int which, const MMArgs& a);

@@ -46,7 +46,7 @@ struct DirectArgs {
   int64_t ldc;
   uint32_t mu1, mu2;                     // 2^32 / Z1, 2^32 / Z2, rounded up
   int nbx, nby;                          // column, row blocks
-  int parts;                             // of the contraction (bf16), whose partial outputs go to G, [part][rows][columns]
+  int parts;                             // of the contraction (bf16: of 64 x 64 blocks alone), whose partial outputs go to G, [part][rows][columns]
   float* G;
 };
 
@@ -79,9 +79,9 @@ __global__ __launch_bounds__(64 * kWaves, MI * NJ > 8 ? 2 : 4) void k_mm_direct(
   const int plane = (int)(blockIdx.x / (unsigned)p.nbx), bx = (int)blockIdx.x - plane * p.nbx;
   const int bz = p.parts > 1 ? plane / p.nby : 0, by = plane - bz * p.nby;
   const int m0 = by * BM, n0 = bx * BN;
-  // (parts: of a contraction whose length is a multiple of 64, in whole pairs of bf16 units)
-  const int u0 = p.parts > 1 ? 2 * (K / 64 * bz / p.parts) : 0;
-  const int units = p.parts > 1 ? 2 * (K / 64 * (bz + 1) / p.parts) - u0 : (K + KU - 1) / KU;
+  // (parts: of a contraction whose length is a multiple of 64, in whole 64s)
+  const int u0 = p.parts > 1 ? 64 / KU * (K / 64 * bz / p.parts) : 0;
+  const int units = p.parts > 1 ? 64 / KU * (K / 64 * (bz + 1) / p.parts) - u0 : (K + KU - 1) / KU;
   // a wave's share of them is contiguous: rows of A whose length is a power of two lie in the same few channels of the L2, and
   // waves that read next to one another would all ask those
   const int first = u0 + units * wave / kWaves, end = u0 + units * (wave + 1) / kWaves;
@@ -238,11 +238,11 @@ __global__ __launch_bounds__(64 * kWaves, MI * NJ > 8 ? 2 : 4) void k_mm_direct(
       for (int w = 1; w < kWaves; ++w)
 #pragma unroll
         for (int v = 0; v < V / 4; ++v) sum[v] += *reinterpret_cast<const floatx4*>(s_part + w * (16 * RI * BN) + row * BN + c + 4 * v);
-      if constexpr (BF && MI * NJ == 16) {
+      if constexpr (!BF || MI * NJ == 16) {
         if (p.parts > 1) {
           float* part_to = p.G + ((int64_t)bz * I + out_row) * N + n0 + c;
 #pragma unroll
-          for (int v = 0; v < 2; ++v) *reinterpret_cast<floatx4*>(part_to + 4 * v) = a.lambda * sum[v];
+          for (int v = 0; v < V / 4; ++v) *reinterpret_cast<floatx4*>(part_to + 4 * v) = a.lambda * sum[v];
           continue;
         }
       }
@@ -325,6 +325,9 @@ roast_status launch_variant(bool bf16, int mi, int nj, const DirectArgs& p, hipS
   return ROAST_ERR_UNSUPPORTED;
 }
 
+// the launch that adds up `parts` fp32 outputs of I x N
+double finish_us(int parts, int64_t I, int64_t N) { return 2.5 + 0.12 * parts + (double)parts * (double)I * (double)N * 4.0 / 1.95e6; }
+
 }  // namespace
 
 // The block with the smallest modelled time.  The fp32 constants are fitted to 300 timed launches (most within 8 %) of 16 .. 1024 rows: up to two
@@ -337,23 +340,34 @@ roast_status launch_variant(bool bf16, int mi, int nj, const DirectArgs& p, hipS
 // bf16, by the same margin on what the wide blocks are modelled to take: 206 x 1664 x 1152 17.0 -> 10.5, 512 x 2048 x 2048 without a copy of M 23.8 -> 17.2 (two
 // launches; with one see roast_mm_ring.hip); without a workspace 35 x 4352 x 5504 43.7 -> 19.6.  A 64 x 64 block of bf16 takes 167 ns a unit of 32, 20 bytes a clock and CU:
 // neither more units in flight nor fewer address instructions, whole lines of A or other channels of the L2 change that.
-DirectPlan direct_plan(int which, bool bf16, const MMArgs& a) {
+DirectPlan direct_plan(int which, bool bf16, const MMArgs& a, size_t room) {
   DirectPlan best{0, 0, 1, 1e300};
   const int64_t K = which ? a.O : a.H, N = which ? a.H : a.O, l2 = 1 << 20;
-  for (const Variant& v : kVariants) {
-    if (v.bf16 != bf16 || v.alone[which] == 0.0 || !direct_ok(a, bf16, which == 1, 16 * v.nj)) continue;
-    const int64_t blocks = cdiv(a.I, 16 * v.mi) * cdiv(N, 16 * v.nj);
-    if (blocks > kMaxBlocks) continue;
-    const double r = (double)blocks / 256.0;
-    double rounds = 0.5 * (r + std::ceil(r)), us;
-    if (!bf16 && r <= 2.0) rounds = 2.0;            // (some CUs have two workgroups from the start)
-    us = v.fixed + 1e-3 * (double)K * (r <= 1.0 ? v.alone[which] : v.busy[which] * rounds) + (bf16 ? 0.0 : 0.6 * std::max(0.0, std::ceil(r) - 2.0));
-    if (!bf16 && a.m_size > l2) {                   // weights from beyond the L2, once for each row of blocks
-      const double bytes = (double)cdiv(a.I, 16 * v.mi) * (double)K * (double)N * 4.0 * (1.0 - (double)l2 / (double)a.m_size);
-      us = std::max(us, v.fixed + bytes / (which || v.nj == 4 || a.Z2 <= 16 * v.nj ? 6.5e6 : 3.5e6));
+  auto search = [&](int max_parts) {
+    for (const Variant& v : kVariants) {
+      if (v.bf16 != bf16 || v.alone[which] == 0.0 || !direct_ok(a, bf16, which == 1, 16 * v.nj)) continue;
+      const int64_t blocks = cdiv(a.I, 16 * v.mi) * cdiv(N, 16 * v.nj);
+      for (int parts = 1; parts <= max_parts && blocks * parts <= kMaxBlocks; ++parts) {
+        if (parts > 1 && (K < 128 * parts || blocks * parts > 768 || (size_t)parts * (size_t)a.I * (size_t)N * 4 > room)) break;
+        const double r = (double)(blocks * parts) / 256.0;
+        double rounds = 0.5 * (r + std::ceil(r)), us;
+        if (!bf16 && r <= 2.0) rounds = 2.0;        // (some CUs have two workgroups from the start)
+        us = v.fixed + 1e-3 * (double)K / parts * (r <= 1.0 ? v.alone[which] : v.busy[which] * rounds) + (bf16 ? 0.0 : 0.6 * std::max(0.0, std::ceil(r) - 2.0));
+        if (!bf16 && a.m_size > l2) {               // weights from beyond the L2, once for each row of blocks
+          const double bytes = (double)cdiv(a.I, 16 * v.mi) * (double)K * (double)N * 4.0 * (1.0 - (double)l2 / (double)a.m_size);
+          us = std::max(us, v.fixed + bytes / (which || v.nj == 4 || a.Z2 <= 16 * v.nj ? 6.5e6 : 3.5e6));
+        }
+        if (parts > 1) us += 0.8 + finish_us(parts, a.I, N);
+        if (us < best.us) best = {v.mi, v.nj, parts, us};
+      }
     }
-    if (us < best.us) best = {v.mi, v.nj, 1, us};
-  }
+  };
+  search(1);
+  // fp32 with a workspace (whose planes leave room for the outputs of parts): parts of the contraction, where one workgroup to a block leaves half of the CUs idle or a row of A is
+  // far longer than one of the output.  26 x 448 x 14400 dX 50.9 -> 16.3 us, 20 x 10560 x 704 33.7 -> 15.1, 36 x 320 x 4160 dX 17.5 -> 10.5, none of 140 random products slower.
+  if (room > 0 && best.mi && a.H % 64 == 0 && a.O % 64 == 0 && a.Z1 % 32 == 0 && a.Z2 % 32 == 0 &&
+      (cdiv(a.I, 16 * best.mi) * cdiv(N, 16 * best.nj) <= 128 || K >= 16 * N))
+    search(kWideParts);
   return best;
 }
 
@@ -364,7 +378,7 @@ DirectPlan direct_plan(int which, bool bf16, const MMArgs& a) {
 static double ring_us(int which, int parts, const MMArgs& a, bool copy) {
   const double K = (double)(which ? a.O : a.H), N = (double)(which ? a.H : a.O), part = K / parts;
   const int64_t wgs = cdiv(a.I, 64) * ((which ? a.H : a.O) / 64) * parts, rest = wgs % 256;
-  const double finish = parts == 1 ? 0.0 : 2.5 + 0.12 * parts + (double)parts * (double)a.I * N * 4.0 / 1.95e6;
+  const double finish = parts == 1 ? 0.0 : finish_us(parts, a.I, (int64_t)N);
   if (!copy) return 5.0 + (double)cdiv(wgs, 256) * part * (which ? 9.7e-3 : 5.2e-3) + finish;
   const double index = 2.0e-3 * (a.Z2 >= 128 ? 1.25 : 1.0);
   double us = 1.3 + (double)(wgs / 256) * (4.05 + part * (index + 1.0e-3));

@@ -1685,7 +1685,6 @@ roast_status x3_mm_bwd_dM(const MMArgs& a, const float* X, int64_t ldx, const fl
 
 static MMPlan find_mm_plan(const MMArgs& a, bool f32, int which, bool copy, bool workspace) {
   MMPlan p{};
-  p.direct = direct_plan(which, !f32, a);
   bool blocks;                           // the larger kernels take the shape
   if (f32) {
     blocks = workspace && (which == 0 ? x3_fwd_ok(a) : x3_dx_ok(a));
@@ -1694,6 +1693,7 @@ static MMPlan find_mm_plan(const MMArgs& a, bool f32, int which, bool copy, bool
     blocks = mfma_elem_ok(a);
     if (blocks && copy) p.wide = which == 0 ? wide_fwd_plan(a, workspace ? kWideParts : 1, false) : dx_plan(a, workspace ? kWideParts : 1);
   }
+  p.direct = direct_plan(which, !f32, a, blocks && f32 ? (which ? x3_dx_workspace(a) : x3_fwd_workspace(a)) : 0);
   // (8 %: what the models are good for)
   const double larger = !blocks ? 0.0 : f32 ? x3_us(which, a) : bf16_us(which, a, workspace);
   bool direct = p.direct.mi && (!blocks ? f32 : 1.08 * p.direct.us < larger);
@@ -1706,6 +1706,16 @@ static MMPlan find_mm_plan(const MMArgs& a, bool f32, int which, bool copy, bool
   }
   p.route = direct ? MMRoute::Direct : !blocks ? MMRoute::Generic : p.wide.bm ? MMRoute::Wide : MMRoute::Columns128;
   return p;
+}
+
+roast_status direct_f32(int which, const DirectPlan& d, const MMArgs& a, const float* A, int64_t lda, const float* M, float* C, int64_t ldc, void* ws, hipStream_t s) {
+  DirectPlan plan = d;
+  if (plan.parts > 1 && (ldc % 4 != 0 || !aligned16(C))) plan.parts = 1;      // (the sums of the parts are stored 16 bytes at a time)
+  const roast_status st = direct_mm(which, false, plan, a, A, lda, M, nullptr, C, ldc, (float*)ws, s);
+  if (st != ROAST_OK || plan.parts == 1) return st;
+  KernArgs p{};
+  p.G = (float*)ws; p.C32 = C; p.ldc = ldc;
+  return split_finish(p, (unsigned)plan.parts, a.I, which ? a.H : a.O, s);
 }
 
 MMPlan mm_plan(const MMArgs& a, bool f32, int which, bool copy, bool workspace) {

@@ -1,0 +1,69 @@
+"""Forward and dX of small fp32 calls in parts of the contraction, with a workspace: whole and uneven parts, every block that takes them, rows around the
+block edge, tile places inside and across parts, unaligned and strided outputs (which are not split), infinities."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2207_10702_amd import workloads as wl
+from tests.util import F32_TOL, rel_err, to_dev, to_host_f64
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+FWD, DX = 0, 1
+# (which product, rows, contraction, columns, Z1, Z2, |M|)
+CASES = [
+    (FWD, 20, 10560, 704, 32, 32, 368657),
+    (FWD, 51, 9088, 320, 128, 128, 193973),
+    (FWD, 1, 4096, 256, 64, 64, 4097),
+    (FWD, 33, 6144, 512, 96, 96, 30011),
+    (DX, 26, 14400, 448, 64, 64, 16384),
+    (DX, 17, 4160, 256, 32, 32, 48896),
+    (DX, 36, 4160, 320, 64, 32, 970006),
+    (DX, 54, 6336, 256, 96, 96, 20011),
+]
+
+
+def setup(roast, case, lam, use_sign=True):
+    which, I, K, N, Z1, Z2, m = case
+    H, O = (N, K) if which else (K, N)
+    rng = np.random.default_rng(I + K + N)
+    h = wl.draw_hash(rng, use_sign=use_sign, align=1)
+    d = roast.mm_desc(H, O, Z1, Z2, m, 2, lam, h)
+    blocks = roast.roast_mm_direct_blocks(d, torch.float32, I, which, True)
+    assert blocks and blocks[3] > 1
+    need = (roast.roast_mm_bwd_dx_workspace if which else roast.roast_mm_fwd_workspace)(d, torch.float32, I)
+    assert need >= 4 * blocks[3] * I * N
+    return rng, h, d, H, O, (roast.roast_mm_bwd_dx if which else roast.roast_mm_fwd), need
+
+
+@pytest.mark.parametrize("case", CASES)
+@pytest.mark.parametrize("pad", [0, 3, 4])             # 3: outputs that the parts are not added up for
+def test_parts_match_oracle(roast, case, pad):
+    which, I, K, N, Z1, Z2, m = case
+    lam = np.float32(0.37)
+    rng, h, d, H, O, call, need = setup(roast, case, lam)
+    M = wl.draw_m(rng, m, ("normal", 0.05))
+    A = (rng.standard_normal((I, K)) * np.exp2(rng.integers(-6, 6, size=(I, K)))).astype(np.float32)
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+    Ad = torch.full((I, K + pad), 9.0, device="cuda")[:, :K].copy_(to_dev(A))
+    out = torch.full((I, N + pad), 7.0, device="cuda")
+    call(d, Ad, to_dev(M), out[:, :N], ws=ws)
+    assert torch.all(out[:, N:] == 7.0)
+    W = oracle.materialize_w(h, 2, H, O, Z1, Z2, float(lam), M)
+    ref = (oracle.mm_bwd_dx if which else oracle.mm_fwd)(A.astype(np.float64), W)
+    # as for the calls in one part: chains of 64, of those, and of the parts
+    assert rel_err(to_host_f64(out[:, :N]), ref) <= F32_TOL
+
+
+@pytest.mark.parametrize("case", [CASES[0], CASES[5]])
+def test_an_infinity_stays_in_its_row(roast, case):
+    which, I, K, N, Z1, Z2, m = case
+    _, h, d, H, O, call, need = setup(roast, case, 1.0, use_sign=False)
+    A = torch.randn((I, K), device="cuda")
+    A[3, 5] = A[I - 1, K - 1] = float("inf")
+    R = call(d, A, torch.rand(m, device="cuda") + 0.5, ws=torch.empty(need, dtype=torch.uint8, device="cuda"))
+    assert torch.all(R[[3, I - 1]] == float("inf"))
+    R[[3, I - 1]] = 0
+    assert torch.all(torch.isfinite(R))
