@@ -430,6 +430,7 @@ struct AccPlan {
   float less;            // the last of three and more is by that much of a length shorter than the others
   bool owned;            // (fixed point) every slot has one workgroup that sees all of its chunks and writes dM
   bool take_max;         // ... and the route kernel takes the largest |dOut|
+  bool sampled;          // ... of a sample of dOut: see local_pbits
   __host__ __device__ int R() const { return (int)(g << s_log2); }
   __host__ __device__ uint32_t segments(uint32_t count) const {
     const uint32_t usual = count < mean ? count : mean, n = (uint32_t)(((float)usual * share + (float)(count - usual)) * per + up);
@@ -466,6 +467,7 @@ inline AccPlan acc_plan(const EmbedArgs& a, const BucketPlan& p, bool fixed) {
   k.take_max = k.owned && a.B <= 4 * a.N;   // (beyond that few workgroups would read a large dOut: 70 000 chunks of 32, 2 M bags 197 us, 95 with a launch for it; 0.4 M 70 and 68, 0.14 M 42 and 46)
   // Skew: lists have room for twice their mean load and half of what there is beyond that, the rest is spill.  Owned slots:
   // lists have room for the mean load and all there is beyond twice that, any number of entries can be spilled.
+  k.sampled = k.take_max && a.bag_off == nullptr;   // (pooled: a row of dOut that no chunk refers to counts too)
   k.cap = (uint32_t)((k.owned ? room - p.n_items : p.n_items + room / 2) / p.nb);
   k.spill_cap = (uint32_t)std::min<int64_t>(room - (int64_t)p.nb * k.cap, 0x7fffffff);
   const int seg = fixed && k.R() == 4096 && a.Z >= 32 ? kPass : kSeg;
@@ -498,8 +500,18 @@ __global__ __launch_bounds__(256) void k_embed_zero(uint32_t* __restrict__ p, in
 // quantum is at least 2^-31 of the largest contribution (finer than fp32 for any realistic batch).
 struct FixedScale {
   uint32_t absmax_bits;   // max over dOut of the bits of |x| (order-independent: integer max)
-  uint32_t pad[3];
+  uint32_t not_finite;    // (a sample only) a workgroup has found an Inf or NaN and makes all of dM NaN
+  uint32_t pad[2];
 };
+
+__device__ inline uint32_t absmax4(const vfloat4& x) {
+  return max(max(__float_as_uint(x.x) & 0x7fffffffu, __float_as_uint(x.y) & 0x7fffffffu), max(__float_as_uint(x.z) & 0x7fffffffu, __float_as_uint(x.w) & 0x7fffffffu));
+}
+__device__ inline uint32_t wave_max(uint32_t m) {
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, d, 64));
+  return m;
+}
 
 __global__ __launch_bounds__(256) void k_embed_absmax(const float* __restrict__ dOut, int64_t n,
                                                       FixedScale* __restrict__ fs) {
@@ -510,10 +522,6 @@ __global__ __launch_bounds__(256) void k_embed_absmax(const float* __restrict__ 
   const int64_t head = min(n, (int64_t)((16 - ((uintptr_t)dOut & 15)) & 15) / 4);   // floats before the first aligned one
   const int64_t nvec = (n - head) / 4;
   const vfloat4* v = reinterpret_cast<const vfloat4*>(dOut + head);
-  auto take = [&](const vfloat4& x) {
-    m = max(m, max(max(__float_as_uint(x.x) & 0x7fffffffu, __float_as_uint(x.y) & 0x7fffffffu),
-                   max(__float_as_uint(x.z) & 0x7fffffffu, __float_as_uint(x.w) & 0x7fffffffu)));
-  };
   // a workgroup takes contiguous 32 KiB pieces (8 x 256 lanes x 16 bytes), round-robin over the grid
   constexpr int U = 8;
   const int64_t piece = (int64_t)U * 256;
@@ -525,13 +533,12 @@ __global__ __launch_bounds__(256) void k_embed_absmax(const float* __restrict__ 
       x[u] = __builtin_nontemporal_load(v + i);
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) take(x[u]);
+    for (int u = 0; u < U; ++u) m = max(m, absmax4(x[u]));
   }
   if (tid < head) m = max(m, __float_as_uint(dOut[tid]) & 0x7fffffffu);
   const int64_t tail0 = head + 4 * nvec;
   if (tail0 + tid < n) m = max(m, __float_as_uint(dOut[tail0 + tid]) & 0x7fffffffu);
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, d, 64));
+  m = wave_max(m);
   __shared__ uint32_t s_m[4];
   if ((threadIdx.x & 63) == 0) s_m[threadIdx.x >> 6] = m;
   __syncthreads();
@@ -545,8 +552,7 @@ __global__ __launch_bounds__(256) void k_embed_absmax(const float* __restrict__ 
 }
 
 // 2^shift as a double; NaN when dOut holds an Inf or NaN (the result is then NaN everywhere).
-__device__ inline double fixed_scale(const FixedScale* fs, float lambda, int pbits) {
-  const uint32_t bits = fs->absmax_bits;
+__device__ inline double fixed_scale(uint32_t bits, float lambda, int pbits) {
   if (bits >= 0x7f800000u) return __longlong_as_double(0x7ff8000000000000ll);
   const float bound = fabsf(lambda) * __uint_as_float(bits);   // every |contribution| <= bound
   if (!(bound > 0.f)) return 1.0;
@@ -555,6 +561,20 @@ __device__ inline double fixed_scale(const FixedScale* fs, float lambda, int pbi
   frexpf(bound, &ex);                                           // bound < 2^ex
   return ldexp(1.0, pbits - ex);
 }
+__device__ inline double fixed_scale(const FixedScale* fs, float lambda, int pbits) { return fixed_scale(fs->absmax_bits, lambda, pbits); }
+
+// Where every slot has one workgroup that sees all of its chunks, the scale only has to allow for those chunks, and each workgroup
+// takes its own: from the largest magnitude of a sample of dOut, the same one in every run, with up to 6 bits to spare.  A workgroup that
+// meets a chunk beyond that starts over with its own largest.  So dOut is read once, not twice (10007 x 26 lookups of 128 values 87 -> 69 us).
+// The bits to spare are those that its chunks, fewer than all of the call, leave: the quantum is not larger than that of the
+// largest |dOut| of the call and all chunks (but for one bit where a workgroup has most of them).
+__device__ inline int local_pbits(uint32_t entries) { return min(50, (int)__builtin_clz(entries | 1u) + 31); }   // (entries * 2^pbits < 2^63; 50: fixed_raw)
+__device__ inline uint32_t sample_limit(uint32_t bits, float lambda, int spare) {
+  if (bits >= 0x7f800000u) return 0xffffffffu;                  // (everything is NaN already)
+  const float l = ldexpf(__uint_as_float(bits), spare);
+  return fabsf(lambda) * l < __uint_as_float(0x7f800000u) ? __float_as_uint(l) : bits;   // (no product may overflow unseen)
+}
+__device__ inline int local_spare(int pbits, int pbits_all) { return min(max(pbits - pbits_all, 1), 6); }
 
 __device__ inline unsigned long long to_fixed(float v, double scale) {
   return (unsigned long long)__double2ll_rn((double)v * scale);
@@ -612,13 +632,15 @@ __device__ inline uint32_t absmax_of(const vfloat4* __restrict__ v, int64_t firs
 #pragma unroll
     for (int u = 0; u < U; ++u) x[u] = v[min(i0 + (int64_t)u * threads, end - 1)];        // (clamped: max is idempotent)
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) m = max(m, __float_as_uint(x[u][e]) & 0x7fffffffu);
+    for (int u = 0; u < U; ++u) m = max(m, absmax4(x[u]));
   }
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, d, 64));
-  return m;
+  return wave_max(m);
+}
+
+// This thread's piece of a sample of them: a 128-byte line for every eight threads, evenly spaced.
+__device__ inline vfloat4 sample_of(const vfloat4* __restrict__ v, int64_t first, int64_t end, int threads) {
+  const int64_t i = first + (end - first) / (threads / 8) * (threadIdx.x / 8) + threadIdx.x % 8;
+  return v[min(i, end - 1)];
 }
 
 // entry = (chunk number g, key); key = offset | (negative sign << 31).  A workgroup waits in turn for the ids, for the
@@ -645,18 +667,23 @@ __global__ __launch_bounds__(kRouteThreads) void k_embed_route(EmbedArgs a, AccP
   uint32_t* s_over = reinterpret_cast<uint32_t*>(s_ord + (twice ? 2 * items : items));   // [items] (twice) those | rank there << 16
   uint32_t* s_src = s_over + (twice ? items : 0);                  // [rows_wg] gradient row of each lookup (pooled calls only)
   constexpr int W = kRouteThreads / 64;
-  __shared__ uint32_t s_wave[W], s_overs;
+  __shared__ uint32_t s_wave[W], s_max[W], s_overs;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (tid == 0) s_overs = 0u;
   for (int i = tid; i < nb; i += kRouteThreads) hist[i] = 0u;
   __syncthreads();
+  const int64_t n0 = (int64_t)blockIdx.x * rows_wg;
+  const int rows_here = (int)min((int64_t)rows_wg, a.N - n0);
+  vfloat4 sample = {};
+  if (FIXED && k.sampled) sample = sample_of(reinterpret_cast<const vfloat4*>(dOut), n0 * (a.D / 4), (n0 + rows_here) * (a.D / 4), kRouteThreads);
+  auto new_max = [&](uint32_t m) {
+    if (m > __hip_atomic_load(&fs->absmax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&fs->absmax_bits, m);
+  };
   auto take_max = [&] {
     const int64_t pieces = (a.bag_off ? a.B : a.N) * a.D / 4, share = (pieces + gridDim.x - 1) / gridDim.x, first = share * blockIdx.x;
     const uint32_t m = absmax_of(reinterpret_cast<const vfloat4*>(dOut), first, min(pieces, first + share), kRouteThreads);
-    if (lane == 0 && m > __hip_atomic_load(&fs->absmax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&fs->absmax_bits, m);
+    if (lane == 0) new_max(m);
   };
-  const int64_t n0 = (int64_t)blockIdx.x * rows_wg;
-  const int rows_here = (int)min((int64_t)rows_wg, a.N - n0);
   for (int q = tid; q < rows_here; q += kRouteThreads) {
     const int64_t n = n0 + q;
     if (a.bag_off) s_src[q] = (uint32_t)bag_of(a.bag_off, a.B, n);
@@ -681,7 +708,11 @@ __global__ __launch_bounds__(kRouteThreads) void k_embed_route(EmbedArgs a, AccP
     got[j] = cnt[j] ? atomicAdd(&cursor[i], cnt[j]) : 0u;
     sum += cnt[j];
   }
-  if (FIXED && k.take_max) take_max();
+  if (FIXED && k.take_max && !k.sampled) take_max();
+  if (FIXED && k.sampled) {
+    const uint32_t m = wave_max(absmax4(sample));
+    if (lane == 0) s_max[wave] = m;
+  }
   uint32_t run = sum;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
@@ -690,6 +721,12 @@ __global__ __launch_bounds__(kRouteThreads) void k_embed_route(EmbedArgs a, AccP
   }
   if (lane == 63) s_wave[wave] = run;
   __syncthreads();
+  if (FIXED && k.sampled && tid == 0) {
+    uint32_t m = s_max[0];
+#pragma unroll
+    for (int w = 1; w < W; ++w) m = max(m, s_max[w]);
+    new_max(m);
+  }
   run -= sum;
 #pragma unroll
   for (int w = 0; w < W; ++w)
@@ -757,10 +794,11 @@ __global__ __launch_bounds__(kRouteThreads) void k_embed_route(EmbedArgs a, AccP
 // the same slots, next to one another: where adds into the image one chunk at a time (two segments of unsorted lists)
 // meet in the same LDS words, runs of them cost a register add (pooled gradient of 0.85 M chunks 45 -> 30 us with its sums;
 // 0.73 M chunks of 16 over an M of 0.24 Mi 55 -> 38).  LPI: lanes per chunk, Z / 4 (4, 8 or 16; 0: any other).
-template <bool FIXED, int LPI>
+// SAMPLED: fixed point where AccPlan::sampled.
+template <bool FIXED, int LPI, bool SAMPLED = false>
 __global__ __launch_bounds__(kAccThreads, 4) void k_embed_accum(EmbedArgs a, AccPlan k, const uint32_t* __restrict__ cursor, const uint2* __restrict__ list,
                                                      const float* __restrict__ dOut, float* __restrict__ dM, int pbits,
-                                                     const FixedScale* fs, unsigned long long* __restrict__ acc) {
+                                                     FixedScale* fs, unsigned long long* __restrict__ acc) {
   // fp64 image: LDS fp32 atomic adds were measured ~20x slower than fp64 ones on this chip.
   // FIXED: the same 8-byte slots hold 64-bit fixed-point sums.
   using img_t = typename std::conditional<FIXED, unsigned long long, double>::type;
@@ -789,11 +827,30 @@ __global__ __launch_bounds__(kAccThreads, 4) void k_embed_accum(EmbedArgs a, Acc
   uint32_t* s_src = bin + span / 2;                               // sorted: chunk of dOut | sign << 31
   uint16_t* s_at = reinterpret_cast<uint16_t*>(s_src + acc_sorted(Z));    // ... and place in the image
   double scale = 0.0;
-  if constexpr (FIXED) scale = fixed_scale(fs, a.lambda, pbits);
-  for (int i = tid; i < span; i += kAccThreads) img[i] = img_t(0);
+  // (sampled) bits of the largest |dOut| that the scale allows for, and of the largest that is added
+  uint32_t limit = 0u, top = 0u;
+  auto uniform = [](double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(double, (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)b) | (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)) << 32);
+  };
+  if constexpr (FIXED) {
+    const uint32_t bits = __builtin_amdgcn_readfirstlane(fs->absmax_bits);
+    if constexpr (SAMPLED) {
+      const int own = local_pbits(count + spilled), spare = local_spare(own, pbits);
+      scale = uniform(fixed_scale(bits, a.lambda, own - spare));
+      pbits = own;
+      limit = sample_limit(bits, a.lambda, spare);
+    } else {
+      scale = fixed_scale(bits, a.lambda, pbits);
+    }
+  }
   const uint32_t low = (uint32_t)slot0 - (uint32_t)Z;             // M offset of the image's first slot (modulo 2^32)
+  auto clear = [&] {
+    for (int i = tid; i < span; i += kAccThreads) img[i] = img_t(0);
+  };
+  clear();
 #pragma unroll 1
-  for (int r = 0; r < 2; ++r) {
+  for (int r = 0; r < 2;) {
     const uint2* lst = list + (size_t)b * k.cap;
     uint32_t entries = count, len = k.length<FIXED>(entries, nseg), first = seg * len;
     if (r == 1) {
@@ -823,7 +880,7 @@ __global__ __launch_bounds__(kAccThreads, 4) void k_embed_accum(EmbedArgs a, Acc
 #pragma unroll
       for (int u = 0; u < kPer; ++u) {
         at[u] = (ent[u].y & 0x7fffffffu) - low;
-        if (r == 1 && (FIXED && k.owned ? (ent[u].x >> 31) && at[u] >= (uint32_t)Z : part == 0 && at[u] < (uint32_t)Z)) at[u] = 0u;
+        if (r == 1 && (FIXED && (SAMPLED || k.owned) ? (ent[u].x >> 31) && at[u] >= (uint32_t)Z : part == 0 && at[u] < (uint32_t)Z)) at[u] = 0u;
         if (at[u] - 1u >= (uint32_t)(S + Z - 1)) at[u] = 0u;        // (not picked)
         if (at[u]) {
           const int sh = 16 * (at[u] & 1);
@@ -934,6 +991,7 @@ __global__ __launch_bounds__(kAccThreads, 4) void k_embed_accum(EmbedArgs a, Acc
               cur = x.at[u];
               n = 0;
             }
+            if constexpr (SAMPLED) top = max(top, x.at[u] ? absmax4(x.d[u]) : 0u);   // (not of what fills up the shares)
             const float sc = __uint_as_float(__float_as_uint(a.lambda) ^ (x.src[u] & 0x80000000u));
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -956,17 +1014,51 @@ __global__ __launch_bounds__(kAccThreads, 4) void k_embed_accum(EmbedArgs a, Acc
       }
       __syncthreads();
     }
+    ++r;
+    if (SAMPLED && r == 2) {
+      // Has a chunk exceeded what the scale allows for?  Then once more, with the largest of them instead of the sample's.
+      top = wave_max(top);
+      if (lane == 0) s_wave[wave] = top;
+      __syncthreads();
+#pragma unroll 1
+      for (int w = 0; w < kAccThreads / 64; ++w) top = max(top, s_wave[w]);
+      top = __builtin_amdgcn_readfirstlane(top);
+      if (top > limit) {
+        limit = 0xffffffffu;
+        scale = uniform(fixed_scale(top, a.lambda, pbits));
+        clear();
+        if (scale == scale) r = 0;
+      }
+      __syncthreads();
+    }
   }
   __syncthreads();
-  const int own = !(FIXED && k.owned) && part == Q - 1 ? S + Z : S;
+  if constexpr (SAMPLED) {
+    // An Inf or NaN makes all of dM NaN: the first workgroup to find one that the sample has not adds NaN to every slot.
+    if (scale != scale && fs->absmax_bits < 0x7f800000u) {
+      if (tid == 0) s_wave[0] = atomicExch(&fs->not_finite, 1u);
+      __syncthreads();
+      if (s_wave[0] == 0u)
+        for (int64_t i = tid; i < a.m_size; i += kAccThreads) unsafeAtomicAdd(dM + i, __uint_as_float(0x7fc00000u));
+      return;
+    }
+  }
+  const int own = !(FIXED && (SAMPLED || k.owned)) && part == Q - 1 ? S + Z : S;
   for (int i = tid; i < own && slot0 + i < a.m_size; i += kAccThreads) {
     const img_t v = img[Z + i];
     if constexpr (FIXED) {
-      if (acc) {
+      if (!SAMPLED && acc) {
         if (v != 0ull) atomicAdd(acc + slot0 + i, v);
       } else {
-        if (scale != scale) dM[slot0 + i] += __uint_as_float(0x7fc00000u);
-        else if (v != 0ull) dM[slot0 + i] += (float)((double)(long long)v / scale);
+        // (sampled: another workgroup may be adding NaN)
+        if constexpr (SAMPLED) {
+          if (scale != scale) unsafeAtomicAdd(dM + slot0 + i, __uint_as_float(0x7fc00000u));
+          else if (v != 0ull) unsafeAtomicAdd(dM + slot0 + i, (float)((double)(long long)v / scale));
+        } else if (scale != scale) {
+          dM[slot0 + i] += __uint_as_float(0x7fc00000u);
+        } else if (v != 0ull) {
+          dM[slot0 + i] += (float)((double)(long long)v / scale);
+        }
       }
     } else {
       const float f = (float)v;
@@ -1007,12 +1099,14 @@ roast_status bucket_run(const EmbedArgs& a, const BucketPlan& p, const int64_t* 
   const int S = k.R() >> k.q_log2;
   const dim3 grid((unsigned)((p.nb + 7) / 8 * 8) * k.most << k.q_log2);
   auto run = [&](auto LPI) -> roast_status {
-    auto* accum = &k_embed_accum<FIXED, decltype(LPI)::value>;
+    constexpr int L = decltype(LPI)::value;
+    auto* accum = FIXED && k.sampled ? &k_embed_accum<FIXED, L, FIXED> : &k_embed_accum<FIXED, L>;
     static std::atomic<bool> configured{false};   // per instantiation; a race between host threads only repeats the calls
     if (!configured.load(std::memory_order_acquire)) {
       // (the route kernel also has a little static LDS)
       if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_embed_route<FIXED>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 8192) != hipSuccess ||
-          hipFuncSetAttribute(reinterpret_cast<const void*>(accum), hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024) != hipSuccess)
+          hipFuncSetAttribute(reinterpret_cast<const void*>(&k_embed_accum<FIXED, L>), hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024) != hipSuccess ||
+          hipFuncSetAttribute(reinterpret_cast<const void*>(&k_embed_accum<FIXED, L, FIXED>), hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024) != hipSuccess)
         return ROAST_ERR_HIP;
       configured.store(true, std::memory_order_release);
     }
@@ -1063,7 +1157,7 @@ roast_status embed_bwd_atomic_launch(const EmbedArgs& a, const int64_t* rows, co
   return bucket_run<false>(a, p, rows, tables, dOut, dM, (char*)ws, 0, nullptr, nullptr, s);
 }
 
-// DETERMINISTIC: largest |dOut| -> fixed-point scale; zeroed 64-bit accumulator of |M| slots in the
+// DETERMINISTIC: largest |dOut| (or that of a sample of it, see local_pbits) -> fixed-point scale; zeroed 64-bit accumulator of |M| slots in the
 // workspace; the same route + accumulate pipeline (or one thread per element for the shapes it does
 // not take) with integer atomics; then dM += accumulator / scale, one rounding per slot.
 size_t embed_det_workspace_bytes(const EmbedArgs& a) {
