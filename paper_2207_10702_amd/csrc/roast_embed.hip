@@ -44,17 +44,28 @@ __device__ inline void for_each_chunk(const EmbedArgs& a, bool walk, uint64_t ta
 // Pooled gradient: the bag of lookup n = the last b with bag_off[b] <= n (bag_off[0] == 0, so one
 // exists; empty bags share their offset with the next one and are skipped by "last").  The result is
 // clamped to [0, B-1] whatever the offsets hold, so a malformed offsets array cannot push a read out
-// of dOut.
-__device__ inline int64_t bag_of(const int64_t* __restrict__ bag_off, int64_t B, int64_t n) {
+// of dOut.  What it costs is one wait for memory after the other: first the place where bags of equal sizes have it, then
+// seven places a time (13 waits of a bisection of 8191 bags: 1, or 6 where sizes differ).
+__device__ inline int64_t bag_of(const int64_t* __restrict__ bag_off, int64_t B, int64_t N, int64_t n) {
+  const int64_t guess = min(max((int64_t)(((double)n + 0.5) * ((double)B / (double)N)), (int64_t)0), B - 1);
+  const int64_t at = bag_off[guess], next = bag_off[min(guess + 1, B - 1)];
+  if (at <= n && (next > n || guess == B - 1)) return guess;
   int64_t lo = 0, hi = B;
   while (hi - lo > 1) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (bag_off[mid] <= n) lo = mid; else hi = mid;
+    const int64_t step = (hi - lo + 7) >> 3;
+    int64_t v[7];
+#pragma unroll
+    for (int i = 0; i < 7; ++i) v[i] = bag_off[min(lo + (i + 1) * step, hi - 1)];
+    int below = 0;
+#pragma unroll
+    for (int i = 0; i < 7; ++i) below += lo + (i + 1) * step < hi && v[i] <= n ? 1 : 0;
+    lo += below * step;
+    hi = min(hi, lo + step);
   }
   return lo;
 }
 // row of dOut that lookup n takes its gradient from
-__device__ inline int64_t grad_row(const EmbedArgs& a, int64_t n) { return a.bag_off ? bag_of(a.bag_off, a.B, n) : n; }
+__device__ inline int64_t grad_row(const EmbedArgs& a, int64_t n) { return a.bag_off ? bag_of(a.bag_off, a.B, a.N, n) : n; }
 
 // Streaming lookup / direct-atomic gradient.  A wave takes rows_wave lookups (64, fewer in a small call): each lane
 // hashes the chunks of one lookup into the wave's LDS key list (offset | sign bit, 32-bit), then the wave walks the
@@ -686,7 +697,7 @@ __global__ __launch_bounds__(kRouteThreads) void k_embed_route(EmbedArgs a, AccP
   };
   for (int q = tid; q < rows_here; q += kRouteThreads) {
     const int64_t n = n0 + q;
-    if (a.bag_off) s_src[q] = (uint32_t)bag_of(a.bag_off, a.B, n);
+    if (a.bag_off) s_src[q] = (uint32_t)bag_of(a.bag_off, a.B, a.N, n);
     for_each_chunk(a, walk != 0, tables[n], (uint64_t)rows[n], [&](int64_t c, int64_t off, int sgn) {
       s_key[q * C + c] = (uint32_t)off | (sgn < 0 ? 0x80000000u : 0u);
       const uint32_t b = k.bucket((uint32_t)off);
@@ -789,18 +800,23 @@ __global__ __launch_bounds__(kRouteThreads) void k_embed_route(EmbedArgs a, AccP
   }
 }
 
+// Sums in fp64, of rows of dOut that belong to one lookup each or to the lookups of a bag; fixed point, with the scale of the call or a workgroup's own.
+// A row that several lookups share stays in the L2 (plain loads: 8191 bags of 26 30 -> 27 us), one that is read once goes by it (with plain loads 1.7 M rows of 128
+// 197 -> 226 us, 0.26 M 45 -> 51).
+enum { ACC_ROWS, ACC_BAGS, ACC_FIXED, ACC_SAMPLED };
+
 // What bounds it: the gather of 128-byte pieces of dOut (5.7 TB/s on 6.8 M chunks of 32; 152 of the kernel's 188 us), beside which
 // the sort, the image and its flush (29 us) are only partly hidden by the other workgroup of the CU.  Sorting puts the chunks of a popular row, which add to
 // the same slots, next to one another: where adds into the image one chunk at a time (two segments of unsorted lists)
 // meet in the same LDS words, runs of them cost a register add (pooled gradient of 0.85 M chunks 45 -> 30 us with its sums;
 // 0.73 M chunks of 16 over an M of 0.24 Mi 55 -> 38).  LPI: lanes per chunk, Z / 4 (4, 8 or 16; 0: any other).
-// SAMPLED: fixed point where AccPlan::sampled.
-template <bool FIXED, int LPI, bool SAMPLED = false>
+template <int KIND, int LPI>
 __global__ __launch_bounds__(kAccThreads, 4) void k_embed_accum(EmbedArgs a, AccPlan k, const uint32_t* __restrict__ cursor, const uint2* __restrict__ list,
                                                      const float* __restrict__ dOut, float* __restrict__ dM, int pbits,
                                                      FixedScale* fs, unsigned long long* __restrict__ acc) {
   // fp64 image: LDS fp32 atomic adds were measured ~20x slower than fp64 ones on this chip.
   // FIXED: the same 8-byte slots hold 64-bit fixed-point sums.
+  constexpr bool FIXED = KIND >= ACC_FIXED, SAMPLED = KIND == ACC_SAMPLED;
   using img_t = typename std::conditional<FIXED, unsigned long long, double>::type;
   extern __shared__ __attribute__((aligned(16))) char img_raw[];
   __shared__ uint32_t s_wave[kAccThreads / 64];
@@ -815,6 +831,7 @@ __global__ __launch_bounds__(kAccThreads, 4) void k_embed_accum(EmbedArgs a, Acc
   const int S = k.R() >> k.q_log2, Z = a.Z;
   const int64_t slot0 = (int64_t)b * k.R() + part * S;
   if (slot0 >= a.m_size) return;
+  const uint32_t largest = FIXED ? fs->absmax_bits : 0u;          // (asked for with the cursors)
   const uint32_t count = min(cursor[b], k.cap), spilled = min(cursor[k.nb], k.spill_cap);
   const uint32_t nseg = k.segments(count);
   if (seg >= nseg) return;
@@ -834,14 +851,14 @@ __global__ __launch_bounds__(kAccThreads, 4) void k_embed_accum(EmbedArgs a, Acc
     return __builtin_bit_cast(double, (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)b) | (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)) << 32);
   };
   if constexpr (FIXED) {
-    const uint32_t bits = __builtin_amdgcn_readfirstlane(fs->absmax_bits);
     if constexpr (SAMPLED) {
+      const uint32_t bits = __builtin_amdgcn_readfirstlane(largest);
       const int own = local_pbits(count + spilled), spare = local_spare(own, pbits);
       scale = uniform(fixed_scale(bits, a.lambda, own - spare));
       pbits = own;
       limit = sample_limit(bits, a.lambda, spare);
     } else {
-      scale = fixed_scale(bits, a.lambda, pbits);
+      scale = fixed_scale(largest, a.lambda, pbits);
     }
   }
   const uint32_t low = (uint32_t)slot0 - (uint32_t)Z;             // M offset of the image's first slot (modulo 2^32)
@@ -979,7 +996,10 @@ __global__ __launch_bounds__(kAccThreads, 4) void k_embed_accum(EmbedArgs a, Acc
           }
 #pragma unroll
           for (int u = 0; u < U; ++u)
-            x.d[u] = __builtin_nontemporal_load(reinterpret_cast<const vfloat4*>(from + (int64_t)(x.src[u] & 0x7fffffffu) * (LPI ? 4 * LPI : Z)));
+          {
+            const vfloat4* p = reinterpret_cast<const vfloat4*>(from + (int64_t)(x.src[u] & 0x7fffffffu) * (LPI ? 4 * LPI : Z));
+            x.d[u] = KIND == ACC_BAGS ? *p : __builtin_nontemporal_load(p);
+          }
         };
         auto add = [&](const Batch& x) {
 #pragma unroll
@@ -1035,7 +1055,7 @@ __global__ __launch_bounds__(kAccThreads, 4) void k_embed_accum(EmbedArgs a, Acc
   __syncthreads();
   if constexpr (SAMPLED) {
     // An Inf or NaN makes all of dM NaN: the first workgroup to find one that the sample has not adds NaN to every slot.
-    if (scale != scale && fs->absmax_bits < 0x7f800000u) {
+    if (scale != scale && largest < 0x7f800000u) {
       if (tid == 0) s_wave[0] = atomicExch(&fs->not_finite, 1u);
       __syncthreads();
       if (s_wave[0] == 0u)
@@ -1100,13 +1120,14 @@ roast_status bucket_run(const EmbedArgs& a, const BucketPlan& p, const int64_t* 
   const dim3 grid((unsigned)((p.nb + 7) / 8 * 8) * k.most << k.q_log2);
   auto run = [&](auto LPI) -> roast_status {
     constexpr int L = decltype(LPI)::value;
-    auto* accum = FIXED && k.sampled ? &k_embed_accum<FIXED, L, FIXED> : &k_embed_accum<FIXED, L>;
+    constexpr int kOne = FIXED ? ACC_FIXED : ACC_ROWS, kOther = FIXED ? ACC_SAMPLED : ACC_BAGS;
+    auto* accum = (FIXED ? k.sampled : a.bag_off != nullptr) ? &k_embed_accum<kOther, L> : &k_embed_accum<kOne, L>;
     static std::atomic<bool> configured{false};   // per instantiation; a race between host threads only repeats the calls
     if (!configured.load(std::memory_order_acquire)) {
       // (the route kernel also has a little static LDS)
       if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_embed_route<FIXED>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 8192) != hipSuccess ||
-          hipFuncSetAttribute(reinterpret_cast<const void*>(&k_embed_accum<FIXED, L>), hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024) != hipSuccess ||
-          hipFuncSetAttribute(reinterpret_cast<const void*>(&k_embed_accum<FIXED, L, FIXED>), hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024) != hipSuccess)
+          hipFuncSetAttribute(reinterpret_cast<const void*>(&k_embed_accum<kOne, L>), hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024) != hipSuccess ||
+          hipFuncSetAttribute(reinterpret_cast<const void*>(&k_embed_accum<kOther, L>), hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024) != hipSuccess)
         return ROAST_ERR_HIP;
       configured.store(true, std::memory_order_release);
     }
