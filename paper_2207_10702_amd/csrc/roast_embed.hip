@@ -524,23 +524,24 @@ __device__ inline uint32_t wave_max(uint32_t m) {
   return m;
 }
 
-__global__ __launch_bounds__(256) void k_embed_absmax(const float* __restrict__ dOut, int64_t n,
+constexpr int kMaxThreads = 512;
+__global__ __launch_bounds__(kMaxThreads) void k_embed_absmax(const float* __restrict__ dOut, int64_t n,
                                                       FixedScale* __restrict__ fs) {
   // streaming read: 16-byte loads, eight of them in flight per thread (a scalar grid-stride loop was
   // latency-bound at a third of this rate); head and tail that are not 16-byte aligned go scalar
   uint32_t m = 0u;
-  const int64_t tid = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t tid = (int64_t)blockIdx.x * kMaxThreads + threadIdx.x;
   const int64_t head = min(n, (int64_t)((16 - ((uintptr_t)dOut & 15)) & 15) / 4);   // floats before the first aligned one
   const int64_t nvec = (n - head) / 4;
   const vfloat4* v = reinterpret_cast<const vfloat4*>(dOut + head);
-  // a workgroup takes contiguous 32 KiB pieces (8 x 256 lanes x 16 bytes), round-robin over the grid
+  // a workgroup takes contiguous 64 KiB pieces (8 x 512 lanes x 16 bytes), round-robin over the grid
   constexpr int U = 8;
-  const int64_t piece = (int64_t)U * 256;
+  const int64_t piece = (int64_t)U * kMaxThreads;
   for (int64_t p0 = (int64_t)blockIdx.x * piece; p0 < nvec; p0 += (int64_t)gridDim.x * piece) {
     vfloat4 x[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int64_t i = min(p0 + u * 256 + threadIdx.x, nvec - 1);      // clamped: max is idempotent
+      const int64_t i = min(p0 + u * kMaxThreads + threadIdx.x, nvec - 1);      // clamped: max is idempotent
       x[u] = __builtin_nontemporal_load(v + i);
     }
 #pragma unroll
@@ -550,14 +551,16 @@ __global__ __launch_bounds__(256) void k_embed_absmax(const float* __restrict__ 
   const int64_t tail0 = head + 4 * nvec;
   if (tail0 + tid < n) m = max(m, __float_as_uint(dOut[tail0 + tid]) & 0x7fffffffu);
   m = wave_max(m);
-  __shared__ uint32_t s_m[4];
+  __shared__ uint32_t s_m[kMaxThreads / 64];
   if ((threadIdx.x & 63) == 0) s_m[threadIdx.x >> 6] = m;
   __syncthreads();
   // Atomics on one address complete one after the other (12 ns each: one per wave of 2048 workgroups
-  // took 100 us whatever the size of dOut): one per workgroup, and none where the maximum found
-  // so far is as large already.
+  // took 100 us whatever the size of dOut): one per workgroup, none where the maximum found
+  // so far is as large already, and no more workgroups than the loads of two to a CU need (all of them end together where
+  // dOut is small: 38 MB took 28 us with 2048).
   if (threadIdx.x == 0) {
-    m = max(max(s_m[0], s_m[1]), max(s_m[2], s_m[3]));
+#pragma unroll
+    for (int w = 0; w < kMaxThreads / 64; ++w) m = max(m, s_m[w]);
     if (m > __hip_atomic_load(&fs->absmax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&fs->absmax_bits, m);
   }
 }
@@ -1207,8 +1210,8 @@ roast_status embed_bwd_det_run(const EmbedArgs& a, const int64_t* rows, const ui
     const int64_t zb = (zero_words + 255) / 256;
     if (zb > 0x7fffffffll) return ROAST_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(k_embed_zero, dim3((unsigned)zb), dim3(256), 0, s, (uint32_t*)base, zero_words);
-    const int64_t ab = std::min<int64_t>((n_grad / 4 + 255) / 256 + 1, 256 * 8);
-    hipLaunchKernelGGL(k_embed_absmax, dim3((unsigned)ab), dim3(256), 0, s, dOut, n_grad, fs);
+    const int64_t ab = std::min<int64_t>(n_grad / (4 * 8 * kMaxThreads) + 1, 512);
+    hipLaunchKernelGGL(k_embed_absmax, dim3((unsigned)ab), dim3(kMaxThreads), 0, s, dOut, n_grad, fs);
   }
   roast_status st;
   if (routed) {
