@@ -4,10 +4,12 @@
 //
 // Steps: (1) the tile table (offset, sign) is computed on the device and the tiles are ranked by
 // (offset, tile id); (2) the per-tile products G = X^T dY are written, unscaled, to the workspace,
-// one copy per I-split; (3) one thread per slot j of M walks the tiles whose interval
-// [offset, offset + Z1*Z2) covers j -- a contiguous run of the ranked table because all tiles have
-// the same length -- and adds their contributions in rank order, splits in index order.  No
+// one copy per I-split; (3) a workgroup of consecutive slots of M walks the tiles whose interval
+// [offset, offset + Z1*Z2) reaches into them -- a contiguous run of the ranked table because all tiles have
+// the same length -- and adds their contributions in a fixed order, splits in index order.  No
 // atomics, so the result is bit-identical from run to run.
+#include <type_traits>
+
 #include "roast_internal.hpp"
 
 namespace roast {
@@ -63,49 +65,90 @@ __global__ __launch_bounds__(256) void k_rank_tiles(int64_t nT, const int64_t* _
   }
 }
 
-// dM[j] += sum over every virtual weight that lands on slot j, in a fixed order: the tiles that cover
-// j in rank order, dealt round-robin to the eight lanes that share the slot, each lane adding its
-// tiles (and their parts) in order, then a butterfly over the eight partial sums -- every level adds
-// the same two values on both lanes, and fp addition is commutative, so all lanes agree bit for bit.
-constexpr int kGatherLanes = 8;
-__global__ __launch_bounds__(256) void k_dm_gather(MMArgs a, int splits, const float* __restrict__ G,
-                                                   const int64_t* __restrict__ sorted_off,
-                                                   const uint32_t* __restrict__ order, const int8_t* __restrict__ sgn,
-                                                   float* __restrict__ dM) {
-  const int64_t j = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kGatherLanes;
-  const int sub = threadIdx.x % kGatherLanes;
-  const bool live = j < a.m_size;
-  const int64_t nT = a.nTx * a.nTy, L = (int64_t)a.Z1 * a.Z2;
-  float total = 0.f;
-  int any = 0;
-  if (live) {
-    // first ranked tile with offset > j - L
-    int64_t lo = 0, hi = nT;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if (sorted_off[mid] > j - L) hi = mid; else lo = mid + 1;
+// Number of sorted offsets below x, by all 64 lanes of a wave: 64 places at a time.
+__device__ inline int count_below(const int64_t* __restrict__ sorted_off, int n, int64_t x) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0, hi = n;
+  while (lo < hi) {
+    const int step = (hi - lo + 63) / 64, at = lo + (lane + 1) * step - 1;
+    const bool below = at < hi && sorted_off[min(at, n - 1)] < x;
+    lo += __builtin_popcountll(__builtin_amdgcn_ballot_w64(below)) * step;
+    hi = min(hi, lo + step - 1);
+  }
+  return lo;
+}
+
+// dM[j] += sum over every virtual weight that lands on slot j, in a fixed order: a workgroup has 64 * V consecutive slots, each wave takes every
+// WAVES-th of the tiles that reach into them, in rank order, and the waves' fp64 sums are added in theirs.  Bound: the products, read once; the lanes of
+// a wave read consecutive ones of a tile.  (One slot to eight lanes, each with tiles of its own, read them in pieces of 32 bytes, searched for every slot and
+// divided 64-bit numbers: 41 tokens of 6336 x 7680 over 5.6 Mi slots 641 us.)
+template <int V, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_dm_gather(MMArgs a, int splits, const float* __restrict__ G,
+                                                          const int64_t* __restrict__ sorted_off,
+                                                          const uint32_t* __restrict__ order, const int8_t* __restrict__ sgn,
+                                                          float* __restrict__ dM) {
+  __shared__ double s_sum[WAVES][64 * V];
+  __shared__ uint32_t s_any[WAVES][64];          // bit v: slot 64 * v + lane has a weight
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t w0 = (int64_t)blockIdx.x * (64 * V), L = (int64_t)a.Z1 * a.Z2, plane = a.H * a.O;
+  const int nT = (int)(a.nTx * a.nTy);
+  const int first = count_below(sorted_off, nT, w0 - L + 1), end = count_below(sorted_off, nT, w0 + 64 * V);
+  double total[V];
+  uint32_t any = 0u;
+#pragma unroll
+  for (int v = 0; v < V; ++v) total[v] = 0.0;
+  for (int q = first + wave; q < end; q += WAVES) {
+    const uint32_t t = order[q];
+    const int64_t p0 = w0 - sorted_off[q];
+    const int64_t h0 = (int64_t)(t / (uint32_t)a.nTy) * a.Z1, c0 = (int64_t)(t % (uint32_t)a.nTy) * a.Z2;
+    const double sign = (double)sgn[t];
+    const float* from[V];
+    bool have[V];
+    float es[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      const int64_t p = p0 + 64 * v + lane;
+      have[v] = p >= 0 && p < L;
+      int64_t h, c;
+      if (L < (1ll << 31)) {
+        const uint32_t n = have[v] ? (uint32_t)p : 0u, r = n / (uint32_t)a.Z2;
+        h = h0 + r;
+        c = c0 + (n - r * (uint32_t)a.Z2);
+      } else {
+        const int64_t n = have[v] ? p : 0, r = n / a.Z2;
+        h = h0 + r;
+        c = c0 + (n - r * a.Z2);
+      }
+      have[v] = have[v] && h < a.H && c < a.O;
+      from[v] = G + (have[v] ? h * a.O + c : 0);
+      es[v] = a.hash.use_sign == 2 ? (float)elem_sign(a.hash, a.layer, (uint64_t)h, (uint64_t)c) : 1.f;
+      any |= have[v] ? 1u << v : 0u;
     }
-    for (int64_t q = lo + sub; q < nT; q += kGatherLanes) {
-      const int64_t o = sorted_off[q];
-      if (o > j) break;
-      const uint32_t t = order[q];
-      const int64_t p = j - o;
-      const int64_t h = (int64_t)(t / a.nTy) * a.Z1 + p / a.Z2;
-      const int64_t c = (int64_t)(t % a.nTy) * a.Z2 + p % a.Z2;
-      if (h >= a.H || c >= a.O) continue;
-      float acc = 0.f;
-      for (int s = 0; s < splits; ++s) acc += G[((int64_t)s * a.H + h) * a.O + c];
-      const float es = a.hash.use_sign == 2 ? (float)elem_sign(a.hash, a.layer, (uint64_t)h, (uint64_t)c) : 1.f;
-      total += a.lambda * (float)sgn[t] * es * acc;
-      any = 1;
-    }
+    double sum[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) sum[v] = 0.0;
+#pragma unroll 4
+    for (int s = 0; s < splits; ++s)
+#pragma unroll
+      for (int v = 0; v < V; ++v) sum[v] += (double)from[v][s * plane];
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+      if (have[v]) total[v] += sign * (double)es[v] * sum[v];
   }
 #pragma unroll
-  for (int d = kGatherLanes / 2; d >= 1; d >>= 1) {
-    total += __shfl_xor(total, d, 64);
-    any |= __shfl_xor(any, d, 64);
+  for (int v = 0; v < V; ++v) s_sum[wave][64 * v + lane] = total[v];
+  s_any[wave][lane] = any;
+  __syncthreads();
+  for (int i = threadIdx.x; i < 64 * V; i += 64 * WAVES) {
+    double sum = 0.0;
+    uint32_t some = 0u;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+      sum += s_sum[w][i];
+      some |= s_any[w][i & 63] >> (i >> 6);
+    }
+    if (w0 + i < a.m_size && (some & 1u)) dM[w0 + i] += (float)((double)a.lambda * sum);
   }
-  if (live && sub == 0 && any) dM[j] += total;
 }
 
 // Sum the per-split products and scatter them: one workgroup per (tile, block of rows of the tile).
@@ -218,8 +261,16 @@ roast_status dm_det_run(const MMArgs& a, roast_dtype dt, const void* X, int64_t 
   if (st == ROAST_ERR_UNSUPPORTED) st = generic_dm_launch(a, dt, X, ldx, dY, ldy, nullptr, G, splits, s);
   if (st != ROAST_OK) return st;
 
-  hipLaunchKernelGGL(k_dm_gather, dim3((unsigned)((a.m_size * kGatherLanes + 255) / 256)), dim3(256), 0, s, a, splits, G, soff,
-                     order, sgn, dM);
+  // A small M is few workgroups: one value to a lane, and where a slot has many of them 16 waves to share its tiles (300 tokens of 512 x 1024 over 50000 slots,
+  // 10 products to a slot, 16 waves 10.8 us; 8192 of 768 x 3072 over 47185, 750 to a slot, 39 where eight lanes to a slot took 57).
+  auto gather = [&](auto V, auto WAVES) {
+    constexpr int v = decltype(V)::value, w = decltype(WAVES)::value;
+    hipLaunchKernelGGL((k_dm_gather<v, w>), dim3((unsigned)((a.m_size + 64 * v - 1) / (64 * v))), dim3(64 * w), 0, s, a, splits, G, soff, order, sgn, dM);
+  };
+  using std::integral_constant;
+  if (a.m_size >= (256ll << 10)) gather(integral_constant<int, 4>{}, integral_constant<int, 4>{});
+  else if ((double)a.H * (double)a.O * splits < 32.0 * (double)a.m_size) gather(integral_constant<int, 1>{}, integral_constant<int, 4>{});
+  else gather(integral_constant<int, 1>{}, integral_constant<int, 16>{});
   return hip_status(hipGetLastError());
 }
 
