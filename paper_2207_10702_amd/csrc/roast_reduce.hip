@@ -36,32 +36,48 @@ inline DetLayout det_layout(const MMArgs& a, int splits) {
 }
 
 // rank of tile t among all tiles by (offset, id); writes the sorted offsets and the permutation.
-// Sixteen lanes share a tile: each counts the smaller keys among every sixteenth key of the staged
-// block, and the counts are added up across the lanes (integers: any order).
-constexpr int kRankLanes = 16;
+// Sixteen lanes share TILES tiles; each counts the smaller keys among every sixteenth key of the staged
+// block, and the counts are added up across the lanes (integers: any order).  Bound: a comparison for each pair of tiles.  Offset and
+// id in one key make it one, and several tiles to a lane use a key that was read (11 880 tiles 84 -> 35 us, 65 536 1250 -> 347, beside one tile to a lane, offset and id by themselves).
+constexpr int kRankLanes = 16, kRankBlock = 1024;
+template <int TILES>
 __global__ __launch_bounds__(256) void k_rank_tiles(int64_t nT, const int64_t* __restrict__ off,
                                                     int64_t* __restrict__ sorted_off, uint32_t* __restrict__ order) {
-  __shared__ int64_t buf[256];
-  const int64_t t = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kRankLanes;
+  static_assert(kMaxTilesDet <= 1 << 17, "the id's bits of a key");
+  __shared__ int64_t buf[kRankBlock];
+  const int64_t t0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) / kRankLanes * TILES;
   const int sub = threadIdx.x % kRankLanes;
-  const int64_t mine = t < nT ? off[t] : 0;
-  int rank = 0;
-  for (int64_t base = 0; base < nT; base += 256) {
-    const int64_t u = base + threadIdx.x;
-    buf[threadIdx.x] = u < nT ? off[u] : INT64_MAX;
+  int64_t mine[TILES];
+  int rank[TILES];
+#pragma unroll
+  for (int i = 0; i < TILES; ++i) {
+    mine[i] = t0 + i < nT ? off[t0 + i] << 17 | (t0 + i) : 0;    // (fewer than 2^46 slots: 2^48 bytes)
+    rank[i] = 0;
+  }
+  for (int64_t base = 0; base < nT; base += kRankBlock) {
     __syncthreads();
-    const int lim = (int)min((int64_t)256, nT - base);
-    for (int q = sub; q < lim; q += kRankLanes) {
-      const int64_t o = buf[q];
-      rank += (o < mine || (o == mine && base + q < t)) ? 1 : 0;
+#pragma unroll
+    for (int v = 0; v < kRankBlock / 256; ++v) {
+      const int64_t u = base + 256 * v + threadIdx.x;
+      buf[256 * v + threadIdx.x] = u < nT ? off[u] << 17 | u : INT64_MAX;
     }
     __syncthreads();
+    const int lim = (int)min((int64_t)kRankBlock, nT - base);
+#pragma unroll 4
+    for (int q = sub; q < lim; q += kRankLanes) {
+      const int64_t key = buf[q];
+#pragma unroll
+      for (int i = 0; i < TILES; ++i) rank[i] += key < mine[i] ? 1 : 0;
+    }
   }
 #pragma unroll
-  for (int d = kRankLanes / 2; d >= 1; d >>= 1) rank += __shfl_xor(rank, d, 64);
-  if (t < nT && sub == 0) {
-    sorted_off[rank] = mine;
-    order[rank] = (uint32_t)t;
+  for (int i = 0; i < TILES; ++i) {
+#pragma unroll
+    for (int d = kRankLanes / 2; d >= 1; d >>= 1) rank[i] += __shfl_xor(rank[i], d, 64);
+    if (t0 + i < nT && sub == 0) {
+      sorted_off[rank[i]] = mine[i] >> 17;
+      order[rank[i]] = (uint32_t)(t0 + i);
+    }
   }
 }
 
@@ -252,7 +268,14 @@ roast_status dm_det_run(const MMArgs& a, roast_dtype dt, const void* X, int64_t 
 
   roast_status st = tile_index_launch(a, keys, sgn, s);
   if (st != ROAST_OK) return st;
-  hipLaunchKernelGGL(k_rank_tiles, dim3((unsigned)((nT * kRankLanes + 255) / 256)), dim3(256), 0, s, nT, keys, soff, order);
+  // (few tiles: one to sixteen lanes, for more waves)
+  auto rank = [&](auto TILES) {
+    constexpr int per_wg = 256 / kRankLanes * decltype(TILES)::value;
+    hipLaunchKernelGGL((k_rank_tiles<decltype(TILES)::value>), dim3((unsigned)((nT + per_wg - 1) / per_wg)), dim3(256), 0, s, nT, keys, soff, order);
+  };
+  if (nT <= 4096) rank(std::integral_constant<int, 1>{});
+  else if (nT <= 16384) rank(std::integral_constant<int, 2>{});
+  else rank(std::integral_constant<int, 4>{});
   st = hip_status(hipGetLastError());
   if (st != ROAST_OK) return st;
 

@@ -24,6 +24,10 @@ torch = pytest.importorskip("torch")
     (256, 128, 128, 32, (256 << 10) - 1, True),
     (256, 128, 128, 32, 256 << 10, True),      # windows of 256
     (1000, 520, 32, 32, (256 << 10) + 255, True),
+    (256, 256, 4, 4, 300, True),               # 4096 tiles at 285 places, and more than 4096 and 16384 (ranks of 1, 2, 4 tiles to a lane)
+    (258, 260, 4, 4, 5000, True),
+    (512, 516, 4, 4, 16, True),                # 16512 tiles at one place
+    (520, 520, 4, 4, 90_000, True),
 ])
 @pytest.mark.parametrize("I", [3, 700])
 def test_gradient_is_the_oracles(roast, H, O, Z1, Z2, m, sign, I):
