@@ -175,6 +175,7 @@ struct WidePlan {
 constexpr int kWideParts = 16;
 WidePlan wide_fwd_plan(const MMArgs& a, int max_parts, bool x3);   // max_parts: 1 where no workspace is given, else kWideParts
 WidePlan wide_dx_plan(const MMArgs& a, int max_parts, bool x3);
+WidePlan wide_square_plan(int which, const MMArgs& a, const WidePlan& plan);   // that launch (bf16 forward, dX) or a faster one in as many parts
 WidePlan wide_dm_plan(const MMArgs& a, int parts, bool x3);        // parts == 0: atomic adds, any number of parts
 roast_status wide_mm(int which, const MMArgs& a, const WidePlan& plan, const uint16_t* A, int64_t lda, int64_t a_plane,
                      const uint16_t* Mb, bool x3, uint16_t* C, float* C32, int64_t ldc, float* ws, hipStream_t s);

@@ -1704,6 +1704,7 @@ static MMPlan find_mm_plan(const MMArgs& a, bool f32, int which, bool copy, bool
       direct = true;
     }
   }
+  if (!f32 && !direct && p.wide.bm) p.wide = wide_square_plan(which, a, p.wide);
   p.route = direct ? MMRoute::Direct : !blocks ? MMRoute::Generic : p.wide.bm ? MMRoute::Wide : MMRoute::Columns128;
   return p;
 }

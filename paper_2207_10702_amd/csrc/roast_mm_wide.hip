@@ -18,7 +18,7 @@
 //     XOR of the weight fragments, in the second half of the product slot before the fragment's first
 //     use: 3 % on a 256 x 256 block, 4-8 % on the smaller ones (at the start of the slot that uses them, 6-9 %).
 // One workgroup: 8 waves, a 256 x BN block (BN = 256: 2 x 4 waves of 128 x 64; BN = 128: 4 x 2 waves of
-// 64 x 64), two LDS stages of one 64-deep contraction step each.  A step is four phases per wave --
+// 64 x 64; 128 rows: 2 x 4 waves of 64 x 48 or 64 x 32), two LDS stages of one 64-deep contraction step each.  A step is four phases per wave --
 // (upper, lower half of its rows) x (first, second 32 of the step) -- and a phase a memory slot and a
 // product slot.  The two waves of a SIMD run half a phase apart (the second four waves pass one
 // barrier more at the start): while one issues LDS reads and loads, the other's products have the
@@ -950,6 +950,7 @@ roast_status launch_block(const WideArgs& p, int bm, int bn, hipStream_t s) {
 template <int MODE>
 roast_status launch_hashed(const WideArgs& p, int bm, int bn, bool x3, hipStream_t s) {
   if (x3) return launch_block<MODE, true, false>(p, bm, bn, s);
+  if (bm == 128 && bn == 128) return shadow_copies(p.a.m_size) == 4 ? launch<MODE, 128, 128, false, true>(p, s) : launch<MODE, 128, 128, false, false>(p, s);
   return shadow_copies(p.a.m_size) == 4 ? launch_block<MODE, false, true>(p, bm, bn, s) : launch_block<MODE, false, false>(p, bm, bn, s);
 }
 
@@ -1037,6 +1038,21 @@ WidePlan plan_hashed(int which, const MMArgs& a, int max_parts, bool x3) {
   return of[best];
 }
 
+// The same launch in 128 x 128 blocks, where all of them run at a time and that is modelled to be faster: more CUs for a product that leaves a third of them or more
+// without a block.  In microseconds with blocks of 128 x 192 or 256 x 128 and with these, by their number: 1659 x 2432 x 896 247, 16.8 and 14.5;
+// 3823 x 448 x 896 120, 15.0 and 12.4; 3549 x 896 x 3008 196, 35.9 and 29.2; 1198 x 2752 x 1792 220, 25.4 and 20.7; 1290 x 1344 x 320 121, 9.2 and 7.8.
+// In two rounds they are slower than what there is (264 of them 23.7 and 33.9), and so they are for fp32 planes (252 over 1280 indices 83.0 and 87.8).  The
+// parts stay as they are: a call without a copy of M gives the same sums.  Tiles that a block holds whole, and 16 blocks at least (below, no call is long).
+WidePlan plan_square(int which, const MMArgs& a, const WidePlan& w) {
+  const int64_t N = which == MODE_FWD ? a.O : a.H, zn = which == MODE_FWD ? a.Z2 : a.Z1, zk = which == MODE_FWD ? a.Z1 : a.Z2;
+  const int64_t wgs = cdiv(a.I, 128) * cdiv(N, 128) * w.parts, K = which == MODE_FWD ? a.H : a.O;
+  const int64_t rows = w.parts > 1 ? w.rows : cdiv(K, BK) * BK;
+  if (w.nblk != 1 || wgs > 256 || wgs < 16 || 128 % zn != 0 || (cdiv(rows, zk) + 1) * (128 / zn + 1) > table_entries(128, 128)) return w;
+  const double finish = w.parts > 1 ? 3.8 + (double)w.parts * (double)a.I * (double)N * 4.0 / 3.0e6 : 0.0;
+  const double us = (double)(rows / BK) * (0.45 + 0.07 * (double)wgs / 256.0) + 3.9 + finish;
+  return us < w.us ? WidePlan{128, 128, 1, w.parts, w.rows, us} : w;
+}
+
 // parts > 0: the number of parts is given (and the products go to a workspace)
 WidePlan plan_dm(const MMArgs& a, int parts, bool x3) {
   WidePlan best{};
@@ -1071,6 +1087,7 @@ WidePlan wide_fwd_plan(const MMArgs& a, int max_parts, bool x3) {
 WidePlan wide_dx_plan(const MMArgs& a, int max_parts, bool x3) {
   return remembered<WidePlan>(a, 4 * max_parts + MODE_DX, x3, [&] { return plan_hashed(MODE_DX, a, max_parts, x3); });
 }
+WidePlan wide_square_plan(int which, const MMArgs& a, const WidePlan& plan) { return plan_square(which, a, plan); }
 WidePlan wide_dm_plan(const MMArgs& a, int parts, bool x3) {
   return remembered<WidePlan>(a, 4 * parts + MODE_DM, x3, [&] { return plan_dm(a, parts, x3); });
 }
