@@ -289,10 +289,12 @@ size_t roast_embed_bwd_workspace(const roast_embed_desc* d, int64_t N, roast_red
 /*
  * Gradient of the lookup (Section 4.3):  dM[offset(t,r,c) + o] += lambda * sign * dOut[n, c*Z + o].
  * dOut: N x D fp32 (row stride D); dM: m_size fp32, accumulated into.
- * DETERMINISTIC: every product fl(lambda * sign * dOut[..]) is converted to 64-bit fixed point with a
- * quantum derived from the largest |dOut| of the call (at least 31 bits below it), summed with
- * integer atomics -- exact, hence independent of the order -- and added to dM with one rounding per
- * slot; bit-identical from run to run.  dOut must be finite (an Inf or NaN turns all of dM into NaN).
+ * DETERMINISTIC: every product fl(lambda * sign * dOut[..]) is converted to 64-bit fixed point, summed as
+ * whole numbers -- exact, hence independent of the order -- and added to dM with one rounding per
+ * slot; bit-identical from run to run for the same arguments (the same lookups in another order may round
+ * otherwise).  The quantum is at least 31 bits below the largest |dOut|: of the call, or, where each slot of dM
+ * belongs to one workgroup, of a fixed sample of dOut's elements, or of that workgroup's own chunks where one of them
+ * is too large for the sample's quantum.  dOut must be finite (an Inf or NaN turns all of dM into NaN).
  * ws / ws_bytes: device scratch of at least roast_embed_bwd_workspace() bytes (may be NULL / 0 in
  * ATOMIC mode); its contents on return are unspecified.
  */

@@ -580,21 +580,23 @@ __device__ inline double fixed_scale(const FixedScale* fs, float lambda, int pbi
 // Where every slot has one workgroup that sees all of its chunks, the scale only has to allow for those chunks, and each workgroup
 // takes its own: from the largest magnitude of a sample of dOut, the same one in every run, with up to 6 bits to spare.  A workgroup that
 // meets a chunk beyond that starts over with its own largest.  So dOut is read once, not twice (10007 x 26 lookups of 128 values 87 -> 69 us).
-// The bits to spare are those that its chunks, fewer than all of the call, leave: the quantum is not larger than that of the
-// largest |dOut| of the call and all chunks (but for one bit where a workgroup has most of them).
-__device__ inline int local_pbits(uint32_t entries) { return min(50, (int)__builtin_clz(entries | 1u) + 31); }   // (entries * 2^pbits < 2^63; 50: fixed_raw)
+// The chunks are counted by the places asked for in the bucket's list, whether it had room for them or not: that is the
+// same number in every run, where how many are found behind the lists is not (a chunk that two full lists ask for is there once).
+// The bits to spare are those that these chunks, no more than all of the call, leave (at least one: fixed_pbits leaves a bit for the sign
+// and rounds up): the quantum is not larger than that of the largest |dOut| of the call and all chunks.
+__device__ inline int local_pbits(uint32_t chunks) { return min(50, (int)__builtin_clz(chunks | 1u) + 31); }   // (chunks * 2^pbits < 2^63; 50: fixed_raw)
 __device__ inline uint32_t sample_limit(uint32_t bits, float lambda, int spare) {
   if (bits >= 0x7f800000u) return 0xffffffffu;                  // (everything is NaN already)
   const float l = ldexpf(__uint_as_float(bits), spare);
   return fabsf(lambda) * l < __uint_as_float(0x7f800000u) ? __float_as_uint(l) : bits;   // (no product may overflow unseen)
 }
-__device__ inline int local_spare(int pbits, int pbits_all) { return min(max(pbits - pbits_all, 1), 6); }
+__device__ inline int local_spare(int pbits, int pbits_all) { return min(pbits - pbits_all, 6); }
 
 __device__ inline unsigned long long to_fixed(float v, double scale) {
   return (unsigned long long)__double2ll_rn((double)v * scale);
 }
 
-// The same for values below 2^51 (pbits <= 45 where chunks are routed), in sums: adding 1.5 * 2^52 rounds to a whole number,
+// The same for values below 2^51 (where chunks are routed: pbits of a call <= 45, of a workgroup <= 50), in sums: adding 1.5 * 2^52 rounds to a whole number,
 // which the low bits hold; the sum of n of them is too large by n times this constant.
 constexpr double kFixedMagic = 6755399441055744.0;
 __device__ inline unsigned long long fixed_raw(float v, double scale) {
@@ -838,7 +840,7 @@ __global__ __launch_bounds__(kAccThreads, 4) void k_embed_accum(EmbedArgs a, Acc
   const int64_t slot0 = (int64_t)b * k.R() + part * S;
   if (slot0 >= a.m_size) return;
   const uint32_t largest = FIXED ? fs->absmax_bits : 0u;          // (asked for with the cursors)
-  const uint32_t count = min(cursor[b], k.cap), spilled = min(cursor[k.nb], k.spill_cap);
+  const uint32_t asked = cursor[b], count = min(asked, k.cap), spilled = min(cursor[k.nb], k.spill_cap);
   const uint32_t nseg = k.segments(count);
   if (seg >= nseg) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -859,7 +861,7 @@ __global__ __launch_bounds__(kAccThreads, 4) void k_embed_accum(EmbedArgs a, Acc
   if constexpr (FIXED) {
     if constexpr (SAMPLED) {
       const uint32_t bits = __builtin_amdgcn_readfirstlane(largest);
-      const int own = local_pbits(count + spilled), spare = local_spare(own, pbits);
+      const int own = local_pbits(asked), spare = local_spare(own, pbits);
       scale = uniform(fixed_scale(bits, a.lambda, own - spare));
       pbits = own;
       limit = sample_limit(bits, a.lambda, spare);
