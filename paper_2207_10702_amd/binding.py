@@ -63,8 +63,9 @@ _lib = None
 _call = None              # the module of csrc/roast_call.cpp, once the library is loaded
 
 
-def _connect(lib):
-    """The compiled form of the calls below, on the library that has been loaded; None without one (torch is not there)."""
+def _connect(lib, source=None):
+    """The compiled form of the calls below, on the library that has been loaded; None without one (torch is not there).
+    source: what knows the current device and stream, torch._C."""
     try:
         import torch
     except ImportError:
@@ -80,7 +81,7 @@ def _connect(lib):
     spec.loader.exec_module(module)
     names = ("roast_mm_fwd_ws", "roast_mm_bwd_dx_ws", "roast_mm_bwd_dM", "roast_embed_fwd", "roast_embed_bwd", "roast_embed_bag_fwd",
              "roast_embed_bag_bwd", "roast_optim_step", "roast_m_shadow_bytes", "roast_m_planes_bytes", "roast_m_shadow_bf16", "roast_m_planes_bf16")
-    module.connect(torch._C, *(C.cast(getattr(lib, n), C.c_void_p).value for n in names))
+    module.connect(source or torch._C, *(C.cast(getattr(lib, n), C.c_void_p).value for n in names))
     return module
 
 

@@ -105,7 +105,11 @@ bool current_stream(void** s) {
 bool number(PyObject* o, int* v) {
   if (!PyLong_CheckExact(o)) return false;
   const long x = PyLong_AsLong(o);
-  if (x != (int)x) { PyErr_Clear(); return false; }
+  if (x == -1 && PyErr_Occurred()) {     // (beyond a long)
+    PyErr_Clear();
+    return false;
+  }
+  if (x != (int)x) return false;
   *v = (int)x;
   return true;
 }

@@ -88,3 +88,33 @@ def test_the_same_errors(roast, case):
     assert err.value.status == roast.ROAST_ERR_WORKSPACE and "roast_mm_bwd_dM" in str(err.value)
     with pytest.raises(ValueError, match="bag_offsets"):
         roast.roast_embed_bag_fwd(e, t["rows"], t["tables"], t["off"].int(), t["M"], torch.zeros((I // 6, 2 * Z), device="cuda"))
+
+
+class Recorded:
+    """torch._C as far as the compiled form asks it, every question noted."""
+    def __init__(self):
+        self.asked = []
+
+    def _cuda_getDevice(self):
+        self.asked.append("device")
+        return torch._C._cuda_getDevice()
+
+    def _cuda_getCurrentRawStream(self, device):
+        self.asked.append("stream")
+        return torch._C._cuda_getCurrentRawStream(device)
+
+
+@pytest.mark.parametrize("mode", [2 ** 31, -2 ** 31 - 1, 2 ** 40, 2 ** 63, 2 ** 70, -2 ** 70])
+def test_a_mode_beyond_an_int_ends_the_checks(roast, case, monkeypatch, mode):
+    """Nothing after it is called, least of all with the interpreter's error pending; the Python form then takes it as ctypes does."""
+    d, e, t = case
+    recorded = Recorded()
+    monkeypatch.setattr(roast, "_call", roast._connect(roast.load(), recorded))
+    dM = torch.zeros(MS, device="cuda")
+    try:
+        assert roast._call.mm_bwd_dM(d, t["X"], t["dY"], dM, 0, None) == 0 and recorded.asked == ["device", "stream"]
+        assert roast._call.mm_bwd_dM(d, t["X"], t["dY"], dM, mode, None) is None
+        assert roast._call.embed_bwd(e, t["rows"], t["tables"], t["g"], dM, mode, None) is None
+        assert recorded.asked == ["device", "stream"]
+    finally:
+        roast._connect(roast.load())
