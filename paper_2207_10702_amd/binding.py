@@ -81,7 +81,7 @@ def _connect(lib, source=None):
     spec.loader.exec_module(module)
     names = ("roast_mm_fwd_ws", "roast_mm_bwd_dx_ws", "roast_mm_bwd_dM", "roast_embed_fwd", "roast_embed_bwd", "roast_embed_bag_fwd",
              "roast_embed_bag_bwd", "roast_optim_step", "roast_m_shadow_bytes", "roast_m_planes_bytes", "roast_m_shadow_bf16", "roast_m_planes_bf16")
-    module.connect(source or torch._C, *(C.cast(getattr(lib, n), C.c_void_p).value for n in names))
+    module.connect(source or torch._C, RoastMMDesc, RoastEmbedDesc, RoastOptimDesc, *(C.cast(getattr(lib, n), C.c_void_p).value for n in names))
     return module
 
 

@@ -31,6 +31,10 @@ struct Library {
 };
 Library lib{};
 PyObject *get_device = nullptr, *get_stream = nullptr;   // torch._C._cuda_getDevice, _cuda_getCurrentRawStream
+PyObject* classes[3] = {};                               // the descriptors' ctypes structures, see index_of
+constexpr int index_of(const roast_mm_desc*) { return 0; }
+constexpr int index_of(const roast_embed_desc*) { return 1; }
+constexpr int index_of(const roast_optim_desc*) { return 2; }
 
 constexpr long kNothingDone = -1;
 
@@ -77,15 +81,16 @@ bool code(const at::Tensor& t, roast_dtype* dt) {
   *dt = t.scalar_type() == at::kFloat ? ROAST_F32 : ROAST_BF16;
   return true;
 }
-// A descriptor: a ctypes structure of this size
+// A descriptor: binding.py's structure for it, or one derived from that, as ctypes takes it
 template <typename D>
 bool descriptor(PyObject* o, D* d) {
   Py_buffer b;
+  if (!PyObject_TypeCheck(o, reinterpret_cast<PyTypeObject*>(classes[index_of(d)]))) return false;
   if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) {
     PyErr_Clear();
     return false;
   }
-  const bool ok = b.len == (Py_ssize_t)sizeof(D);
+  const bool ok = b.len >= (Py_ssize_t)sizeof(D);      // (a derived structure may be longer)
   if (ok) memcpy(d, b.buf, sizeof(D));
   PyBuffer_Release(&b);
   return ok;
@@ -239,16 +244,20 @@ PyObject* call(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return PyLong_FromLong(st);
 }
 
-// torch._C, then the addresses of the library's functions in the order of Library
+// torch._C, the descriptors' classes, then the addresses of the library's functions in the order of Library
 PyObject* connect(PyObject*, PyObject* const* a, Py_ssize_t n) {
   constexpr Py_ssize_t count = sizeof(Library) / sizeof(void*);
-  if (n != 1 + count) {
-    PyErr_SetString(PyExc_TypeError, "connect: torch._C and the addresses of the library's functions");
+  if (n != 4 + count || !PyType_Check(a[1]) || !PyType_Check(a[2]) || !PyType_Check(a[3])) {
+    PyErr_SetString(PyExc_TypeError, "connect: torch._C, the classes of the descriptors and the addresses of the library's functions");
     return nullptr;
   }
   void* f[count];
   for (Py_ssize_t i = 0; i < count; ++i)
-    if (f[i] = PyLong_AsVoidPtr(a[1 + i]); PyErr_Occurred()) return nullptr;
+    if (f[i] = PyLong_AsVoidPtr(a[4 + i]); PyErr_Occurred()) return nullptr;
+  for (int i = 0; i < 3; ++i) {
+    Py_INCREF(a[1 + i]);
+    Py_XSETREF(classes[i], a[1 + i]);
+  }
   Py_XSETREF(get_stream, nullptr);
   Py_XSETREF(get_device, PyObject_GetAttrString(a[0], "_cuda_getDevice"));
   if (!get_device) return nullptr;

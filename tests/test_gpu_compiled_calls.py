@@ -1,5 +1,7 @@
 """The compiled form of the Python layer's calls: the results of the Python form (which a call with an explicit stream takes), the same
 errors, and anything but a plain tensor left to the Python form."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -118,3 +120,23 @@ def test_a_mode_beyond_an_int_ends_the_checks(roast, case, monkeypatch, mode):
         assert recorded.asked == ["device", "stream"]
     finally:
         roast._connect(roast.load())
+
+
+def test_a_descriptor_is_its_own_structure(roast, case):
+    """A buffer of its length is none, nor a structure of another name with the same fields; one derived from it is, as for ctypes."""
+    d, e, t = case
+    o = roast.optim_desc(roast.ROAST_OPT_SGD, 0.1)
+    Y, out, dM = torch.zeros((I, O), device="cuda"), torch.zeros((I, 2 * Z), device="cuda"), torch.zeros(MS, device="cuda")
+    forms = [(d, lambda x: roast._call.mm_fwd(x, t["X"], t["M"], Y, None, None)), (e, lambda x: roast._call.embed_fwd(x, t["rows"], t["tables"], t["M"], out)),
+             (o, lambda x: roast._call.optim_step(x, t["M"].clone(), dM, None, None, None))]
+    for desc, call in forms:
+        assert call(desc) == 0
+        lookalike = type("Lookalike", (C.Structure,), {"_fields_": type(desc)._fields_})
+        derived = type("Derived", (type(desc),), {"_fields_": [("note", C.c_int64)]})
+        for no in (bytes(desc), bytearray(desc), np.frombuffer(bytes(desc), dtype=np.uint8), lookalike.from_buffer_copy(desc), None, C.byref(desc)):
+            assert call(no) is None
+        assert call(derived.from_buffer_copy(bytes(desc) + bytes(8))) == 0
+        for other, _ in forms:
+            assert other is desc or call(other) is None
+    with pytest.raises(AttributeError):                           # as without the compiled form
+        roast.roast_mm_fwd(bytes(d), t["X"], t["M"], Y)
