@@ -8,6 +8,7 @@ fallback: if the library has not been built, loading fails.
 import ctypes as C
 import functools
 import os
+import warnings
 from typing import Dict, Optional, Tuple
 
 import numpy as np
@@ -64,7 +65,8 @@ _call = None              # the module of csrc/roast_call.cpp, once the library 
 
 
 def _connect(lib, source=None):
-    """The compiled form of the calls below, on the library that has been loaded; None without one (torch is not there).
+    """The compiled form of the calls below, on the library that has been loaded; None without one: torch is not there, or
+    the file is missing or was built for other sources or another torch, and cannot be built here.  The Python form then does all of them.
     source: what knows the current device and stream, torch._C."""
     try:
         import torch
@@ -73,15 +75,20 @@ def _connect(lib, source=None):
     if not hasattr(torch._C, "_cuda_getCurrentRawStream"):
         return None
     import importlib.util
-    if not os.path.exists(CALL_PATH):
-        from . import build as _build
-        _build._compile_call()
-    spec = importlib.util.spec_from_file_location("_roast_call", CALL_PATH)
-    module = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(module)
-    names = ("roast_mm_fwd_ws", "roast_mm_bwd_dx_ws", "roast_mm_bwd_dM", "roast_embed_fwd", "roast_embed_bwd", "roast_embed_bag_fwd",
-             "roast_embed_bag_bwd", "roast_optim_step", "roast_m_shadow_bytes", "roast_m_planes_bytes", "roast_m_shadow_bf16", "roast_m_planes_bf16")
-    module.connect(source or torch._C, RoastMMDesc, RoastEmbedDesc, RoastOptimDesc, *(C.cast(getattr(lib, n), C.c_void_p).value for n in names))
+    from . import build as _build
+    try:
+        if not _build.call_is_current(CALL_PATH):
+            _build.compile_call(CALL_PATH)
+        spec = importlib.util.spec_from_file_location("_roast_call", CALL_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        names = ("roast_mm_fwd_ws", "roast_mm_bwd_dx_ws", "roast_mm_bwd_dM", "roast_embed_fwd", "roast_embed_bwd", "roast_embed_bag_fwd",
+                 "roast_embed_bag_bwd", "roast_optim_step", "roast_m_shadow_bytes", "roast_m_planes_bytes", "roast_m_shadow_bf16", "roast_m_planes_bf16")
+        module.connect(source or torch._C, RoastMMDesc, RoastEmbedDesc, RoastOptimDesc, *(C.cast(getattr(lib, n), C.c_void_p).value for n in names))
+    except Exception as e:
+        warnings.warn(f"{CALL_PATH} cannot be used ({e}): calls go through ctypes, 2 to 4 us slower; build it with python -m paper_2207_10702_amd.build",
+                      RuntimeWarning, stacklevel=3)
+        return None
     return module
 
 

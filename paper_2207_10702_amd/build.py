@@ -1,8 +1,10 @@
 """Build in-tree: the HIP library paper_2207_10702_amd/libroast_hip.so (gfx950 only) and the Python layer's _roast_call.so."""
+import hashlib
 import os
 import subprocess
 import sys
 import sysconfig
+import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -30,20 +32,48 @@ def _compile(src: str) -> str:
     return obj
 
 
-def _compile_call(_=None) -> None:
+def call_stamp() -> str:
+    """What a build of roast_call.cpp is for: its source, this Python and this torch, whose structures it reads."""
+    import torch
+    h = hashlib.sha256(f"{sys.version} {torch.__version__}".encode())
+    for path in (os.path.join(CSRC, "roast_call.cpp"), os.path.join(ROOT, "include", "roast.h")):
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return "roast_call for " + h.hexdigest()[:32]
+
+
+def call_is_current(path: str) -> bool:
+    if not os.path.exists(path):
+        return False
+    if not os.path.exists(os.path.join(CSRC, "roast_call.cpp")):
+        return True                            # (nothing to compare with)
+    with open(path, "rb") as f:
+        return call_stamp().encode() in f.read()
+
+
+def compile_call(path: str = CALL) -> None:
+    """Written beside its place and then moved there: another process finds a whole file or none."""
     import torch
     root = torch.__path__[0]
     inc, lib = os.path.join(root, "include"), os.path.join(root, "lib")
-    subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
-                    "-I" + os.path.join(ROOT, "include"), "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
-                    "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "roast_call.cpp"), "-o", CALL,
-                    "-L" + lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"], check=True)
+    fd, part = tempfile.mkstemp(prefix="_roast_call.", suffix=".so", dir=os.path.dirname(path))
+    os.close(fd)
+    try:
+        subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+                        f'-DROAST_CALL_STAMP="{call_stamp()}"', "-I" + os.path.join(ROOT, "include"), "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+                        "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "roast_call.cpp"), "-o", part,
+                        "-L" + lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"], check=True)
+        os.chmod(part, 0o755)
+        os.replace(part, path)
+    except BaseException:
+        os.unlink(part)
+        raise
 
 
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
-        call = ex.submit(_compile_call)
+        call = ex.submit(compile_call)
         objs = list(ex.map(_compile, SOURCES))
         call.result()
     subprocess.run([_hipcc(), "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB, *objs], check=True)

@@ -12,6 +12,9 @@
 
 #include "roast.h"
 
+// (build.py looks for it in the file)
+extern "C" __attribute__((used, visibility("default"))) const char roast_call_stamp[] = ROAST_CALL_STAMP;
+
 namespace {
 
 // functions of the library that binding.py has loaded, by address
