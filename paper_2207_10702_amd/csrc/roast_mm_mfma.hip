@@ -1711,7 +1711,9 @@ static MMPlan find_mm_plan(const MMArgs& a, bool f32, int which, bool copy, bool
 
 roast_status direct_f32(int which, const DirectPlan& d, const MMArgs& a, const float* A, int64_t lda, const float* M, float* C, int64_t ldc, void* ws, hipStream_t s) {
   DirectPlan plan = d;
-  if (plan.parts > 1 && (ldc % 4 != 0 || !aligned16(C))) plan.parts = 1;      // (the sums of the parts are stored 16 bytes at a time)
+  // The sums of the parts are stored 16 bytes at a time.  Other outputs take the block that is best for one part: a large one, chosen for
+  // its parts, leaves most CUs without work (51 x 9088 x 320, rows of 321: 58.7 us in the parts' block, 29.5 in its own).
+  if (plan.parts > 1 && (ldc % 4 != 0 || !aligned16(C))) plan = remembered<DirectPlan>(a, which, true, [&] { return direct_plan(which, false, a, 0); });
   const roast_status st = direct_mm(which, false, plan, a, A, lda, M, nullptr, C, ldc, (float*)ws, s);
   if (st != ROAST_OK || plan.parts == 1) return st;
   KernArgs p{};
