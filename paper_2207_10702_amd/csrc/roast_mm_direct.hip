@@ -32,7 +32,7 @@ struct __attribute__((packed, aligned(4))) Floats {
 
 constexpr int kWaves = 8;
 constexpr int kTable = 2048;             // tile-table entries (8 bytes each) in LDS
-constexpr int64_t kMaxBlocks = 0xffffffffll / (64 * kWaves);   // of a launch, whose threads are counted in 32 bits
+constexpr int64_t kMaxBlocks = 0xffffffffll / (64 * kWaves) / 8 * 8;   // of a launch, whose threads are counted in 32 bits
 
 struct DirectArgs {
   MMArgs a;
@@ -48,6 +48,7 @@ struct DirectArgs {
   int nbx, nby;                          // column, row blocks
   int parts;                             // of the contraction (bf16: of 64 x 64 blocks alone), whose partial outputs go to G, [part][rows][columns]
   float* G;
+  bool eighths;                          // (bf16, 64 x 64 blocks, no copy of M) how the blocks go to the XCDs, see direct_mm
 };
 
 template <typename V, typename T>
@@ -76,8 +77,19 @@ __global__ __launch_bounds__(64 * kWaves, MI * NJ > 8 ? 2 : 4) void k_mm_direct(
   const int K = DX ? (int)a.O : (int)a.H, N = DX ? (int)a.H : (int)a.O, I = (int)a.I;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, g = lane >> 4;
-  const int plane = (int)(blockIdx.x / (unsigned)p.nbx), bx = (int)blockIdx.x - plane * p.nbx;
-  const int bz = p.parts > 1 ? plane / p.nby : 0, by = plane - bz * p.nby;
+  int bx, by, bz;
+  if (BF && !SH && MI * NJ == 16 && p.eighths) {
+    const int plane = p.nbx * p.nby, total = plane * p.parts, chunk = (total + 7) / 8, t = ((int)blockIdx.x & 7) * chunk + ((int)blockIdx.x >> 3);
+    if (((int)blockIdx.x >> 3) >= chunk || t >= total) return;    // whole workgroup leaves before any barrier
+    bz = t / plane;
+    bx = (t - bz * plane) / p.nby;
+    by = t - bz * plane - bx * p.nby;
+  } else {
+    const int plane = (int)(blockIdx.x / (unsigned)p.nbx);
+    bx = (int)blockIdx.x - plane * p.nbx;
+    bz = p.parts > 1 ? plane / p.nby : 0;
+    by = plane - bz * p.nby;
+  }
   const int m0 = by * BM, n0 = bx * BN;
   // (parts: of a contraction whose length is a multiple of 64, in whole 64s)
   const int u0 = p.parts > 1 ? 64 / KU * (K / 64 * bz / p.parts) : 0;
@@ -295,7 +307,7 @@ roast_status launch_one(const DirectArgs& p, hipStream_t s) {
   const int64_t blocks = (int64_t)p.nby * p.nbx * p.parts;   // (direct_plan: at most kMaxBlocks)
   constexpr size_t lds = std::max<size_t>((size_t)kTable * 8, (size_t)kWaves * std::min(16 * MI * 16 * NJ, 2048) * 4);
   static_assert(lds <= 64 * 1024, "LDS without an attribute");
-  hipLaunchKernelGGL((k_mm_direct<T, SH, DX, MI, NJ>), dim3((unsigned)blocks), dim3(64 * kWaves), lds, s, p);
+  hipLaunchKernelGGL((k_mm_direct<T, SH, DX, MI, NJ>), dim3((unsigned)(p.eighths ? cdiv(blocks, 8) * 8 : blocks)), dim3(64 * kWaves), lds, s, p);
   return hip_status(hipGetLastError());
 }
 
@@ -411,6 +423,10 @@ roast_status direct_mm(int which, bool bf16, const DirectPlan& d, const MMArgs& 
   auto mu = [](int64_t z) { return (uint32_t)(((1ull << 32) + (uint64_t)z - 1) / (uint64_t)z); };
   p.mu1 = mu(a.Z1); p.mu2 = mu(a.Z2);
   p.nbx = (int)cdiv(which ? a.H : a.O, 16 * d.nj); p.nby = (int)cdiv(a.I, 16 * d.mi); p.parts = d.parts; p.G = G;
+  // Workgroups go to the 8 XCDs round-robin.  Blocks by rows, columns fastest, read the fp32 weights of an M beyond an XCD's L2 from the memory-side cache once for each row of
+  // blocks: there XCD j takes the j-th eighth of the blocks, rows fastest, and they pass through its L2 once (184 x 6336 x 9024 over 9.6 Mi slots 155 -> 92 us, 173 x 7296 x 10880
+  // over 2.1 Mi 143 -> 112).  For a smaller M that gains nothing and the divisions cost 0.3 us (6.5 and 6.8).
+  p.eighths = bf16 && !M_bf16 && d.mi == 4 && d.nj == 4 && p.nby > 1 && a.m_size > (1 << 20);
   return which ? launch_variant<true>(bf16, d.mi, d.nj, p, s) : launch_variant<false>(bf16, d.mi, d.nj, p, s);
 }
 

@@ -81,3 +81,15 @@ def test_an_infinity_stays_in_its_row(roast, which, I, K, N):
     assert torch.all(R[[3, I - 1]] == float("inf"))
     R[[3, I - 1]] = 0
     assert torch.all(torch.isfinite(R))
+
+
+@pytest.mark.parametrize("case", [
+    (FWD, 524, 1984, 1408, 64, 64, 1 << 20, 1),        # without a copy: rows of blocks one after the other
+    (FWD, 524, 1984, 1408, 64, 64, (1 << 20) + 1, 1),  # by eighths: 198 blocks, the last eighth two short
+    (FWD, 65, 4288, 576, 32, 32, (1 << 20) + 1, 7),    # 126
+    (FWD, 130, 3200, 704, 96, 96, (1 << 20) + 1, 5),   # 165
+    (DX, 129, 6656, 448, 64, 64, (1 << 20) + 1, 9),
+])
+def test_blocks_by_eighths(roast, case):
+    """A call without a copy of an M beyond the L2 deals its blocks to the XCDs as one with a copy does."""
+    test_blocks_through_lds_match_oracle(roast, case, 0)
