@@ -400,12 +400,15 @@ static double ring_us(int which, int parts, const MMArgs& a, bool copy) {
 }
 
 // The best number of parts of those blocks for a call that takes copy_us, or nocopy_us without a copy of M, on other kernels: where a call with a copy is 8 % faster
-// for it and one without, which has to give the same sums, no more than 10 % slower.  (mi == 0: none.)
+// for it and one without, which has to give the same sums, no more than 10 % slower by the model.  Two rounds at most: in a third (60 products of
+// 8500 to 12000 indices and 513 to 620 workgroups) calls without a copy took 1.04 to 1.43 times as long as on other kernels, those with one 0.76 to 1.30 times.
+// Elsewhere, in draws of 16 to 2048 rows that take these blocks: 690 without a copy 1.18 times faster in the geometric mean, seven of them 5 to 11 % slower; 370 with one 1.40, two 8 and 11 %
+// slower.  (mi == 0: none.)
 DirectPlan ring_plan(int which, const MMArgs& a, int max_parts, double copy_us, double nocopy_us) {
   DirectPlan best{0, 0, 1, copy_us / 1.08};
   if (a.I > 2048 || !ring_ok(which, a) || !direct_ok(a, true, which == 1, 64)) return best;
   const int64_t K = which ? a.O : a.H, blocks = cdiv(a.I, 64) * ((which ? a.H : a.O) / 64);
-  for (int parts = 1; parts <= max_parts && (parts == 1 || (K >= 128 * parts && blocks * parts <= 512)); ++parts) {
+  for (int parts = 1; parts <= max_parts && blocks * parts <= 512 && (parts == 1 || K >= 128 * parts); ++parts) {
     const double us = ring_us(which, parts, a, true);
     if (us < best.us && ring_us(which, parts, a, false) <= 1.1 * nocopy_us) best = {4, 4, parts, us};
   }
