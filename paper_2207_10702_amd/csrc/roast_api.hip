@@ -47,6 +47,7 @@ roast_status make_embed_args(const roast_embed_desc* d, int64_t N, EmbedArgs* a)
   a->hash = make_hash_dev(d->hash, d->m_size, d->Z);
   a->bag_off = nullptr;
   a->B = 0;
+  a->bags_each = 0.0;
   return ROAST_OK;
 }
 
@@ -364,6 +365,7 @@ roast_status roast_embed_bag_fwd(const roast_embed_desc* d, int64_t N, int64_t B
   if (!bag_offsets || !M || !out || (N > 0 && (!rows || !table_ids))) return ROAST_ERR_ARG;
   a.bag_off = bag_offsets;
   a.B = B;
+  a.bags_each = N ? (double)B / (double)N : 0.0;
   return embed_bag_fwd_launch(a, rows, table_ids, M, out, (hipStream_t)stream);
 }
 
@@ -386,6 +388,7 @@ roast_status roast_embed_bag_bwd(const roast_embed_desc* d, int64_t N, int64_t B
   if (!rows || !table_ids || !bag_offsets || !dOut || !dM) return ROAST_ERR_ARG;
   a.bag_off = bag_offsets;
   a.B = B;
+  a.bags_each = N ? (double)B / (double)N : 0.0;
   if (mode == ROAST_REDUCE_DETERMINISTIC) {
     const size_t need = embed_det_workspace_bytes(a);
     if (need == 0) return ROAST_ERR_UNSUPPORTED;

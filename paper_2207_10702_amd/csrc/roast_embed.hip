@@ -44,28 +44,33 @@ __device__ inline void for_each_chunk(const EmbedArgs& a, bool walk, uint64_t ta
 // Pooled gradient: the bag of lookup n = the last b with bag_off[b] <= n (bag_off[0] == 0, so one
 // exists; empty bags share their offset with the next one and are skipped by "last").  The result is
 // clamped to [0, B-1] whatever the offsets hold, so a malformed offsets array cannot push a read out
-// of dOut.  What it costs is one wait for memory after the other: first the place where bags of equal sizes have it, then
-// seven places a time (13 waits of a bisection of 8191 bags: 1, or 6 where sizes differ).
-__device__ inline int64_t bag_of(const int64_t* __restrict__ bag_off, int64_t B, int64_t N, int64_t n) {
-  const int64_t guess = min(max((int64_t)(((double)n + 0.5) * ((double)B / (double)N)), (int64_t)0), B - 1);
-  const int64_t at = bag_off[guess], next = bag_off[min(guess + 1, B - 1)];
-  if (at <= n && (next > n || guess == B - 1)) return guess;
-  int64_t lo = 0, hi = B;
+// of dOut.  What it costs is one wait for memory after the other, 13 in a bisection of 8191 bags.  Four places are asked for first: the two where bags of equal
+// sizes have it, which then is all, and one a little to each side, between which bags of about equal sizes have it; the rest is a bisection, of no more places than
+// without them.  Over 100 pooled gradients of 200 to 10^6 lookups, against the bisection alone: bags of equal sizes 1.09 times faster with atomic adds and 1.05 in a fixed order,
+// of random ones 1.00 to 1.05 and 0.99 to 1.02 (a call at worst 0.96).  (A search at seven places a time after a wrong guess was slower than the bisection, 0.84 to 1.0: it asks for more lines.)
+__device__ inline int64_t bag_of(const EmbedArgs& a, int64_t n) {
+  const int64_t* __restrict__ bag_off = a.bag_off;
+  const int64_t B = a.B;
+  const int64_t guess = min(max((int64_t)(((double)n + 0.5) * a.bags_each), (int64_t)0), B - 1), near = (B >> 6) + 4;
+  const int64_t below = max(guess - near, (int64_t)0), above = min(guess + 1 + near, B - 1);
+  const int64_t at = bag_off[guess], next = bag_off[min(guess + 1, B - 1)], at_below = bag_off[below], at_above = bag_off[above];
+  int64_t lo, hi;
+  if (at <= n) {
+    if (next > n || guess == B - 1) return guess;
+    lo = at_above <= n ? above : guess + 1;
+    hi = at_above <= n ? B : above;
+  } else {
+    lo = at_below <= n ? below : 0;
+    hi = at_below <= n ? guess : max(below, (int64_t)1);
+  }
   while (hi - lo > 1) {
-    const int64_t step = (hi - lo + 7) >> 3;
-    int64_t v[7];
-#pragma unroll
-    for (int i = 0; i < 7; ++i) v[i] = bag_off[min(lo + (i + 1) * step, hi - 1)];
-    int below = 0;
-#pragma unroll
-    for (int i = 0; i < 7; ++i) below += lo + (i + 1) * step < hi && v[i] <= n ? 1 : 0;
-    lo += below * step;
-    hi = min(hi, lo + step);
+    const int64_t mid = (lo + hi) >> 1;
+    if (bag_off[mid] <= n) lo = mid; else hi = mid;
   }
   return lo;
 }
 // row of dOut that lookup n takes its gradient from
-__device__ inline int64_t grad_row(const EmbedArgs& a, int64_t n) { return a.bag_off ? bag_of(a.bag_off, a.B, a.N, n) : n; }
+__device__ inline int64_t grad_row(const EmbedArgs& a, int64_t n) { return a.bag_off ? bag_of(a, n) : n; }
 
 // Streaming lookup / direct-atomic gradient.  A wave takes rows_wave lookups (64, fewer in a small call): each lane
 // hashes the chunks of one lookup into the wave's LDS key list (offset | sign bit, 32-bit), then the wave walks the
@@ -702,7 +707,7 @@ __global__ __launch_bounds__(kRouteThreads) void k_embed_route(EmbedArgs a, AccP
   };
   for (int q = tid; q < rows_here; q += kRouteThreads) {
     const int64_t n = n0 + q;
-    if (a.bag_off) s_src[q] = (uint32_t)bag_of(a.bag_off, a.B, a.N, n);
+    if (a.bag_off) s_src[q] = (uint32_t)bag_of(a, n);
     for_each_chunk(a, walk != 0, tables[n], (uint64_t)rows[n], [&](int64_t c, int64_t off, int sgn) {
       s_key[q * C + c] = (uint32_t)off | (sgn < 0 ? 0x80000000u : 0u);
       const uint32_t b = k.bucket((uint32_t)off);

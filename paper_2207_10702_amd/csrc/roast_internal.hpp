@@ -31,6 +31,7 @@ struct EmbedArgs {
   // dOut[n]; bag b covers lookups [bag_off[b], bag_off[b+1]).  nullptr / 0 for per-lookup calls.
   const int64_t* bag_off;
   int64_t B;
+  double bags_each;   // B / N: where to look first
 };
 
 // A plan takes a microsecond or two to find, as long as a third of a small call's host time: each thread keeps
