@@ -658,10 +658,12 @@ __device__ inline uint32_t absmax_of(const vfloat4* __restrict__ v, int64_t firs
   return wave_max(m);
 }
 
-// This thread's piece of a sample of them: a 128-byte line for every eight threads, evenly spaced.
+// This thread's piece of a sample of them: a 128-byte line for every eight threads, evenly spaced, but each a line further on in its share of them: else whole rows to
+// a share would give every line the same columns, and rows whose other columns are larger would start over (N = 262144, D = 128, three quarters of the columns 1000 times
+// as large as the first: 83 -> 58 us).
 __device__ inline vfloat4 sample_of(const vfloat4* __restrict__ v, int64_t first, int64_t end, int threads) {
-  const int64_t i = first + (end - first) / (threads / 8) * (threadIdx.x / 8) + threadIdx.x % 8;
-  return v[min(i, end - 1)];
+  const uint32_t line = threadIdx.x / 8, share = (uint32_t)(end - first) / (uint32_t)(threads / 8);
+  return v[min(first + share * line + (share >= 8u ? line % (share / 8u) * 8u : 0u) + threadIdx.x % 8, end - 1)];
 }
 
 // entry = (chunk number g, key); key = offset | (negative sign << 31).  A workgroup waits in turn for the ids, for the

@@ -24,8 +24,9 @@ def sample(dOut, C):
     rows, top = items // C, np.float32(0)
     for n0 in range(0, N, rows):
         own = np.abs(dOut[n0:n0 + rows].reshape(-1))
+        share = len(own) // 4 // 64               # of a line, in 16 bytes
         for line in range(64):
-            first = 4 * (len(own) // 4 // 64 * line)
+            first = 4 * (share * line + (line % (share // 8) * 8 if share >= 8 else 0))
             top = max(top, own[min(first, len(own) - 4):first + LINE].max())
     return top
 
@@ -110,3 +111,26 @@ def test_scales_are_those_of_the_rule(roast, N, D, Z, m, hot, where):
         dM = torch.zeros(m, device="cuda")
         roast.roast_embed_bwd(d, *args, dM, mode, ws)
         assert np.array_equal(dM.cpu().numpy().view(np.uint32), ref.view(np.uint32))
+
+
+@pytest.mark.parametrize("N,D,Z,m", [(32_768, 128, 32, 1_000_003), (32_768, 256, 64, 500_009), (69_632, 64, 32, 1_000_003), (16_385, 128, 16, 300_007)])
+@pytest.mark.parametrize("part", ["columns", "rows"])
+def test_the_sample_is_of_all_columns_and_rows(roast, N, D, Z, m, part):
+    """Whole rows to a line's share, and only the first columns, or every second row, small: no workgroup has to start over."""
+    rng = np.random.default_rng(N + D)
+    h = wl.draw_hash(rng, use_sign=True, align=1)
+    d = roast.embed_desc(D, Z, m, 1.0, h)
+    rows, tables = rng.integers(0, 1 << 33, N), np.zeros(N, dtype=np.uint32)
+    dOut = rng.standard_normal((N, D)).astype(np.float32)
+    if part == "columns":
+        dOut[:, LINE:] *= np.float32(2.0 ** 30)
+    else:
+        dOut[1::2] *= np.float32(2.0 ** 30)
+    off, sgn = roast.roast_chunk_index_device(d, to_dev(rows), to_dev(tables))
+    ref, _, again = expected(off.cpu().numpy(), sgn.cpu().numpy(), D, Z, m, dOut)
+    assert not again.any()
+    mode = roast.ROAST_REDUCE_DETERMINISTIC
+    ws = torch.randint(0, 256, (roast.roast_embed_bwd_workspace(d, N, mode),), dtype=torch.uint8, device="cuda")
+    dM = torch.zeros(m, device="cuda")
+    roast.roast_embed_bwd(d, to_dev(rows), to_dev(tables), to_dev(dOut), dM, mode, ws)
+    assert np.array_equal(dM.cpu().numpy().view(np.uint32), ref.view(np.uint32))
