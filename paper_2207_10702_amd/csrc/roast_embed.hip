@@ -47,7 +47,7 @@ __device__ inline void for_each_chunk(const EmbedArgs& a, bool walk, uint64_t ta
 // of dOut.  What it costs is one wait for memory after the other, 13 in a bisection of 8191 bags.  Four places are asked for first: the two where bags of equal
 // sizes have it, which then is all, and one a little to each side, between which bags of about equal sizes have it; the rest is a bisection, of no more places than
 // without them.  Over 100 pooled gradients of 200 to 10^6 lookups, against the bisection alone: bags of equal sizes 1.09 times faster with atomic adds and 1.05 in a fixed order,
-// of random ones 1.00 to 1.05 and 0.99 to 1.02 (a call at worst 0.96).  (A search at seven places a time after a wrong guess was slower than the bisection, 0.84 to 1.0: it asks for more lines.)
+// of random ones 1.00 to 1.05 and 0.99 to 1.02 (a call at worst 0.96; 0.88 where a lookup is one chunk and bags differ a thousandfold).  (A search at seven places a time after a wrong guess was slower than the bisection, 0.84 to 1.0: it asks for more lines.)
 __device__ inline int64_t bag_of(const EmbedArgs& a, int64_t n) {
   const int64_t* __restrict__ bag_off = a.bag_off;
   const int64_t B = a.B;
