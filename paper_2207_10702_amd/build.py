@@ -52,14 +52,16 @@ def call_is_current(path: str) -> bool:
 
 
 def compile_call(path: str = CALL) -> None:
-    """Written beside its place and then moved there: another process finds a whole file or none."""
+    """Written beside its place and then moved there: another process finds a whole file or none.  NDEBUG: torch's headers bring a thread-local counter
+    without it, and while a library with thread-local data of which a thread has used none is loaded, glibc before 2.39 looks up every other
+    thread-local variable of that thread the long way (t.is_cuda, t.stride and the like took a third longer)."""
     import torch
     root = torch.__path__[0]
     inc, lib = os.path.join(root, "include"), os.path.join(root, "lib")
     fd, part = tempfile.mkstemp(prefix="_roast_call.", suffix=".so", dir=os.path.dirname(path))
     os.close(fd)
     try:
-        subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+        subprocess.run(["g++", "-O2", "-DNDEBUG", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
                         f'-DROAST_CALL_STAMP="{call_stamp()}"', "-I" + os.path.join(ROOT, "include"), "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
                         "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "roast_call.cpp"), "-o", part,
                         "-L" + lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10"], check=True)

@@ -1,6 +1,7 @@
 """Loading the compiled form of the Python layer's calls: without a usable file, and without what it takes to build one, the library
-loads all the same and its calls go through ctypes; a file of other sources is built anew; no process sees half a file."""
+loads all the same and its calls go through ctypes; a file of other sources is built anew; no process sees half a file; the file has no thread-local data."""
 import os
+import struct
 import subprocess
 import warnings
 
@@ -79,3 +80,15 @@ def test_a_stale_file_is_built_anew_beside_its_place(call_path, monkeypatch):
         warnings.simplefilter("error")
         assert binding._connect(binding.load()) is not None
     assert len(seen) == 1 and os.listdir(os.path.dirname(call_path)) == ["_roast_call.so"]
+
+
+def test_the_file_has_no_thread_local_data():
+    """With some that no thread uses, every use of another library's thread-local data takes longer as long as the file is loaded."""
+    binding.load()
+    with open(binding.CALL_PATH, "rb") as f:
+        elf = f.read()
+    assert elf[:6] == b"\x7fELF\x02\x01"                        # 64 bits, little-endian
+    at, = struct.unpack_from("<Q", elf, 32)                      # program headers: where,
+    size, count = struct.unpack_from("<HH", elf, 54)             # and how many
+    kinds = [struct.unpack_from("<I", elf, at + i * size)[0] for i in range(count)]
+    assert 1 in kinds and 7 not in kinds                         # (PT_LOAD, PT_TLS)
