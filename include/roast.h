@@ -188,10 +188,11 @@ roast_status roast_mm_bwd_dx(const roast_mm_desc* d, roast_dtype dt, int64_t I, 
  *    the fp32 bar of the conventions above.  Short calls, and calls without a
  *    workspace, multiply in fp32 from M itself (Z1, Z2, H and O multiples of 4, H and O below 65536; other shapes without
  *    a workspace run on the vector ALUs).
+ * Short calls of either type may take the workspace too, for the partial outputs of parts of a long contraction.
  * The *_workspace queries return the bytes that these kernels take for these sizes (0: nothing to gain, or a
- * shape the matrix-core kernels do not cover; the plain call is used).  Which kernels a call runs on also depends on
- * what only the call knows (leading dimensions, addresses, a copy of M): a short call is given the bytes and
- * leaves them alone, but they are checked all the same.
+ * shape the matrix-core kernels do not cover; the plain call is used).  Which kernels a call runs on, and whether they use all of
+ * the bytes, some or none, also depends on what only the call knows (leading dimensions, addresses, a copy of M): they are
+ * checked all the same.
  * workspace: NULL (same as the plain call), or a DEVICE buffer, 16-byte aligned, of at least the
  * queried size (else ROAST_ERR_WORKSPACE); its contents are scratch, owned by the caller, and may be
  * reused by the next call on the same stream.  Results are deterministic for a fixed shape.
@@ -247,7 +248,7 @@ typedef struct {
 int roast_mm_wide_blocks(const roast_mm_desc* d, roast_dtype dt, int64_t I, int which, int workspace, roast_mm_blocks* out);
 
 /*
- * The same for the kernels of small calls, which make the whole product in one launch (strip and parts are 1; bf16 with a workspace also in
+ * The same for the kernels of small calls, which make the whole product in one launch (strip and parts are 1; with a workspace also in
  * parts, which a second launch adds up): roast_mm_fwd or roast_mm_bwd_dx, fp32 or bf16 (with a copy of M or without one).  Every call is on the wide blocks, on these, or on neither.
  */
 int roast_mm_direct_blocks(const roast_mm_desc* d, roast_dtype dt, int64_t I, int which, int workspace, roast_mm_blocks* out);
