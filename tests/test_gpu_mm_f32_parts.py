@@ -69,27 +69,30 @@ def test_an_infinity_stays_in_its_row(roast, case):
     assert torch.all(torch.isfinite(R))
 
 
-def best_us(call, runs=30):
+def best_us(*calls, runs=40):
+    """The best time of each, in turn."""
     begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    best = float("inf")
+    best = [float("inf")] * len(calls)
     for _ in range(runs):
-        begin.record()
-        for _ in range(8):
-            call()
-        end.record()
-        end.synchronize()
-        best = min(best, begin.elapsed_time(end) * 1e3 / 8)
+        for k, call in enumerate(calls):
+            begin.record()
+            for _ in range(8):
+                call()
+            end.record()
+            end.synchronize()
+            best[k] = min(best[k], begin.elapsed_time(end) * 1e3 / 8)
     return best
 
 
 @pytest.mark.parametrize("case", [CASES[0], CASES[1], CASES[4]])
 def test_an_output_without_parts_takes_its_own_block(roast, case):
     """Such a call runs on the kernel of one without a workspace, in the same block and the same time.  (The block of the parts takes twice
-    as long in one; best of 30, with a third to spare.)"""
+    as long in one; the best of 40 each, with a third to spare.)"""
     which, I, K, N, Z1, Z2, m = case
     _, h, d, H, O, call, need = setup(roast, case, 1.0)
     A, M, out = torch.randn((I, K), device="cuda"), torch.randn(m, device="cuda"), torch.zeros((I, N + 1), device="cuda")[:, :N]
     ws = torch.empty(need, dtype=torch.uint8, device="cuda")
     plain = call(d, A, M, out).clone()
     assert torch.equal(call(d, A, M, out, ws=ws), plain)
-    assert best_us(lambda: call(d, A, M, out, ws=ws)) < 4 / 3 * best_us(lambda: call(d, A, M, out))
+    with_room, without = best_us(lambda: call(d, A, M, out, ws=ws), lambda: call(d, A, M, out))
+    assert with_room < 4 / 3 * without
